@@ -8,7 +8,6 @@
 //   interpolant of eq. chebcheb.
 // * The map from Chebyshev moments to Lagrange moments used by the moment
 //   kernel: l_a(x) = sum_k gam[a][k] T_k(x/L).
-// * The composite Gauss-Legendre panel rule of the moment kernel.
 // * Per-node degrees (eq. chebcheb with N_k points for node k): the Chebyshev
 //   coefficients of each node's factor, the smallest degree whose dropped
 //   coefficients sum to at most a tolerance, and the truncated K tables.
@@ -21,8 +20,7 @@ namespace tai {
 namespace {
 
 constexpr int kNodeThreads = 256;
-constexpr int kPanelBase = 128;  // threads [128, 128 + kMomOrder) build the panel rule
-constexpr int kXiBase = 160;     // threads [160, 160 + n) build the Chebyshev nodes
+constexpr int kXiBase = 128;     // threads [128, 128 + n) build the Chebyshev nodes
 
 // Legendre P_m and P_{m-1} at x by the three-term recurrence.
 __device__ inline void legendre_pair(int m, double x, double& pm, double& pm1) {
@@ -61,12 +59,6 @@ __device__ inline void nodes_body(double omega, int nq, int n, double L, int kin
     const int k = nq - 1 - tid;  // ascending order
     tb.t[k] = 0.5 * omega * (1.0 + z);
     tb.w[k] = 0.5 * omega * zw;
-  } else if (tid >= kPanelBase && tid < kPanelBase + kMomOrder) {
-    const int i = tid - kPanelBase;
-    double z, zw;
-    gauss_root(kMomOrder, i, z, zw);
-    tb.pz[kMomOrder - 1 - i] = z;
-    tb.pw[kMomOrder - 1 - i] = zw;
   } else if (tid >= kXiBase && tid < kXiBase + n) {
     const int a = tid - kXiBase;
     const double th = (kind == 0) ? M_PI * a / (n - 1) : (2.0 * a + 1.0) * M_PI / (2.0 * n);
@@ -86,6 +78,10 @@ nodes_batch_kernel(const PrepMol* __restrict__ mols, int nq, int n, int kind) {
   nodes_body(m.omega, nq, n, m.L, kind, m.tb);
 }
 
+// Entries of gam written: the n*n map and zeros up to its 256-byte boundary,
+// so that the moment kernel may read whole padded rows.
+__host__ __device__ inline int64_t gam_entries(int n) { return ((int64_t)n * n + 31) / 32 * 32; }
+
 // K tables (nq*n*n entries) followed by the n*n Chebyshev-to-Lagrange map.
 __device__ inline void ktables_body(int nq, int n, int kind, const NodeTables& tb) {
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -97,11 +93,13 @@ __device__ inline void ktables_body(int nq, int n, int kind, const NodeTables& t
     const double dx = tb.xi[a] - tb.xi[b];
     const double t = tb.t[k];
     tb.K[g] = exp(-t * t * dx * dx);
-  } else if (g < nk + (int64_t)n * n) {
+  } else if (g < nk + gam_entries(n)) {
     const int ak = (int)(g - nk);
     const int a = ak / n, k = ak % n;
     double v;
-    if (kind == 0) {
+    if (ak >= n * n) {
+      v = 0.0;
+    } else if (kind == 0) {
       // Lobatto: l_a(u) = sum_k 2/(N c_a c_k) T_k(u_a) T_k(u), N = n-1,
       // c_0 = c_N = 2, other c = 1; T_k(u_a) = cos(pi a k / N)
       const int N = n - 1;
@@ -272,8 +270,7 @@ inline size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 size_t node_tables_bytes(int nq, int n) {
   return align256(sizeof(double) * nq) * 2 + align256(sizeof(double) * n) +
          align256(sizeof(double) * (size_t)nq * n * n) + align256(sizeof(double) * n * n) +
-         align256(sizeof(double) * kMomOrder) * 2 + align256(sizeof(double) * (size_t)nq * n * n) +
-         align256(sizeof(int32_t) * nq);
+         align256(sizeof(double) * (size_t)nq * n * n) + align256(sizeof(int32_t) * nq);
 }
 
 NodeTables carve_node_tables(void* base, int nq, int n) {
@@ -284,8 +281,6 @@ NodeTables carve_node_tables(void* base, int nq, int n) {
   tb.xi = reinterpret_cast<double*>(p); p += align256(sizeof(double) * n);
   tb.K = reinterpret_cast<double*>(p); p += align256(sizeof(double) * (size_t)nq * n * n);
   tb.gam = reinterpret_cast<double*>(p); p += align256(sizeof(double) * n * n);
-  tb.pz = reinterpret_cast<double*>(p); p += align256(sizeof(double) * kMomOrder);
-  tb.pw = reinterpret_cast<double*>(p); p += align256(sizeof(double) * kMomOrder);
   tb.C = reinterpret_cast<double*>(p); p += align256(sizeof(double) * (size_t)nq * n * n);
   tb.nk = reinterpret_cast<int32_t*>(p);
   return tb;
@@ -302,7 +297,7 @@ hipError_t launch_nodes(double omega, int nq, int n, double L, int kind, double 
   hipLaunchKernelGGL(nodes_kernel, dim3(1), dim3(kNodeThreads), 0, s, omega, nq, n, L, kind, tb);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t total = (int64_t)nq * n * n + (int64_t)n * n;
+  const int64_t total = (int64_t)nq * n * n + gam_entries(n);
   const int blocks = (int)((total + 255) / 256);
   hipLaunchKernelGGL(ktables_kernel, dim3(blocks), dim3(256), 0, s, nq, n, kind, tb);
   e = hipGetLastError();
@@ -315,7 +310,7 @@ hipError_t launch_nodes_batch(const PrepMol* mols, int nmol, int nq, int n, int 
   hipLaunchKernelGGL(nodes_batch_kernel, dim3(1, nmol), dim3(kNodeThreads), 0, s, mols, nq, n, kind);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t total = (int64_t)nq * n * n + (int64_t)n * n;
+  const int64_t total = (int64_t)nq * n * n + gam_entries(n);
   const int blocks = (int)((total + 255) / 256);
   hipLaunchKernelGGL(ktables_batch_kernel, dim3(blocks, nmol), dim3(256), 0, s, mols, nq, n, kind);
   e = hipGetLastError();

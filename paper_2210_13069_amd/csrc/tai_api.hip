@@ -831,7 +831,7 @@ int tai_moments_partitioned(tai_ctx* c, const tai_basis* b, const tai_params* p,
   NodeTables tb = tai::carve_node_tables(c->nodes.p, p->nq, p->n);
   hipError_t e;
   {
-    // the node map and the panel rule of the moments do not depend on the box
+    // the node map of the moments does not depend on the box
     Timed tm(c, kStNodes, s);
     e = tai::launch_nodes(p->omega, p->nq, p->n, boxes[nparts - 1], p->nodes, 0.0, tb, s);
   }

@@ -10,20 +10,14 @@ namespace tai {
 
 enum Prec { kFP64 = 0, kFP32 = 1, kBF16X3 = 2, kBF16X6 = 3, kF16X3 = 4 };
 
-// Composite Gauss-Legendre rule used for the 1D moments: the pair's support
-// is split into kMomPanels equal panels of kMomOrder nodes each.
-constexpr int kMomPanels = 4;
-constexpr int kMomOrder = 24;
-
 // Device-resident FP64 tables for one (omega, nq, n, L, nodes).
 struct NodeTables {
   double* t;     // [nq]      Gauss-Legendre nodes on (0, omega)
   double* w;     // [nq]      weights
   double* xi;    // [n]       Chebyshev nodes on [-L, L]
   double* K;     // [nq][n][n] exp(-t_k^2 (xi_a - xi_b)^2)
-  double* gam;   // [n][n]    Chebyshev-to-Lagrange map: l_a(x) = sum_k gam[a][k] T_k(x/L)
-  double* pz;    // [kMomOrder] panel rule nodes on [-1, 1]
-  double* pw;    // [kMomOrder] panel rule weights
+  double* gam;   // [n][n]    Chebyshev-to-Lagrange map: l_a(x) = sum_k gam[a][k] T_k(x/L),
+                 //           zeros up to the next 256-byte boundary
   double* C;     // [nq][n][n] Chebyshev coefficients of each node's factor,
                  //            zero beyond its degree (launch_degrees)
   int32_t* nk;   // [nq]      per-node degree N_k (launch_degrees)
