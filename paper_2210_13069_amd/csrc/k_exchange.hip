@@ -652,28 +652,61 @@ exch_dot_kernel(const double* __restrict__ X, const double* __restrict__ Phi, in
       }
 }
 
-// out[i] = sum_g part[g][i], runs in order
-__global__ void __launch_bounds__(256)
-sum_runs_kernel(const double* __restrict__ part, int nrun, int64_t len, double* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= len) return;
-  double s = 0.0;
-  for (int g = 0; g < nrun; ++g) s += part[(int64_t)g * len + i];
-  out[i] = s;
+// Sums over partial results.  A work group of 256 threads owns COLS
+// consecutive outputs and splits their parts into 256 / COLS runs, one per row
+// of threads; the runs' sums are added in order, so the result does not depend
+// on scheduling.  What bounds it is memory, and with a thread per output the
+// latency of a serial chain on a tenth of the chip.  Measured, a thread per
+// output against this: 631 parts of a 92 x 92 matrix 247 -> 10 us (the upper
+// half read once, 21 MB); the partial grids of one J and its node runs, 256 + 32
+// of 32^3 values 72 -> 16 us, 170 + 32 of 48^3 values 71 -> 30 us.
+constexpr int kSumThreads = 256;
+constexpr int kGridCols = 32;   // grid tensors: many outputs, up to 512 parts
+constexpr int kDotCols = 8;     // pair matrices: few outputs, up to 1024 parts
+
+template <int COLS>
+__device__ inline double sum_column(const double* __restrict__ col, int nparts, int64_t stride, bool in) {
+  constexpr int ROWS = kSumThreads / COLS;
+  __shared__ double s_sum[ROWS][COLS];
+  const int c = threadIdx.x % COLS, r = threadIdx.x / COLS;
+  const int per = (nparts + ROWS - 1) / ROWS;
+  const int g0 = r * per, g1 = min(nparts, g0 + per);
+  double v = 0.0;
+  if (in) {
+#pragma unroll 8
+    for (int g = g0; g < g1; ++g) v += col[(int64_t)g * stride];
+  }
+  s_sum[r][c] = v;
+  __syncthreads();
+  double t = 0.0;
+  if (r == 0) {
+#pragma unroll
+    for (int q = 0; q < ROWS; ++q) t += s_sum[q][c];
+  }
+  return t;   // valid in row 0
 }
 
-// K(mu, nu) = 2 (2/sqrt(pi)) sum_s part[s][mu][nu], slices in order.
-__global__ void __launch_bounds__(256)
-exch_dot_sum_kernel(const double* __restrict__ part, int nsplit, int nb, double* __restrict__ Kx) {
+// out[y][i] = sum_g part[y][g][i], y = blockIdx.y
+__global__ void __launch_bounds__(kSumThreads)
+sum_parts_kernel(const double* __restrict__ part, int nparts, int64_t len, double* __restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * kGridCols + threadIdx.x % kGridCols;
+  const double t = sum_column<kGridCols>(part + (int64_t)blockIdx.y * nparts * len + i, nparts, len, i < len);
+  if (i < len && threadIdx.x < kGridCols) out[(int64_t)blockIdx.y * len + i] = t;
+}
+
+// K(mu, nu) = K(nu, mu) = scale sum_s part[s][mu][nu], mu <= nu (the entries
+// of the upper tiles).
+__global__ void __launch_bounds__(kSumThreads)
+exch_dot_sum_kernel(const double* __restrict__ part, int nsplit, int nb, double scale, double* __restrict__ Kx) {
   const int64_t nn = (int64_t)nb * nb;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nn) return;
-  // both (mu, nu) and (nu, mu) take the entry of the upper tiles
+  const int64_t i = (int64_t)blockIdx.x * kDotCols + threadIdx.x % kDotCols;
   const int64_t mu = i / nb, nu = i - mu * nb;
-  const int64_t src = mu <= nu ? i : nu * nb + mu;
-  double s = 0.0;
-  for (int k = 0; k < nsplit; ++k) s += part[(int64_t)k * nn + src];
-  Kx[i] = 2.0 * kTwoOverSqrtPi * s;
+  const bool in = i < nn && mu <= nu;
+  const double t = sum_column<kDotCols>(part + i, nsplit, nn, in);
+  if (in && threadIdx.x < kDotCols) {
+    Kx[i] = scale * t;
+    Kx[nu * nb + mu] = scale * t;
+  }
 }
 
 // full pair index -> position in the listed pairs (-1 elsewhere)
@@ -724,6 +757,31 @@ int node_runs(int64_t groups, int nq) {
 
 }  // namespace
 
+void launch_sum_parts(const double* part, int nparts, int64_t len, int batch, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(sum_parts_kernel, dim3(nblk(len, kGridCols), batch), dim3(kSumThreads), 0, s, part, nparts, len,
+                     out);
+}
+
+// Slices of the inner index: enough work groups to fill the device several
+// times over its upper tiles, whole batches, and no more partials than fit.
+int64_t dot_slice(int64_t total, int nb, int64_t part_len) {
+  const int64_t tb64 = (nb + 63) / 64, tiles = tb64 * (tb64 + 1) / 2;   // tiles on and above the diagonal
+  const int64_t fit = part_len / ((int64_t)nb * nb);
+  const int64_t nsplit = std::min<int64_t>({1024, std::max<int64_t>(1, 2048 / tiles), fit});
+  if (nsplit < 1) return 0;
+  return ((total + nsplit - 1) / nsplit + kDK - 1) / kDK * kDK;
+}
+
+hipError_t launch_dot_split(const double* X, const double* Phi, int nb, int norb, int64_t n3, int64_t slice,
+                            double scale, double* part, double* Kx, hipStream_t s) {
+  const int nsplit = (int)(((int64_t)norb * n3 + slice - 1) / slice);
+  const dim3 dg(nblk(nb, 64), nblk(nb, 64), nsplit);
+  hipLaunchKernelGGL(exch_dot_kernel, dg, dim3(256), 0, s, X, Phi, nb, norb, n3, slice, part);
+  hipLaunchKernelGGL(exch_dot_sum_kernel, dim3(nblk((int64_t)nb * nb, kDotCols)), dim3(kSumThreads), 0, s, part, nsplit, nb,
+                     scale, Kx);
+  return hipGetLastError();
+}
+
 hipError_t launch_mode_products(const double* X, int64_t T, int64_t xmod, const double* K, int64_t kstride,
                                 const double* w, int n, int nq, double* T1, int64_t T0, int64_t kstride0,
                                 int nq0, double* Phi, double* part, int64_t part_len, hipStream_t s) {
@@ -757,7 +815,7 @@ hipError_t launch_mode_products(const double* X, int64_t T, int64_t xmod, const 
     hipLaunchKernelGGL((exch_mode0_kernel<3, 10, 2>), mg, dim3(256), 0, s, T1, K, w, n, nq0, out, kstride0);
   else if (NT == 3) hipLaunchKernelGGL((exch_mode0_kernel<3>), mg, dim3(256), 0, s, T1, K, w, n, nq0, out, kstride0);
   else hipLaunchKernelGGL((exch_mode0_kernel<4>), mg, dim3(256), 0, s, T1, K, w, n, nq0, out, kstride0);
-  if (g > 1) hipLaunchKernelGGL(sum_runs_kernel, dim3(nblk(len, 256)), dim3(256), 0, s, part, g, len, Phi);
+  if (g > 1) launch_sum_parts(part, g, len, 1, Phi, s);
   return hipGetLastError();
 }
 
@@ -773,11 +831,8 @@ ExchangeWork exchange_work_plan(int n, int nq, int nb, int norb, bool listed, in
     if (cap > 0) p.tchunk = std::min<int64_t>(p.tchunk, cap);
   }
   const int64_t total = (int64_t)norb * n3;
-  const int64_t tb64 = (nb + 63) / 64, tiles = tb64 * (tb64 + 1) / 2;   // tiles on and above the diagonal
-  int nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(1024, 2048 / tiles));
-  const int64_t slice = ((total + nsplit - 1) / nsplit + kDK - 1) / kDK * kDK;
-  p.nsplit = (int)((total + slice - 1) / slice);
-  p.slice = slice;
+  p.slice = dot_slice(total, nb, INT64_MAX);
+  p.nsplit = (int)((total + p.slice - 1) / p.slice);
   size_t b = 0;
   p.off_X = b; b += align256(8 * (size_t)p.ntensor * n3);
   p.off_Phi = b; b += align256(8 * (size_t)p.ntensor * n3);
@@ -842,11 +897,7 @@ hipError_t launch_exchange(int prec, const double* M, int nb, int64_t npair, con
     if (e != hipSuccess) return e;
   }
   // K = 2 (2/sqrt(pi)) X Phi^T
-  const dim3 dg(nblk(nb, 64), nblk(nb, 64), p.nsplit);
-  hipLaunchKernelGGL(exch_dot_kernel, dg, dim3(256), 0, s, X, Phi, nb, norb, n3, p.slice, part);
-  const int64_t nn = (int64_t)nb * nb;
-  hipLaunchKernelGGL(exch_dot_sum_kernel, dim3(nblk(nn, 256)), dim3(256), 0, s, part, p.nsplit, nb, Kx);
-  return hipGetLastError();
+  return launch_dot_split(X, Phi, nb, norb, n3, p.slice, 2.0 * kTwoOverSqrtPi, part, Kx, s);
 }
 
 }  // namespace tai

@@ -403,6 +403,16 @@ ExchangeWork exchange_work_plan(int n, int nq, int nb, int norb, bool listed, in
 hipError_t launch_mode_products(const double* X, int64_t T, int64_t xmod, const double* K, int64_t kstride,
                                 const double* w, int n, int nq, double* T1, int64_t T0, int64_t kstride0,
                                 int nq0, double* Phi, double* part, int64_t part_len, hipStream_t s);
+// out[y][i] = sum_g part[y][g][i] for y < batch, i < len, in a fixed order
+// (k_exchange.hip).
+void launch_sum_parts(const double* part, int nparts, int64_t len, int batch, double* out, hipStream_t s);
+// Kx[mu][nu] = scale sum_f X(mu, f) Phi(nu, f), f over norb blocks of n3 values
+// (row mu of block j at (j nb + mu) n3), a matrix taken to be symmetric; the
+// inner index runs in slices of dot_slice (0: part_len doubles hold no slice)
+// whose partial matrices, nb^2 each, go to part.
+int64_t dot_slice(int64_t total, int nb, int64_t part_len);
+hipError_t launch_dot_split(const double* X, const double* Phi, int nb, int norb, int64_t n3, int64_t slice,
+                            double scale, double* part, double* Kx, hipStream_t s);
 hipError_t launch_exchange(int prec, const double* M, int nb, int64_t npair, const int32_t* pairs, int n, int nq,
                            const NodeTables& tb, const double* Q, int norb, void* work, const ExchangeWork& p,
                            double* Kx, hipStream_t s);
