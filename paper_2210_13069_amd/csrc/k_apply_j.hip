@@ -21,6 +21,7 @@
 #include "tai_internal.h"
 #include "tai_device.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace tai {
@@ -485,6 +486,14 @@ rho16_kernel(const float* __restrict__ M, const double* __restrict__ Dt, int n, 
   }
 }
 
+// Part y of ny of the a0 values, cut at even values (the pairs of a0 values of
+// the HALF form start at the same places in every split).
+__device__ inline void a0_range(int n, int y, int ny, int& alo, int& ahi) {
+  const int h = (n + 1) / 2;
+  alo = min(n, 2 * (y * h / ny));
+  ahi = min(n, 2 * ((y + 1) * h / ny));
+}
+
 // Inner layout of the split J_p contraction: position pos = nseg a2 + s
 // (segment-minor) holds slice a[s] of Phi(.., a2) on the A side and slice
 // b[s] of m_2(a2) on the B side, zero padded to kc = 32 ceil(nseg n / 32).
@@ -506,7 +515,8 @@ __host__ __device__ inline int j16_kc(int S, int n) {
   return (nseg * n + 31) / 32 * 32;
 }
 
-// Phi split into its slices in the A layout: Ps[a0][a1][kc] (bf16).
+// Phi split into its slices in the A layout: Ps[a0][a1][kc] (bf16), for the
+// grid tensors of one or several spans one after another.
 template <int S>
 __global__ void __launch_bounds__(256)
 phi_split_kernel(const double* __restrict__ Phi, int n, int kc, __bf16* __restrict__ Ps) {
@@ -528,15 +538,25 @@ phi_split_kernel(const double* __restrict__ Phi, int n, int kc, __bf16* __restri
 }
 
 // J_p in split BF16 for 256 pairs per work group of 512 threads (wave w owns
-// the two 16-pair tiles at blockIdx.x*256 + 32 w).  Each lane holds the m_2
+// the two 16-pair tiles at blk*256 + 32 w).  Each lane holds the m_2
 // slices of its pair in the B layout for the whole kernel; per a0 the slab
 // Ps(a0, :, :) is staged in LDS (double-buffered) and X = Phi(a0) m_2 comes
 // out of the matrix cores one 16-row block of a1 at a time, contracted at
-// once with m_1 (FP32) and, per a0, with m_0 (FP64).
+// once with m_1 (FP32) and, per a0, with m_0 (FP64).  All spans in one launch
+// and the a0 values split over grid y, as in jp_spans_kernel: four boxes of
+// 7844 pairs each (n = 40) kept 31 compute units busy four times over.
 template <int NT, int S, int KC>
 __global__ void __launch_bounds__(512, 1)
-jp16_kernel(const float* __restrict__ M, const __bf16* __restrict__ Ps, int n, int64_t npair,
-            double* __restrict__ Jp) {
+jp16_kernel(const float* __restrict__ Mall, const __bf16* __restrict__ Psall, int n, int nspan, Spans sp,
+            double* __restrict__ Jpall, int64_t len) {
+  int z = 0;
+  while (z + 1 < nspan && (int64_t)blockIdx.x >= sp.blk[z + 1]) ++z;
+  const int64_t off = sp.off[z], npair = sp.off[z + 1] - off, blk = (int64_t)blockIdx.x - sp.blk[z];
+  const float* M = Mall + 3 * (int64_t)n * off;
+  const __bf16* Ps = Psall + (int64_t)z * n * n * (32 * KC);
+  double* Jp = Jpall + blockIdx.y * len + off;
+  int alo, ahi;
+  a0_range(n, blockIdx.y, gridDim.y, alo, ahi);
   constexpr int PT = 2;
   constexpr int kc = 32 * KC;
   constexpr int RS = kc + 8;                       // LDS row stride (bf16)
@@ -554,7 +574,7 @@ jp16_kernel(const float* __restrict__ M, const __bf16* __restrict__ Ps, int n, i
   bool pok[PT];
 #pragma unroll
   for (int t = 0; t < PT; ++t) {
-    const int64_t p = (int64_t)blockIdx.x * 256 + wave * 32 + 16 * t + r16;
+    const int64_t p = blk * 256 + wave * 32 + 16 * t + r16;
     pok[t] = p < npair;
     pc[t] = pok[t] ? p : 0;
   }
@@ -636,12 +656,12 @@ jp16_kernel(const float* __restrict__ M, const __bf16* __restrict__ Ps, int n, i
   };
 
   double jacc[PT] = {};
-  load(0);
-  for (int a0 = 0; a0 < n; ++a0) {
+  if (alo < ahi) load(alo);
+  for (int a0 = alo; a0 < ahi; ++a0) {
     __bf16* bufp = s_p[a0 & 1];
     store(bufp);
     __syncthreads();  // slab a0 in LDS; every wave is past slab a0-2 in this buffer
-    if (a0 + 1 < n) load(a0 + 1);
+    if (a0 + 1 < ahi) load(a0 + 1);
     double y[PT] = {};
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
@@ -698,20 +718,28 @@ repeat_weights_kernel(const double* __restrict__ w, int nq, int reps, double sca
 }
 
 // J_p for 256 pairs per work group of 512 threads: wave w owns the two
-// 16-pair tiles at blockIdx.x*256 + 32 w.  Per a0 the slab Phi(a0, :, :) is
-// staged in LDS (double-buffered, the next slab's loads in flight during the
-// MFMAs); X = Phi(a0) m_2 comes out of the matrix cores one 16-row block of
-// a1 at a time and is contracted at once with m_1 and m_0.
-template <class Op, int NT>
+// 16-pair tiles at blk*256 + 32 w.  The rows (a0, a1) of Phi are taken A0P
+// values of a0 at a time: the slab Phi(a0 .. a0 + A0P - 1, :, :) is staged in
+// LDS (double-buffered, the next slab's loads in flight during the MFMAs);
+// X = Phi(a0 ..) m_2 comes out of the matrix cores one block of 16 rows at a
+// time and is contracted at once with m_1 and m_0.
+//   HALF: n <= 16 NT - 8.  Two values of a0 then fill 2 NT - 1 blocks of rows
+// instead of 2 NT, and the inner index stops at 16 NT - 8: at n = 40, 50 MFMAs
+// per pair of a0 values instead of 72, at n = 24 18 instead of 32.  Otherwise
+// one value of a0 per slab, whose weights m_1 take half the registers.
+//   a0 in [alo, ahi): the launch splits the a0 values where the pairs alone
+// leave the chip idle (jp_splits), each part writing its own sums.
+template <class Op, int NT, bool HALF>
 __device__ __forceinline__ void jp_mfma_body(const double* __restrict__ M, const double* __restrict__ Phi, int n,
-                                             int64_t npair, double* __restrict__ Jp, int64_t blk) {
-  constexpr int NP = 16 * NT, NK = NP / 4, PT = 2;
-  constexpr int PS = NP + 1;                        // LDS row stride (doubles)
-  constexpr int SLAB = NP * NP;                     // padded slab values
+                                             int64_t npair, double* __restrict__ Jp, int64_t blk, int alo, int ahi) {
+  constexpr int A0P = HALF ? 2 : 1, RT = HALF ? 2 * NT - 1 : NT, NK = HALF ? 4 * NT - 2 : 4 * NT, PT = 2;
+  constexpr int ROWS = 16 * RT, COLS = 4 * NK;
+  constexpr int PS = COLS + 1;                      // LDS row stride
+  constexpr int SLAB = ROWS * COLS;                 // padded slab values
   constexpr int PER = (SLAB + 511) / 512;           // staged values per thread
   using T = typename Op::T;
   using Acc = typename Op::Acc;
-  __shared__ T s_phi[2][NP * PS];
+  __shared__ T s_phi[2][ROWS * PS];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r16 = lane & 15, kg = lane >> 4;
@@ -729,9 +757,9 @@ __device__ __forceinline__ void jp_mfma_body(const double* __restrict__ M, const
     pc[t] = pok[t] ? p : 0;
   }
   // B fragments m_2(a2 = 4 s + l/16, p) and the weights m_1(a1, p) of this
-  // lane's output rows a1 = 16 i + row_of(l/16, r)
+  // lane's output rows (a0 offset, a1), offset n + a1 = 16 i + row_of(l/16, r)
   T bm[PT][NK];
-  double w1[PT][NT][4];
+  double w1[PT][RT][4];
 #pragma unroll
   for (int t = 0; t < PT; ++t) {
 #pragma unroll
@@ -740,44 +768,50 @@ __device__ __forceinline__ void jp_mfma_body(const double* __restrict__ M, const
       bm[t][st] = (T)((pok[t] && a2 < n) ? M2[(int64_t)a2 * npair + pc[t]] : 0.0);
     }
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int a1 = 16 * i + Op::row_of(kg, r);
+        const int row = 16 * i + Op::row_of(kg, r);
+        const int a1 = HALF && row >= n ? row - n : row;
         w1[t][i][r] = (pok[t] && a1 < n) ? M1[(int64_t)a1 * npair + pc[t]] : 0.0;
       }
   }
 
   double pre[PER];
   auto load = [&](int a0) {
+    const int rows = min(A0P, ahi - a0) * n;        // rows past the a0 range are zero
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int e = threadIdx.x + 512 * i;
-      const int a1 = e / NP, a2 = e % NP;
-      pre[i] = (e < SLAB && a1 < n && a2 < n) ? Phi[a0 * n2 + (int64_t)a1 * n + a2] : 0.0;
+      const int row = e / COLS, a2 = e % COLS;
+      pre[i] = (e < SLAB && row < rows && a2 < n) ? Phi[a0 * n2 + (int64_t)row * n + a2] : 0.0;
     }
   };
   auto store = [&](T* buf) {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int e = threadIdx.x + 512 * i;
-      if (e < SLAB) buf[(e / NP) * PS + (e % NP)] = (T)pre[i];
+      if (e < SLAB) buf[(e / COLS) * PS + (e % COLS)] = (T)pre[i];
     }
   };
 
   double jacc[PT] = {};
-  load(0);
-  for (int a0 = 0; a0 < n; ++a0) {
-    T* buf = s_phi[a0 & 1];
+  if (alo < ahi) load(alo);
+  int par = 0;
+  for (int a0 = alo; a0 < ahi; a0 += A0P, par ^= 1) {
+    T* buf = s_phi[par];
     store(buf);
-    __syncthreads();  // slab a0 in LDS; every wave is past slab a0-2 in this buffer
-    if (a0 + 1 < n) load(a0 + 1);
-    double m0v[PT];
+    __syncthreads();  // this slab in LDS; every wave is past the slab before the last in this buffer
+    if (a0 + A0P < ahi) load(a0 + A0P);
+    double m0v[A0P][PT];
 #pragma unroll
-    for (int t = 0; t < PT; ++t) m0v[t] = pok[t] ? M0[(int64_t)a0 * npair + pc[t]] : 0.0;
-    double y[PT] = {};
+    for (int u = 0; u < A0P; ++u)
 #pragma unroll
-    for (int i = 0; i < NT; ++i) {
+      for (int t = 0; t < PT; ++t)
+        m0v[u][t] = (pok[t] && a0 + u < ahi) ? M0[(int64_t)(a0 + u) * npair + pc[t]] : 0.0;
+    double y[A0P][PT] = {};
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
       Acc X[PT];
 #pragma unroll
       for (int t = 0; t < PT; ++t) X[t] = Acc{0, 0, 0, 0};
@@ -787,13 +821,34 @@ __device__ __forceinline__ void jp_mfma_body(const double* __restrict__ M, const
 #pragma unroll
         for (int t = 0; t < PT; ++t) X[t] = Op::mma(av, bm[t][st], X[t]);
       }
+      // the block's rows belong to one value of a0, or the block holds the
+      // boundary between the two
+      if (!HALF || 16 * i + 15 < n) {
 #pragma unroll
-      for (int t = 0; t < PT; ++t)
+        for (int t = 0; t < PT; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) y[t] += w1[t][i][r] * (double)X[t][r];
+          for (int r = 0; r < 4; ++r) y[0][t] += w1[t][i][r] * (double)X[t][r];
+      } else if (16 * i >= n) {
+#pragma unroll
+        for (int t = 0; t < PT; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) y[A0P - 1][t] += w1[t][i][r] * (double)X[t][r];
+      } else {
+#pragma unroll
+        for (int t = 0; t < PT; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const bool first = 16 * i + Op::row_of(kg, r) < n;
+            const double v = w1[t][i][r] * (double)X[t][r];
+            y[0][t] += first ? v : 0.0;
+            y[A0P - 1][t] += first ? 0.0 : v;
+          }
+      }
     }
 #pragma unroll
-    for (int t = 0; t < PT; ++t) jacc[t] += m0v[t] * y[t];
+    for (int u = 0; u < A0P; ++u)
+#pragma unroll
+      for (int t = 0; t < PT; ++t) jacc[t] += m0v[u][t] * y[u][t];
   }
   // the four lanes l/16 = 0..3 of a column hold partial sums over a1
 #pragma unroll
@@ -805,35 +860,35 @@ __device__ __forceinline__ void jp_mfma_body(const double* __restrict__ M, const
   }
 }
 
-template <class Op, int NT>
-__global__ void __launch_bounds__(512, 1)
-jp_mfma_kernel(const double* __restrict__ M, const double* __restrict__ Phi, int n, int64_t npair,
-               double* __restrict__ Jp) {
-  jp_mfma_body<Op, NT>(M, Phi, n, npair, Jp, blockIdx.x);
-}
-
 // J_p of every span in one launch: work groups blk[z] .. blk[z+1] take the
-// pairs of span z (256 each) against its own Phi (Phi + z n^3).
-template <class Op, int NT>
+// pairs of span z (256 each) against its own Phi (Phi + z n^3); one span is the
+// plain J.  Grid y splits the a0 values; part y's sums go to Jp + y len.
+template <class Op, int NT, bool HALF>
 __global__ void __launch_bounds__(512, 1)
 jp_spans_kernel(const double* __restrict__ M, const double* __restrict__ Phi, int n, int nspan, Spans sp,
-                double* __restrict__ Jp) {
+                double* __restrict__ Jp, int64_t len) {
   int z = 0;
   while (z + 1 < nspan && (int64_t)blockIdx.x >= sp.blk[z + 1]) ++z;
   const int64_t o = sp.off[z];
-  jp_mfma_body<Op, NT>(M + 3 * (int64_t)n * o, Phi + (int64_t)z * n * n * n, n, sp.off[z + 1] - o, Jp + o,
-                       (int64_t)blockIdx.x - sp.blk[z]);
+  int alo, ahi;
+  a0_range(n, blockIdx.y, gridDim.y, alo, ahi);
+  jp_mfma_body<Op, NT, HALF>(M + 3 * (int64_t)n * o, Phi + (int64_t)z * n * n * n, n, sp.off[z + 1] - o,
+                             Jp + blockIdx.y * len + o, (int64_t)blockIdx.x - sp.blk[z], alo, ahi);
 }
 
+// J from the sums over the a0 values of the J_p launch: parts 0 .. nsplit - 1
+// in order, part y at Jp + y npair.
 __global__ void __launch_bounds__(256)
-unpack_kernel(const double* __restrict__ Jp, int nb, int64_t npair, const int32_t* __restrict__ pairs,
+unpack_kernel(const double* __restrict__ Jp, int nsplit, int nb, int64_t npair, const int32_t* __restrict__ pairs,
               double* __restrict__ J) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= npair) return;
   int mu, nu;
   if (!pair_of(pairs, nb, p, mu, nu)) return;
-  J[(int64_t)mu * nb + nu] = Jp[p];
-  J[(int64_t)nu * nb + mu] = Jp[p];
+  double v = Jp[p];
+  for (int y = 1; y < nsplit; ++y) v += Jp[y * npair + p];
+  J[(int64_t)mu * nb + nu] = v;
+  J[(int64_t)nu * nb + mu] = v;
 }
 
 // Pair density of one orbital, D = q q^T folded over the ordered pairs:
@@ -941,14 +996,69 @@ __global__ void __launch_bounds__(256) to_fp32_kernel(const double* __restrict__
   if (i < count) y[i] = (float)x[i];
 }
 
-template <class Op>
-void launch_pair_contraction_jp(const double* M, int n, int npair, const JWork& w, hipStream_t s) {
-  const unsigned jb = nblk(npair, 256);
-  if (n <= 16) hipLaunchKernelGGL((jp_mfma_kernel<Op, 1>), dim3(jb), dim3(512), 0, s, M, w.Phi, n, (int64_t)npair, w.Jp);
-  else if (n <= 32) hipLaunchKernelGGL((jp_mfma_kernel<Op, 2>), dim3(jb), dim3(512), 0, s, M, w.Phi, n, (int64_t)npair, w.Jp);
-  else if (n <= 48) hipLaunchKernelGGL((jp_mfma_kernel<Op, 3>), dim3(jb), dim3(512), 0, s, M, w.Phi, n, (int64_t)npair, w.Jp);
-  else hipLaunchKernelGGL((jp_mfma_kernel<Op, 4>), dim3(jb), dim3(512), 0, s, M, w.Phi, n, (int64_t)npair, w.Jp);
+namespace {
+// Parts the a0 values of a J_p launch over `blocks` work groups are split
+// into: the one whose last round of work groups on the chip (`slots` at a
+// time) wastes least, each further part charged its share of loading the
+// pairs' moments again.  room: how many parts' sums the caller can hold.
+int jp_splits(int64_t blocks, int n, int64_t slots, int64_t room) {
+  int best = 1;
+  double best_t = 1e300;
+  for (int y = 1; y <= 8 && y <= (n + 1) / 2 && y <= room; ++y) {
+    const double t = (double)((blocks * y + slots - 1) / slots) / y * (1.0 + 0.04 * (y - 1));
+    if (t < best_t * (1.0 - 1e-9)) {
+      best_t = t;
+      best = y;
+    }
+  }
+  return best;
 }
+
+// The spans of a J_p launch and where its sums go: one part straight into
+// the pair vector, several into the partial grids of rho (free by then).
+struct JpPlan {
+  Spans sp{};
+  int nspan = 1, splits = 1;
+  int64_t total = 0;
+  double* out = nullptr;
+};
+JpPlan jp_plan(const int64_t* offs, int nspan, int n, int64_t slots, const JWork& w) {
+  JpPlan p;
+  p.nspan = nspan;
+  p.total = offs[nspan];
+  for (int z = 0; z <= nspan; ++z) {
+    p.sp.off[z] = offs[z];
+    p.sp.blk[z] = z == 0 ? 0 : p.sp.blk[z - 1] + nblk(offs[z] - offs[z - 1], 256);
+  }
+  const int64_t room = (int64_t)w.nchunk * n * n * n / (p.total > 0 ? p.total : 1);
+  p.splits = jp_splits(p.sp.blk[nspan], n, slots, room);
+  p.out = p.splits > 1 ? w.rho_part : w.Jp;
+  return p;
+}
+
+// J_p of the spans in FP64 or FP32 and J from it.  By registers three work
+// groups fit on a compute unit up to n = 16, two for n = 25 .. 32, else one.
+template <class Op>
+void launch_jp(const double* M, int n, const int64_t* offs, int nspan, const double* Phi, const int32_t* pairs, int nb,
+               const JWork& w, double* J, hipStream_t s) {
+  const JpPlan p = jp_plan(offs, nspan, n, n <= 16 ? 768 : n > 24 && n <= 32 ? 512 : 256, w);
+  const dim3 g((unsigned)p.sp.blk[nspan], p.splits);
+  auto go = [&](auto nt) {
+    constexpr int NT = decltype(nt)::value;
+    // beyond n = 48 the weights of two a0 values spill
+    if (NT < 4 && n <= 16 * NT - 8)
+      hipLaunchKernelGGL((jp_spans_kernel<Op, NT, (NT < 4)>), g, dim3(512), 0, s, M, Phi, n, nspan, p.sp, p.out,
+                         p.total);
+    else
+      hipLaunchKernelGGL((jp_spans_kernel<Op, NT, false>), g, dim3(512), 0, s, M, Phi, n, nspan, p.sp, p.out, p.total);
+  };
+  if (n <= 16) go(std::integral_constant<int, 1>{});
+  else if (n <= 32) go(std::integral_constant<int, 2>{});
+  else if (n <= 48) go(std::integral_constant<int, 3>{});
+  else go(std::integral_constant<int, 4>{});
+  hipLaunchKernelGGL(unpack_kernel, dim3(nblk(p.total, 256)), dim3(256), 0, s, p.out, p.splits, nb, p.total, pairs, J);
+}
+}  // namespace
 
 namespace {
 template <int NT, int S>
@@ -977,19 +1087,22 @@ void launch_rho16(int prec, const float* M, int n, int npair, const JWork& w, hi
 }
 inline bool rho_split(int prec) { return prec == kBF16X3; }
 
-template <int NT, int S, int KC>
-void launch_jp16_k(const float* M, const __bf16* Ps, int n, int npair, double* Jp, hipStream_t s) {
-  hipLaunchKernelGGL((jp16_kernel<NT, S, KC>), dim3(nblk(npair, 256)), dim3(512), 0, s, M, Ps, n, (int64_t)npair, Jp);
-}
-// J_p in split BF16: Phi cut into its slices, then the contraction; the
-// inner length kc (a multiple of 32) selects the compiled variant.
+// J_p of the spans in split BF16 and J from it: every span's Phi cut into its
+// slices (Ps: one span's slices, or room for all of them), then the
+// contraction; the inner length kc (a multiple of 32) selects the compiled
+// variant.
 template <int S>
-void launch_jp16_s(const float* M, const double* Phi, void* Psv, int n, int npair, double* Jp, hipStream_t s) {
+void launch_jp16(const float* M, int n, const int64_t* offs, int nspan, const double* Phi, void* Psv,
+                 const int32_t* pairs, int nb, const JWork& w, double* J, hipStream_t s) {
   const int kc = j16_kc(S, n);
   __bf16* Ps = static_cast<__bf16*>(Psv);
-  hipLaunchKernelGGL((phi_split_kernel<S>), dim3(n * n), dim3(256), 0, s, Phi, n, kc, Ps);
+  hipLaunchKernelGGL((phi_split_kernel<S>), dim3(nspan * n * n), dim3(256), 0, s, Phi, n, kc, Ps);
+  const JpPlan p = jp_plan(offs, nspan, n, 256, w);
+  const dim3 g((unsigned)p.sp.blk[nspan], p.splits);
   const int NT = (n + 15) / 16, KC = kc / 32;
-#define TAI_JP16(nt, kcc) if (NT == nt && KC == kcc) return launch_jp16_k<nt, S, kcc>(M, Ps, n, npair, Jp, s)
+#define TAI_JP16(nt, kcc)                                                                                              \
+  if (NT == nt && KC == kcc)                                                                                           \
+  hipLaunchKernelGGL((jp16_kernel<nt, S, kcc>), g, dim3(512), 0, s, M, Ps, n, nspan, p.sp, p.out, p.total)
   if constexpr (S == 2) {
     // 3 n rounded up to 32: n <= 16 -> KC <= 2; <= 32 -> <= 3; <= 48 -> <= 5; <= 64 -> <= 6
     TAI_JP16(1, 1); TAI_JP16(1, 2);
@@ -1004,6 +1117,7 @@ void launch_jp16_s(const float* M, const double* Phi, void* Psv, int n, int npai
     TAI_JP16(4, 10); TAI_JP16(4, 11); TAI_JP16(4, 12);
   }
 #undef TAI_JP16
+  hipLaunchKernelGGL(unpack_kernel, dim3(nblk(p.total, 256)), dim3(256), 0, s, p.out, p.splits, nb, p.total, pairs, J);
 }
 
 // the FP32 pair contraction reads an FP32 copy of the moments (in w.M32),
@@ -1038,6 +1152,15 @@ hipError_t launch_rho_phi(int prec, const double* M, int npair, int n, int nq, c
   hipLaunchKernelGGL(repeat_weights_kernel, dim3(nblk(nq, 256)), dim3(256), 0, s, tb.w, nq, 1, kTwoOverSqrtPi, w.wsc);
   return launch_phi_grid(w.rho, tb.K, w.wsc, n, nq, w, w.Phi, s);
 }
+// J_p and J of the spans in the arithmetic prec
+void launch_projection(int prec, const double* M, const float* M32, int n, const int64_t* offs, int nspan,
+                       const double* Phi, void* Ps, const int32_t* pairs, int nb, const JWork& w, double* J,
+                       hipStream_t s) {
+  if (prec == kBF16X6) launch_jp16<3>(M32, n, offs, nspan, Phi, Ps, pairs, nb, w, J, s);
+  else if (prec == kBF16X3) launch_jp16<2>(M32, n, offs, nspan, Phi, Ps, pairs, nb, w, J, s);
+  else if (prec == kFP32) launch_jp<JF32>(M, n, offs, nspan, Phi, pairs, nb, w, J, s);
+  else launch_jp<JF64>(M, n, offs, nspan, Phi, pairs, nb, w, J, s);
+}
 }  // namespace
 
 hipError_t launch_apply_j(int prec, const double* M, int nb, int npair, const int32_t* pairs, int n, int nq,
@@ -1047,16 +1170,12 @@ hipError_t launch_apply_j(int prec, const double* M, int nb, int npair, const in
   convert_moments(prec, M, n, npair, w, s);
   const hipError_t e = launch_rho_phi(prec, M, npair, n, nq, tb, w, s);
   if (e != hipSuccess) return e;
-  if (split_j(prec)) {
-    if (j_slices(prec) == 3) launch_jp16_s<3>(w.M32, w.Phi, w.Ps, n, npair, w.Jp, s);
-    else launch_jp16_s<2>(w.M32, w.Phi, w.Ps, n, npair, w.Jp, s);
-  } else if (prec == kFP32) launch_pair_contraction_jp<JF32>(M, n, npair, w, s);
-  else launch_pair_contraction_jp<JF64>(M, n, npair, w, s);
+  const int64_t whole[2] = {0, npair};
   if (pairs) {
     const int64_t nn = (int64_t)nb * nb;
     hipLaunchKernelGGL(zero_kernel, dim3(nblk(nn, 256)), dim3(256), 0, s, J, nn);
   }
-  hipLaunchKernelGGL(unpack_kernel, dim3(nblk(npair, 256)), dim3(256), 0, s, w.Jp, nb, (int64_t)npair, pairs, J);
+  launch_projection(prec, M, w.M32, n, whole, 1, w.Phi, w.Ps, pairs, nb, w, J, s);
   return hipGetLastError();
 }
 
@@ -1072,8 +1191,8 @@ hipError_t launch_apply_j(int prec, const double* M, int nb, int npair, const in
 // More boxes: rho of all partitions in one launch (the single list's chunk
 // count shared out among them), the mode products of all box pairs at once
 // on the matrix cores with 2/sqrt(pi) folded into the repeated weights, and
-// J_p of all partitions in one launch; the split-BF16 contractions keep a
-// launch per partition.
+// J_p of all partitions in one launch; the split-BF16 rho keeps a launch per
+// partition.
 namespace {
 template <class Op, int A0W, class MT>
 void launch_rho_spans(const MT* M, int n, const Spans& sp, int nspan, int nchunk, const double* Dt, double* part,
@@ -1083,16 +1202,6 @@ void launch_rho_spans(const MT* M, int n, const Spans& sp, int nspan, int nchunk
   else if (n <= 32) hipLaunchKernelGGL((rho_spans_kernel<Op, 2, A0W, MT>), rg, dim3(512), 0, s, M, Dt, n, sp, part);
   else if (n <= 48) hipLaunchKernelGGL((rho_spans_kernel<Op, 3, A0W, MT>), rg, dim3(512), 0, s, M, Dt, n, sp, part);
   else hipLaunchKernelGGL((rho_spans_kernel<Op, 4, 1, MT>), rg, dim3(512), 0, s, M, Dt, n, sp, part);
-}
-template <class Op>
-void launch_jp_spans(const double* M, int n, const Spans& sp, int nspan, const double* Phi, double* Jp,
-                     hipStream_t s) {
-  const unsigned jb = (unsigned)sp.blk[nspan];
-  if (jb == 0) return;
-  if (n <= 16) hipLaunchKernelGGL((jp_spans_kernel<Op, 1>), dim3(jb), dim3(512), 0, s, M, Phi, n, nspan, sp, Jp);
-  else if (n <= 32) hipLaunchKernelGGL((jp_spans_kernel<Op, 2>), dim3(jb), dim3(512), 0, s, M, Phi, n, nspan, sp, Jp);
-  else if (n <= 48) hipLaunchKernelGGL((jp_spans_kernel<Op, 3>), dim3(jb), dim3(512), 0, s, M, Phi, n, nspan, sp, Jp);
-  else hipLaunchKernelGGL((jp_spans_kernel<Op, 4>), dim3(jb), dim3(512), 0, s, M, Phi, n, nspan, sp, Jp);
 }
 }  // namespace
 
@@ -1110,10 +1219,7 @@ hipError_t launch_apply_j_parts(int prec, const double* M, int nb, const int32_t
   hipLaunchKernelGGL(repeat_weights_kernel, dim3(nblk((int64_t)nq * nparts, 256)), dim3(256), 0, s, w, nq, nparts,
                      kTwoOverSqrtPi, wrep);
   Spans sp{};
-  for (int p = 0; p <= nparts; ++p) {
-    sp.off[p] = offs[p];
-    sp.blk[p] = p == 0 ? 0 : sp.blk[p - 1] + nblk(offs[p] - offs[p - 1], 256);
-  }
+  for (int p = 0; p <= nparts; ++p) sp.off[p] = offs[p];
   // chunks per partition: the single list's count shared out, so that the
   // partial grids of all partitions fit where the list's would
   const int pchunk = wk.nchunk / nparts;
@@ -1151,35 +1257,25 @@ hipError_t launch_apply_j_parts(int prec, const double* M, int nb, const int32_t
                                               n, nq, T2_all, nparts, (int64_t)nparts * nq * n2, nparts * nq, Phi_all,
                                               wk.rho_part, (int64_t)wk.nchunk * n3, s);
     if (e != hipSuccess) return e;
-    if (!split_j(prec)) {
-      if (prec == kFP32) launch_jp_spans<JF32>(M, n, sp, nparts, Phi_all, wk.Jp, s);
-      else launch_jp_spans<JF64>(M, n, sp, nparts, Phi_all, wk.Jp, s);
-      hipLaunchKernelGGL(unpack_kernel, dim3(nblk(total, 256)), dim3(256), 0, s, wk.Jp, nb, total, pairs, J);
-      return hipGetLastError();
-    }
-  }
-  for (int p = 0; p < nparts; ++p) {
-    const int64_t cnt = offs[p + 1] - offs[p];
-    if (cnt == 0) continue;
-    if (one) {
-      const hipError_t e = launch_phi_grid(rho_all, Kx, wrep, n, nq, wk, wk.Phi, s);
-      if (e != hipSuccess) return e;
-    }
-    JWork wp = wk;
-    wp.Jp = wk.Jp + offs[p];
-    wp.Phi = one ? wk.Phi : Phi_all + (int64_t)p * n3;
-    if (split_j(prec)) {
-      const float* M32p = wk.M32 + 3 * (int64_t)n * offs[p];
-      if (j_slices(prec) == 3) launch_jp16_s<3>(M32p, wp.Phi, wk.Ps, n, (int)cnt, wp.Jp, s);
-      else launch_jp16_s<2>(M32p, wp.Phi, wk.Ps, n, (int)cnt, wp.Jp, s);
-    } else if (prec == kFP32) {
-      launch_pair_contraction_jp<JF32>(M + 3 * (int64_t)n * offs[p], n, (int)cnt, wp, s);
-    } else {
-      launch_pair_contraction_jp<JF64>(M + 3 * (int64_t)n * offs[p], n, (int)cnt, wp, s);
-    }
-    hipLaunchKernelGGL(unpack_kernel, dim3(nblk(cnt, 256)), dim3(256), 0, s, wp.Jp, nb, cnt, pairs + offs[p], J);
-    const hipError_t e = hipGetLastError();
+  } else {
+    const hipError_t e = launch_phi_grid(rho_all, Kx, wrep, n, nq, wk, Phi_all, s);
     if (e != hipSuccess) return e;
+  }
+  // The slices of every box's Phi go where the slab products of the mode
+  // products were, as many boxes at a time as fit (all of them unless nq = 1
+  // meets a coarse grid); a single box has its own room.
+  const int64_t ps_box = split_j(prec) ? 2 * n2 * j16_kc(j_slices(prec), n) : 0;
+  const int64_t t2_bytes = 8 * n3 * nq * nparts * nparts;
+  const int group = one || ps_box == 0 ? nparts : (int)std::max<int64_t>(1, std::min<int64_t>(nparts, t2_bytes / ps_box));
+  void* Ps = one || group * ps_box > t2_bytes ? wk.Ps : static_cast<void*>(T2_all);
+  for (int p = 0; p < nparts; p += group) {
+    const int g = std::min(group, nparts - p);
+    int64_t sub[kMaxParts + 1];
+    for (int z = 0; z <= g; ++z) sub[z] = offs[p + z] - offs[p];
+    if (sub[g] == 0) continue;
+    const float* M32 = wk.M32 ? wk.M32 + 3 * (int64_t)n * offs[p] : nullptr;
+    launch_projection(prec, M + 3 * (int64_t)n * offs[p], M32, n, sub, g, Phi_all + p * n3, Ps, pairs + offs[p], nb, wk,
+                      J, s);
   }
   return hipGetLastError();
 }
