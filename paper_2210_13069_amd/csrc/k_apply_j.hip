@@ -9,7 +9,7 @@
 //
 // Both pair contractions run on the FP64 matrix cores (v_mfma_f64_16x16x4):
 //  * rho: for each a0, rho_a0 = (c_a0 o M_1) M_2^T with c_a0(q) = Dt_q m_{q,0}(a0),
-//    an n x n product over the pairs.  A work group owns 8*A0W values of a0
+//    an n x n product over the pairs.  A work group owns 8 or 16 values of a0
 //    and one chunk of pairs, stages the chunk's moments in LDS 64 pairs at a
 //    time (loads for the next batch in flight during the MFMAs) and writes an
 //    n^3 partial; the partials are summed in a fixed order, so the result does
@@ -74,30 +74,54 @@ struct JF32 {
   __device__ static int row_of(int kg, int r) { return 4 * kg + r; }
 };
 
-// grid (ceil(n / (8*A0W)), nchunk), 512 threads.  Wave w owns
-// a0 = blockIdx.x*8*A0W + w*A0W + {0..A0W-1} and all (a1, a2) in NT x NT
-// output tiles of 16 x 16 (n padded to 16*NT with zeros).
-// MT: the element type the moments are read in (the FP32 form reads an FP32
-// copy, half the bytes of the staging loads that bound it).
-template <class Op, int NT, int A0W, class MT>
+// Shapes of the rho kernel.  A work group of eight waves owns A0G values of a0
+// and one chunk of pairs; a wave owns A0W values of a0 and all (a1, a2), as
+// RT x NT output tiles of 16 x 16 over the packed rows (a0, a1):
+//   HALF: n <= 16 NT - 8 and A0W = 2.  Two values of a0 fill 2 NT - 1 blocks of
+// rows instead of 2 NT.
+//   KS = 2: waves w and w + 4 share their values of a0 and take half of each
+// batch's pairs, their sums added at the end.  Half the values of a0 per work
+// group: twice the work groups for short pair lists, and no padding to 16
+// values of a0 at n = 24 or 40.
+template <int NT_, int A0W_, bool HALF_, int KS_>
+struct RhoShape {
+  static constexpr int NT = NT_, A0W = A0W_, KS = KS_;
+  static constexpr bool HALF = HALF_;
+  static constexpr int A0G = 8 * A0W / KS;
+  static constexpr int RT = HALF ? 2 * NT - 1 : A0W * NT;
+  static_assert(!HALF || A0W == 2, "HALF packs two values of a0");
+};
+
+// grid (ceil(n / A0G), nchunk), 512 threads (RhoShape; n padded to 16 NT with
+// zeros).  MT: the element type the moments are read in (the FP32 form reads
+// an FP32 copy, half the bytes of the staging loads that bound it).
+//   What bounds it: FP64 (FP32) matrix cores.  Whole J, 16 values of a0 per
+// work group in whole tiles against HALF with KS = 2, FP64: 500500 pairs at
+// n = 40 3395 -> 2634 us (with the projection's HALF form), at n = 24 1090 ->
+// 776 us.  FP32 keeps one value of a0 per wave: its packed form spilled (12
+// orbitals at n = 40 799 -> 874 us), and splitting a batch would change the
+// FP32 sums.
+template <class Op, class Shape, class MT>
 __device__ __forceinline__ void rho_mfma_body(const MT* __restrict__ M, const double* __restrict__ Dt, int n,
                                               int64_t npair, int64_t chunk, double* __restrict__ part) {
+  constexpr int NT = Shape::NT, A0W = Shape::A0W, KS = Shape::KS, RT = Shape::RT;
+  constexpr bool HALF = Shape::HALF;
   constexpr int NP = 16 * NT;                  // padded extent of a1 and a2
-  constexpr int A0G = 8 * A0W;                 // a0 per work group
+  constexpr int A0G = Shape::A0G;              // a0 per work group
   constexpr int ROWS = A0G + 2 * NP;           // staged rows: c (A0G), m1 (NP), m2 (NP)
   constexpr int PER = ROWS * kKB / 512;        // staged values per thread
-  constexpr int CS = A0G + 1, MS = NP + 1;     // LDS row strides (doubles)
+  constexpr int CS = A0G + 1, MS = NP + 1;     // LDS row strides
   using T = typename Op::T;
   using Acc = typename Op::Acc;
   // two LDS buffers: batch b is read from buffer b & 1 while batch b + 1 is
   // stored into the other after the MFMAs, one barrier per batch
-  __shared__ T s_c2[2][kKB * CS];
-  __shared__ T s_m12[2][kKB * MS];
-  __shared__ T s_m22[2][kKB * MS];
+  constexpr int kBuf = kKB * (CS + 2 * MS);
+  __shared__ __align__(16) T s_buf[2 * kBuf];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r16 = lane & 15, kg = lane >> 4;
   const int a0base = blockIdx.x * A0G;
+  const int wa = KS == 2 ? wave & 3 : wave, kh = KS == 2 ? wave >> 2 : 0;   // a0 values, share of the pairs
   const int64_t q0 = (int64_t)blockIdx.y * chunk;
   const int64_t q1 = (q0 + chunk < npair) ? q0 + chunk : npair;
   const MT* M0 = M;
@@ -128,105 +152,144 @@ __device__ __forceinline__ void rho_mfma_body(const MT* __restrict__ M, const do
       pre[i] = (T)v;
     }
   };
-  auto store = [&](int buf) {
+  auto store = [&](T* buf) {
+    T* s_m1 = buf + kKB * CS;
+    T* s_m2 = s_m1 + kKB * MS;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int e = threadIdx.x + 512 * i;
       const int row = e / kKB, qq = e % kKB;
-      if (row < A0G) s_c2[buf][qq * CS + row] = pre[i];
-      else if (row < A0G + NP) s_m12[buf][qq * MS + row - A0G] = pre[i];
-      else s_m22[buf][qq * MS + row - A0G - NP] = pre[i];
+      if (row < A0G) buf[qq * CS + row] = pre[i];
+      else if (row < A0G + NP) s_m1[qq * MS + row - A0G] = pre[i];
+      else s_m2[qq * MS + row - A0G - NP] = pre[i];
     }
   };
+  // row block i of the wave: this lane's a0 (an offset) and a1
+  auto row_a0 = [&](int i, int row) { return HALF ? (row >= n ? 1 : 0) : i / NT; };
+  auto row_a1 = [&](int i, int row) { return HALF ? (row >= n ? row - n : row) : row - 16 * NT * (i / NT); };
 
-  Acc acc[A0W][NT][NT];
-  v4d tot[Op::kSplitSum ? A0W : 1][NT][NT];  // FP64 sums of the FP32 batches
+  Acc acc[RT][NT];
+  v4d tot[Op::kSplitSum ? RT : 1][NT];  // FP64 sums of the FP32 batches
 #pragma unroll
-  for (int a = 0; a < A0W; ++a)
+  for (int i = 0; i < RT; ++i)
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        acc[a][i][j] = Acc{0, 0, 0, 0};
-        if constexpr (Op::kSplitSum) tot[a][i][j] = v4d{0.0, 0.0, 0.0, 0.0};
-      }
+    for (int j = 0; j < NT; ++j) {
+      acc[i][j] = Acc{0, 0, 0, 0};
+      if constexpr (Op::kSplitSum) tot[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
+    }
 
   load(q0);
-  store(0);
+  store(s_buf);
   __syncthreads();
   int buf = 0;
   for (int64_t qb = q0; qb < q1; qb += kKB, buf ^= 1) {
     const bool more = qb + kKB < q1;
     if (more) load(qb + kKB);  // next batch in flight during the MFMAs
-    const T* s_c = s_c2[buf];
-    const T* s_m1 = s_m12[buf];
-    const T* s_m2 = s_m22[buf];
-#pragma unroll 2
-    for (int st = 0; st < kKB / 4; ++st) {
-      const int kk = 4 * st + kg;  // this lane's pair within the batch
-      T bm[NT], am[NT];
+    const T* s_c = s_buf + buf * kBuf;
+    const T* s_m1 = s_c + kKB * CS;
+    const T* s_m2 = s_m1 + kKB * MS;
+#pragma unroll(HALF && NT == 3 ? 1 : 2)   // more spills
+    for (int st = 0; st < kKB / 4 / KS; ++st) {
+      const int kk = 4 * (st + kh * (kKB / 4 / KS)) + kg;  // this lane's pair within the batch
+      T bm[NT];
 #pragma unroll
       for (int j = 0; j < NT; ++j) bm[j] = s_m2[kk * MS + 16 * j + r16];
+      if constexpr (HALF) {
 #pragma unroll
-      for (int i = 0; i < NT; ++i) am[i] = s_m1[kk * MS + 16 * i + r16];
+        for (int i = 0; i < RT; ++i) {
+          const int row = 16 * i + r16;
+          // rows past 2 n read the zeros staged for a1 >= n
+          const T av = s_c[kk * CS + wa * A0W + row_a0(i, row)] * s_m1[kk * MS + row_a1(i, row)];
 #pragma unroll
-      for (int a = 0; a < A0W; ++a) {
-        const T cq = s_c[kk * CS + wave * A0W + a];
+          for (int j = 0; j < NT; ++j) acc[i][j] = Op::mma(av, bm[j], acc[i][j]);
+        }
+      } else {
+        T am[NT];
 #pragma unroll
-        for (int i = 0; i < NT; ++i) {
-          const T av = cq * am[i];
+        for (int i = 0; i < NT; ++i) am[i] = s_m1[kk * MS + 16 * i + r16];
 #pragma unroll
-          for (int j = 0; j < NT; ++j) acc[a][i][j] = Op::mma(av, bm[j], acc[a][i][j]);
+        for (int a = 0; a < A0W; ++a) {
+          const T cq = s_c[kk * CS + wa * A0W + a];
+#pragma unroll
+          for (int i = 0; i < NT; ++i) {
+            const T av = cq * am[i];
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[a * NT + i][j] = Op::mma(av, bm[j], acc[a * NT + i][j]);
+          }
         }
       }
     }
     if constexpr (Op::kSplitSum) {
 #pragma unroll
-      for (int a = 0; a < A0W; ++a)
+      for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int i = 0; i < NT; ++i)
+        for (int j = 0; j < NT; ++j) {
 #pragma unroll
-          for (int j = 0; j < NT; ++j) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) tot[a][i][j][r] += (double)acc[a][i][j][r];
-            acc[a][i][j] = Acc{0, 0, 0, 0};
-          }
+          for (int r = 0; r < 4; ++r) tot[i][j][r] += (double)acc[i][j][r];
+          acc[i][j] = Acc{0, 0, 0, 0};
+        }
     }
     // the other buffer was last read in the previous batch, which every wave
     // finished before the barrier that ended it
-    if (more) store(buf ^ 1);
+    if (more) store(s_buf + (buf ^ 1) * kBuf);
     __syncthreads();
   }
+  auto sums = [&](int i, int j) -> v4d& {
+    if constexpr (Op::kSplitSum) return tot[i][j];
+    else return acc[i][j];
+  };
 
-  // lane l holds column a2 = 16 j + l%16 and rows a1 = 16 i + row_of(l/16, r)
+  if constexpr (KS == 2) {
+    // the upper waves' sums, as many row blocks at a time as the buffers hold
+    constexpr int kFit = (int)(sizeof(T) * 2 * kBuf / (4 * NT * 64 * sizeof(v4d)));
+    constexpr int FIT = kFit < RT ? kFit : RT;
+    static_assert(FIT >= 1, "a row block of four waves fits in the buffers");
+    v4d* s_sum = reinterpret_cast<v4d*>(s_buf);
+#pragma unroll
+    for (int i0 = 0; i0 < RT; i0 += FIT) {
+      if (i0 > 0) __syncthreads();
+      if (kh == 1) {
+#pragma unroll
+        for (int i = i0; i < i0 + FIT && i < RT; ++i)
+#pragma unroll
+          for (int j = 0; j < NT; ++j) s_sum[((wa * FIT + i - i0) * NT + j) * 64 + lane] = sums(i, j);
+      }
+      __syncthreads();
+      if (kh == 0) {
+#pragma unroll
+        for (int i = i0; i < i0 + FIT && i < RT; ++i)
+#pragma unroll
+          for (int j = 0; j < NT; ++j) sums(i, j) += s_sum[((wa * FIT + i - i0) * NT + j) * 64 + lane];
+      }
+    }
+    if (kh == 1) return;
+  }
+
+  // lane l holds column a2 = 16 j + l%16 and packed rows 16 i + row_of(l/16, r)
   const int64_t n2 = (int64_t)n * n;
 #pragma unroll
-  for (int a = 0; a < A0W; ++a) {
-    const int a0 = a0base + wave * A0W + a;
-    if (a0 >= n) continue;
-    double* out = part + ((int64_t)blockIdx.y * n + a0) * n2;
+  for (int i = 0; i < RT; ++i)
 #pragma unroll
-    for (int i = 0; i < NT; ++i)
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * i + Op::row_of(kg, r);
+      const int a0 = a0base + wa * A0W + row_a0(i, row), a1 = row_a1(i, row);
+      if (a0 >= n || a1 >= n) continue;
+      double* out = part + ((int64_t)blockIdx.y * n + a0) * n2 + (int64_t)a1 * n;
 #pragma unroll
-      for (int j = 0; j < NT; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int a1 = 16 * i + Op::row_of(kg, r), a2 = 16 * j + r16;
-          double v;
-          if constexpr (Op::kSplitSum) v = tot[a][i][j][r];
-          else v = acc[a][i][j][r];
-          if (a1 < n && a2 < n) out[a1 * n + a2] = v;
-        }
-  }
+      for (int j = 0; j < NT; ++j) {
+        const int a2 = 16 * j + r16;
+        if (a2 < n) out[a2] = sums(i, j)[r];
+      }
+    }
 }
 
-template <class Op, int NT, int A0W, class MT = double>
+template <class Op, class Shape, class MT>
 __global__ void __launch_bounds__(512, 1)
 rho_mfma_kernel(const MT* __restrict__ M, const double* __restrict__ Dt, int n, int64_t npair,
                 int64_t chunk, double* __restrict__ part) {
   // batched densities (several orbitals in one launch): density z, its
   // partial grids after those of densities 0 .. z-1
-  rho_mfma_body<Op, NT, A0W, MT>(M, Dt + (int64_t)blockIdx.z * npair, n, npair, chunk,
+  rho_mfma_body<Op, Shape, MT>(M, Dt + (int64_t)blockIdx.z * npair, n, npair, chunk,
                                  part + (int64_t)blockIdx.z * gridDim.y * n * n * n);
 }
 
@@ -239,16 +302,16 @@ struct Spans {
   int64_t blk[kMaxParts + 1];
 };
 
-// rho of every span in one launch: grid (ceil(n / (8*A0W)), nchunk, nspan),
+// rho of every span in one launch: grid (ceil(n / A0G), nchunk, nspan),
 // span z's pairs cut into nchunk chunks, its partial grids after those of
 // spans 0 .. z-1.  An empty span writes zero partial grids.
-template <class Op, int NT, int A0W, class MT>
+template <class Op, class Shape, class MT>
 __global__ void __launch_bounds__(512, 1)
 rho_spans_kernel(const MT* __restrict__ M, const double* __restrict__ Dt, int n, Spans sp, double* __restrict__ part) {
   const int z = blockIdx.z;
   const int64_t cnt = sp.off[z + 1] - sp.off[z];
   const int64_t chunk = (cnt + gridDim.y - 1) / gridDim.y;
-  rho_mfma_body<Op, NT, A0W, MT>(M + 3 * (int64_t)n * sp.off[z], Dt + sp.off[z], n, cnt, chunk,
+  rho_mfma_body<Op, Shape, MT>(M + 3 * (int64_t)n * sp.off[z], Dt + sp.off[z], n, cnt, chunk,
                                  part + (int64_t)z * gridDim.y * n * n * n);
 }
 
@@ -936,9 +999,21 @@ inline unsigned nblk(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 }  // namespace
 
 namespace {
-// a0 values per wave of the rho kernel: two where the accumulators allow
-int rho_a0_per_wave(int prec, int n) { return (prec == kFP64 && n <= 48) ? 2 : 1; }
-int rho_groups(int prec, int n) { return (n + 8 * rho_a0_per_wave(prec, n) - 1) / (8 * rho_a0_per_wave(prec, n)); }
+// a0 groups the chunk capacity of the rho partials is counted with
+int rho_groups(int prec, int n) {
+  const int per = prec == kFP64 && n <= 48 ? 16 : 8;
+  return (n + per - 1) / per;
+}
+// n fits 16 NT - 8 for its number of tiles NT <= 3
+bool half_tiles(int n) { return n <= 48 && (n + 15) / 16 * 16 - n >= 8; }
+// Values of a0 per work group of the shape that rho takes (with_rho_shape)
+// for `chunks` chunks over all pair lists.  FP64 up to n = 48 with whole tiles:
+// 16, or 8 (KS = 2) where 16 would leave half the compute units without a work
+// group; measured, whole J at n = 32 in us: 38 work groups of 16 90, of 8 74;
+// 146 either way 131; 226 120 and 124; n = 48, 237 236 and 246.
+int rho_a0_group(int prec, int n, int64_t chunks) {
+  return prec == kFP64 && n <= 48 && !half_tiles(n) && (int64_t)((n + 15) / 16) * chunks >= 128 ? 16 : 8;
+}
 }  // namespace
 
 int j_nchunk(int prec, int n, int npair) {
@@ -981,15 +1056,47 @@ JWork carve_j_work(void* base, int prec, int nq, int n, int npair) {
   return w;
 }
 
-template <class Op, int A0W, class MT>
-void launch_pair_contraction_rho(const MT* M, int n, int npair, const JWork& w, hipStream_t s, int ndens = 1) {
-  const int64_t chunk = ((int64_t)npair + w.nchunk - 1) / w.nchunk;
-  const dim3 rg((n + 8 * A0W - 1) / (8 * A0W), w.nchunk, ndens);
-  if (n <= 16) hipLaunchKernelGGL((rho_mfma_kernel<Op, 1, A0W, MT>), rg, dim3(512), 0, s, M, w.Dt, n, (int64_t)npair, chunk, w.rho_part);
-  else if (n <= 32) hipLaunchKernelGGL((rho_mfma_kernel<Op, 2, A0W, MT>), rg, dim3(512), 0, s, M, w.Dt, n, (int64_t)npair, chunk, w.rho_part);
-  else if (n <= 48) hipLaunchKernelGGL((rho_mfma_kernel<Op, 3, A0W, MT>), rg, dim3(512), 0, s, M, w.Dt, n, (int64_t)npair, chunk, w.rho_part);
-  else hipLaunchKernelGGL((rho_mfma_kernel<Op, 4, 1, MT>), rg, dim3(512), 0, s, M, w.Dt, n, (int64_t)npair, chunk, w.rho_part);
+namespace {
+// Calls f with the shape of the rho kernel for n and a0 values per work group.
+template <class Op, class F>
+void with_rho_shape(int n, int a0g, F f) {
+  auto shape = [&](auto nt) {
+    constexpr int NT = decltype(nt)::value;
+    if constexpr (NT == 4 || Op::kSplitSum) {
+      f(RhoShape<NT, 1, false, 1>{});
+    } else {
+      if (half_tiles(n)) f(RhoShape<NT, 2, true, 2>{});
+      else if (a0g == 16) f(RhoShape<NT, 2, false, 1>{});
+      else f(RhoShape<NT, 2, false, 2>{});
+    }
+  };
+  if (n <= 16) shape(std::integral_constant<int, 1>{});
+  else if (n <= 32) shape(std::integral_constant<int, 2>{});
+  else if (n <= 48) shape(std::integral_constant<int, 3>{});
+  else shape(std::integral_constant<int, 4>{});
 }
+
+// Chunks of pairs a launch over nspan lists takes out of the capacity: what
+// fills the target number of work groups.
+int rho_chunks(int prec, int n, int nchunk, int nspan) {
+  const int cap = nchunk / nspan;
+  const int g = (n + 7) / 8;
+  return half_tiles(n) && prec == kFP64 && cap > 1 ? std::max(1, std::min(cap, kRhoGroups / (g * nspan))) : cap;
+}
+
+// rho of ndens densities over one pair list into nchunk partial grids each
+template <class Op, class MT>
+void launch_pair_contraction_rho(int prec, const MT* M, int n, int npair, int nchunk, const double* Dt, double* part,
+                                 hipStream_t s, int ndens = 1) {
+  const int64_t chunk = ((int64_t)npair + nchunk - 1) / nchunk;
+  const int a0g = rho_a0_group(prec, n, (int64_t)nchunk * ndens);
+  const dim3 rg((n + a0g - 1) / a0g, nchunk, ndens);
+  with_rho_shape<Op>(n, a0g, [&](auto sh) {
+    hipLaunchKernelGGL((rho_mfma_kernel<Op, decltype(sh), MT>), rg, dim3(512), 0, s, M, Dt, n, (int64_t)npair, chunk,
+                       part);
+  });
+}
+}  // namespace
 
 __global__ void __launch_bounds__(256) to_fp32_kernel(const double* __restrict__ x, int64_t count, float* __restrict__ y) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -998,14 +1105,19 @@ __global__ void __launch_bounds__(256) to_fp32_kernel(const double* __restrict__
 
 namespace {
 // Parts the a0 values of a J_p launch over `blocks` work groups are split
-// into: the one whose last round of work groups on the chip (`slots` at a
-// time) wastes least, each further part charged its share of loading the
-// pairs' moments again.  room: how many parts' sums the caller can hold.
-int jp_splits(int64_t blocks, int n, int64_t slots, int64_t room) {
+// into: least of rounds over the compute units times a work group's length, its
+// a0 values plus a start (loading the pairs' moments) worth kJpStart of them.
+// A second work group on a unit shares its matrix cores, so a round is one per
+// unit.  Measured, whole J at n = 40 in us: 79 work groups 280 / 197 / 210 in
+// 1 / 3 / 6 parts (FP64), 218 / 167 / 183 (FP32); 201 work groups, FP32, 279 in
+// one part, 295 in five; 19 work groups at n = 32 147 in one part, 90 in
+// eight; 240 or more: one.  room: how many parts' sums the caller can hold.
+constexpr double kJpStart = 4.0;
+int jp_splits(int64_t blocks, int n, int64_t room) {
   int best = 1;
   double best_t = 1e300;
-  for (int y = 1; y <= 8 && y <= (n + 1) / 2 && y <= room; ++y) {
-    const double t = (double)((blocks * y + slots - 1) / slots) / y * (1.0 + 0.04 * (y - 1));
+  for (int y = 1; y <= 16 && y <= (n + 1) / 2 && y <= room; ++y) {
+    const double t = (double)((blocks * y + 255) / 256) * ((double)n / y + kJpStart);
     if (t < best_t * (1.0 - 1e-9)) {
       best_t = t;
       best = y;
@@ -1022,7 +1134,7 @@ struct JpPlan {
   int64_t total = 0;
   double* out = nullptr;
 };
-JpPlan jp_plan(const int64_t* offs, int nspan, int n, int64_t slots, const JWork& w) {
+JpPlan jp_plan(const int64_t* offs, int nspan, int n, const JWork& w) {
   JpPlan p;
   p.nspan = nspan;
   p.total = offs[nspan];
@@ -1031,17 +1143,16 @@ JpPlan jp_plan(const int64_t* offs, int nspan, int n, int64_t slots, const JWork
     p.sp.blk[z] = z == 0 ? 0 : p.sp.blk[z - 1] + nblk(offs[z] - offs[z - 1], 256);
   }
   const int64_t room = (int64_t)w.nchunk * n * n * n / (p.total > 0 ? p.total : 1);
-  p.splits = jp_splits(p.sp.blk[nspan], n, slots, room);
+  p.splits = jp_splits(p.sp.blk[nspan], n, room);
   p.out = p.splits > 1 ? w.rho_part : w.Jp;
   return p;
 }
 
-// J_p of the spans in FP64 or FP32 and J from it.  By registers three work
-// groups fit on a compute unit up to n = 16, two for n = 25 .. 32, else one.
+// J_p of the spans in FP64 or FP32 and J from it.
 template <class Op>
 void launch_jp(const double* M, int n, const int64_t* offs, int nspan, const double* Phi, const int32_t* pairs, int nb,
                const JWork& w, double* J, hipStream_t s) {
-  const JpPlan p = jp_plan(offs, nspan, n, n <= 16 ? 768 : n > 24 && n <= 32 ? 512 : 256, w);
+  const JpPlan p = jp_plan(offs, nspan, n, w);
   const dim3 g((unsigned)p.sp.blk[nspan], p.splits);
   auto go = [&](auto nt) {
     constexpr int NT = decltype(nt)::value;
@@ -1097,7 +1208,7 @@ void launch_jp16(const float* M, int n, const int64_t* offs, int nspan, const do
   const int kc = j16_kc(S, n);
   __bf16* Ps = static_cast<__bf16*>(Psv);
   hipLaunchKernelGGL((phi_split_kernel<S>), dim3(nspan * n * n), dim3(256), 0, s, Phi, n, kc, Ps);
-  const JpPlan p = jp_plan(offs, nspan, n, 256, w);
+  const JpPlan p = jp_plan(offs, nspan, n, w);
   const dim3 g((unsigned)p.sp.blk[nspan], p.splits);
   const int NT = (n + 15) / 16, KC = kc / 32;
 #define TAI_JP16(nt, kcc)                                                                                              \
@@ -1138,17 +1249,27 @@ hipError_t launch_phi_grid(const double* rho, const double* K, const double* wsc
   return launch_mode_products(rho, 1, 1, K, 0, wsc, n, nq, w.T1, 1, 0, nq, Phi, w.T2, (int64_t)nq * n3, s);
 }
 
+// rho of one pair list from its pair densities Dt
+void launch_rho_list(int prec, const double* M, const float* M32, int n, int npair, const JWork& w, const double* Dt,
+                     double* rho, hipStream_t s) {
+  int nchunk = w.nchunk;
+  if (rho_split(prec)) {
+    JWork wd = w;
+    wd.Dt = const_cast<double*>(Dt);
+    launch_rho16(prec, M32, n, npair, wd, s);
+  } else {
+    nchunk = rho_chunks(prec, n, nchunk, 1);
+    if (prec == kFP64) launch_pair_contraction_rho<JF64>(prec, M, n, npair, nchunk, Dt, w.rho_part, s);
+    else launch_pair_contraction_rho<JF32>(prec, M32, n, npair, nchunk, Dt, w.rho_part, s);
+  }
+  launch_sum_parts(w.rho_part, nchunk, (int64_t)n * n * n, 1, rho, s);
+}
+
 // rho from the pair densities in w.Dt, then Phi = (2/sqrt(pi)) sum_k w_k rho x_d K_k
 // (into w.rho and w.Phi)
 hipError_t launch_rho_phi(int prec, const double* M, int npair, int n, int nq, const NodeTables& tb, const JWork& w,
                           hipStream_t s) {
-  const int64_t n3 = (int64_t)n * n * n;
-  if (rho_split(prec)) launch_rho16(prec, w.M32, n, npair, w, s);
-  else if (prec == kFP32 || split_j(prec))
-    launch_pair_contraction_rho<JF32, 1>(static_cast<const float*>(w.M32), n, npair, w, s);
-  else if (n <= 48) launch_pair_contraction_rho<JF64, 2>(M, n, npair, w, s);
-  else launch_pair_contraction_rho<JF64, 1>(M, n, npair, w, s);
-  launch_sum_parts(w.rho_part, w.nchunk, n3, 1, w.rho, s);
+  launch_rho_list(prec, M, w.M32, n, npair, w, w.Dt, w.rho, s);
   hipLaunchKernelGGL(repeat_weights_kernel, dim3(nblk(nq, 256)), dim3(256), 0, s, tb.w, nq, 1, kTwoOverSqrtPi, w.wsc);
   return launch_phi_grid(w.rho, tb.K, w.wsc, n, nq, w, w.Phi, s);
 }
@@ -1194,14 +1315,14 @@ hipError_t launch_apply_j(int prec, const double* M, int nb, int npair, const in
 // J_p of all partitions in one launch; the split-BF16 rho keeps a launch per
 // partition.
 namespace {
-template <class Op, int A0W, class MT>
-void launch_rho_spans(const MT* M, int n, const Spans& sp, int nspan, int nchunk, const double* Dt, double* part,
-                      hipStream_t s) {
-  const dim3 rg((n + 8 * A0W - 1) / (8 * A0W), nchunk, nspan);
-  if (n <= 16) hipLaunchKernelGGL((rho_spans_kernel<Op, 1, A0W, MT>), rg, dim3(512), 0, s, M, Dt, n, sp, part);
-  else if (n <= 32) hipLaunchKernelGGL((rho_spans_kernel<Op, 2, A0W, MT>), rg, dim3(512), 0, s, M, Dt, n, sp, part);
-  else if (n <= 48) hipLaunchKernelGGL((rho_spans_kernel<Op, 3, A0W, MT>), rg, dim3(512), 0, s, M, Dt, n, sp, part);
-  else hipLaunchKernelGGL((rho_spans_kernel<Op, 4, 1, MT>), rg, dim3(512), 0, s, M, Dt, n, sp, part);
+template <class Op, class MT>
+void launch_rho_spans(int prec, const MT* M, int n, const Spans& sp, int nspan, int nchunk, const double* Dt,
+                      double* part, hipStream_t s) {
+  const int a0g = rho_a0_group(prec, n, (int64_t)nchunk * nspan);
+  const dim3 rg((n + a0g - 1) / a0g, nchunk, nspan);
+  with_rho_shape<Op>(n, a0g, [&](auto sh) {
+    hipLaunchKernelGGL((rho_spans_kernel<Op, decltype(sh), MT>), rg, dim3(512), 0, s, M, Dt, n, sp, part);
+  });
 }
 }  // namespace
 
@@ -1224,11 +1345,10 @@ hipError_t launch_apply_j_parts(int prec, const double* M, int nb, const int32_t
   // partial grids of all partitions fit where the list's would
   const int pchunk = wk.nchunk / nparts;
   if (!one && !rho_split(prec) && pchunk >= 1) {
-    if (prec == kFP32 || split_j(prec))
-      launch_rho_spans<JF32, 1>(static_cast<const float*>(wk.M32), n, sp, nparts, pchunk, wk.Dt, wk.rho_part, s);
-    else if (n <= 48) launch_rho_spans<JF64, 2>(M, n, sp, nparts, pchunk, wk.Dt, wk.rho_part, s);
-    else launch_rho_spans<JF64, 1>(M, n, sp, nparts, pchunk, wk.Dt, wk.rho_part, s);
-    launch_sum_parts(wk.rho_part, pchunk, n3, nparts, rho_all, s);
+    const int nchunk = rho_chunks(prec, n, wk.nchunk, nparts);
+    if (prec == kFP64) launch_rho_spans<JF64>(prec, M, n, sp, nparts, nchunk, wk.Dt, wk.rho_part, s);
+    else launch_rho_spans<JF32>(prec, static_cast<const float*>(wk.M32), n, sp, nparts, nchunk, wk.Dt, wk.rho_part, s);
+    launch_sum_parts(wk.rho_part, nchunk, n3, nparts, rho_all, s);
   } else {
     for (int p = 0; p < nparts; ++p) {
       const int64_t cnt = offs[p + 1] - offs[p];
@@ -1237,16 +1357,8 @@ hipError_t launch_apply_j_parts(int prec, const double* M, int nb, const int32_t
         hipLaunchKernelGGL(zero_kernel, dim3(nblk(n3, 256)), dim3(256), 0, s, rho_p, n3);
         continue;
       }
-      JWork wp = wk;
-      wp.Dt = wk.Dt + offs[p];
-      const double* Mp = M + 3 * (int64_t)n * offs[p];
-      if (rho_split(prec)) launch_rho16(prec, wk.M32 + 3 * (int64_t)n * offs[p], n, (int)cnt, wp, s);
-      else if (prec == kFP32 || split_j(prec))
-        launch_pair_contraction_rho<JF32, 1>(static_cast<const float*>(wk.M32 + 3 * (int64_t)n * offs[p]), n,
-                                             (int)cnt, wp, s);
-      else if (n <= 48) launch_pair_contraction_rho<JF64, 2>(Mp, n, (int)cnt, wp, s);
-      else launch_pair_contraction_rho<JF64, 1>(Mp, n, (int)cnt, wp, s);
-      launch_sum_parts(wk.rho_part, wk.nchunk, n3, 1, rho_p, s);
+      const float* M32 = wk.M32 ? wk.M32 + 3 * (int64_t)n * offs[p] : nullptr;
+      launch_rho_list(prec, M + 3 * (int64_t)n * offs[p], M32, n, (int)cnt, wk, wk.Dt + offs[p], rho_p, s);
     }
   }
   if (!one) {
@@ -1289,7 +1401,8 @@ constexpr int kMoBlock = 32;
 // `cus` units whose last wave is fullest (the first such, at most the
 // single-density count).
 int mo_chunks(int prec, int n, int npair, int ob, int cus) {
-  const int groups = rho_groups(prec, n) * ob;
+  const int a0g = prec == kFP64 && n <= 48 && !half_tiles(n) ? 16 : 8;
+  const int groups = (n + a0g - 1) / a0g * ob;
   const int cap = j_nchunk(prec, n, npair);
   int best = 1;
   double best_eff = -1.0;
@@ -1334,14 +1447,9 @@ hipError_t launch_coulomb_mo(int prec, const double* M, int nb, int npair, const
     const int ob = norb - i0 < obmax ? norb - i0 : obmax;
     hipLaunchKernelGGL(orbital_pairs_kernel, dim3(nblk(npair, 256), ob), dim3(256), 0, s, Q + (int64_t)i0 * nb, nb,
                        (int64_t)npair, pairs, Dt);
-    JWork wb = w;
-    wb.Dt = Dt;
-    wb.nchunk = nc;
-    wb.rho_part = part;
     if (prec == kFP32)
-      launch_pair_contraction_rho<JF32, 1>(static_cast<const float*>(w.M32), n, npair, wb, s, ob);
-    else if (n <= 48) launch_pair_contraction_rho<JF64, 2>(M, n, npair, wb, s, ob);
-    else launch_pair_contraction_rho<JF64, 1>(M, n, npair, wb, s, ob);
+      launch_pair_contraction_rho<JF32>(prec, static_cast<const float*>(w.M32), n, npair, nc, Dt, part, s, ob);
+    else launch_pair_contraction_rho<JF64>(prec, M, n, npair, nc, Dt, part, s, ob);
     double* Rb = R + (int64_t)i0 * n3;
     launch_sum_parts(part, nc, n3, ob, Rb, s);
     // the block's mode products on the matrix cores (Phi without 2/sqrt(pi),
