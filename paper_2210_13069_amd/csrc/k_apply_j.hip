@@ -1249,9 +1249,9 @@ hipError_t launch_phi_grid(const double* rho, const double* K, const double* wsc
   return launch_mode_products(rho, 1, 1, K, 0, wsc, n, nq, w.T1, 1, 0, nq, Phi, w.T2, (int64_t)nq * n3, s);
 }
 
-// rho of one pair list from its pair densities Dt
+// rho of one pair list from its pair densities Dt, in parity form on request
 void launch_rho_list(int prec, const double* M, const float* M32, int n, int npair, const JWork& w, const double* Dt,
-                     double* rho, hipStream_t s) {
+                     bool parity, double* rho, hipStream_t s) {
   int nchunk = w.nchunk;
   if (rho_split(prec)) {
     JWork wd = w;
@@ -1262,14 +1262,16 @@ void launch_rho_list(int prec, const double* M, const float* M32, int n, int npa
     if (prec == kFP64) launch_pair_contraction_rho<JF64>(prec, M, n, npair, nchunk, Dt, w.rho_part, s);
     else launch_pair_contraction_rho<JF32>(prec, M32, n, npair, nchunk, Dt, w.rho_part, s);
   }
-  launch_sum_parts(w.rho_part, nchunk, (int64_t)n * n * n, 1, rho, s);
+  const int64_t n3 = (int64_t)n * n * n;
+  if (parity) launch_parity_sum(w.rho_part, nchunk, 0, n3, n, 1, rho, s);
+  else launch_sum_parts(w.rho_part, nchunk, n3, 1, rho, s);
 }
 
 // rho from the pair densities in w.Dt, then Phi = (2/sqrt(pi)) sum_k w_k rho x_d K_k
 // (into w.rho and w.Phi)
 hipError_t launch_rho_phi(int prec, const double* M, int npair, int n, int nq, const NodeTables& tb, const JWork& w,
                           hipStream_t s) {
-  launch_rho_list(prec, M, w.M32, n, npair, w, w.Dt, w.rho, s);
+  launch_rho_list(prec, M, w.M32, n, npair, w, w.Dt, false, w.rho, s);
   hipLaunchKernelGGL(repeat_weights_kernel, dim3(nblk(nq, 256)), dim3(256), 0, s, tb.w, nq, 1, kTwoOverSqrtPi, w.wsc);
   return launch_phi_grid(w.rho, tb.K, w.wsc, n, nq, w, w.Phi, s);
 }
@@ -1327,7 +1329,7 @@ void launch_rho_spans(int prec, const MT* M, int n, const Spans& sp, int nspan, 
 }  // namespace
 
 hipError_t launch_apply_j_parts(int prec, const double* M, int nb, const int32_t* pairs, const int64_t* offs,
-                                int nparts, int n, int nq, const double* w, const double* Kx, const double* D,
+                                int nparts, int n, int nq, const double* w, double* Kx, const double* D,
                                 double* J, const JWork& wk, double* rho_all, double* T2_all, double* Phi_all,
                                 double* wrep, hipStream_t s) {
   const int64_t total = offs[nparts];
@@ -1337,6 +1339,7 @@ hipError_t launch_apply_j_parts(int prec, const double* M, int nb, const int32_t
   // one box: the plain path's sequence (the same bits as tai_apply_J); the
   // weights carry 2/sqrt(pi) either way
   const bool one = nparts == 1;
+  const bool parity = !one && phi_octants(n, (int64_t)nparts * nparts);
   hipLaunchKernelGGL(repeat_weights_kernel, dim3(nblk((int64_t)nq * nparts, 256)), dim3(256), 0, s, w, nq, nparts,
                      kTwoOverSqrtPi, wrep);
   Spans sp{};
@@ -1348,7 +1351,8 @@ hipError_t launch_apply_j_parts(int prec, const double* M, int nb, const int32_t
     const int nchunk = rho_chunks(prec, n, wk.nchunk, nparts);
     if (prec == kFP64) launch_rho_spans<JF64>(prec, M, n, sp, nparts, nchunk, wk.Dt, wk.rho_part, s);
     else launch_rho_spans<JF32>(prec, static_cast<const float*>(wk.M32), n, sp, nparts, nchunk, wk.Dt, wk.rho_part, s);
-    launch_sum_parts(wk.rho_part, nchunk, n3, nparts, rho_all, s);
+    if (parity) launch_parity_sum(wk.rho_part, nchunk, nchunk * n3, n3, n, nparts, rho_all, s);
+    else launch_sum_parts(wk.rho_part, nchunk, n3, nparts, rho_all, s);
   } else {
     for (int p = 0; p < nparts; ++p) {
       const int64_t cnt = offs[p + 1] - offs[p];
@@ -1358,10 +1362,16 @@ hipError_t launch_apply_j_parts(int prec, const double* M, int nb, const int32_t
         continue;
       }
       const float* M32 = wk.M32 ? wk.M32 + 3 * (int64_t)n * offs[p] : nullptr;
-      launch_rho_list(prec, M + 3 * (int64_t)n * offs[p], M32, n, (int)cnt, wk, wk.Dt + offs[p], rho_p, s);
+      launch_rho_list(prec, M + 3 * (int64_t)n * offs[p], M32, n, (int)cnt, wk, wk.Dt + offs[p], parity, rho_p, s);
     }
   }
-  if (!one) {
+  if (parity) {
+    hipError_t e = launch_parity_tables(Kx, (int64_t)nparts * nparts * nq, n, s);
+    if (e == hipSuccess)
+      e = launch_phi_octants(rho_all, nparts, nparts, nparts, Kx, (int64_t)nq * n2, wrep, n, nq, T2_all,
+                             (int64_t)nparts * nparts * nq * n3, true, Phi_all, s);
+    if (e != hipSuccess) return e;
+  } else if (!one) {
     // T1 of box pair (p, q) = rho_q through the tables K^(p,q), at
     // T2_all[(p nparts + q) nq]; Phi_p sums its nparts nq node blocks (the
     // partial grids of rho are free again and hold the node runs' sums)
@@ -1431,9 +1441,14 @@ size_t mo_work_bytes(int prec, int n, int nq, int npair, int norb, int cus) {
 // contraction (grid z = orbital, each orbital's chunks of pairs), the chunk
 // sums, the mode products and the node sums; then J_mo(i, j) = <rho_i, Phi_j>.
 hipError_t launch_coulomb_mo(int prec, const double* M, int nb, int npair, const int32_t* pairs, int n, int nq,
-                             const NodeTables& tb, const double* Q, int norb, int cus, void* work, double* Jmo,
-                             const JWork& w, hipStream_t s) {
+                             const NodeTables& tb, bool mirrored, const double* Q, int norb, int cus, void* work,
+                             double* Jmo, const JWork& w, hipStream_t s) {
   const int64_t n3 = (int64_t)n * n * n;
+  const bool parity = mirrored && phi_octants(n, norb);
+  if (parity) {
+    const hipError_t e = launch_parity_tables(tb.K, nq, n, s);
+    if (e != hipSuccess) return e;
+  }
   convert_moments(prec, M, n, npair, w, s);
   const int obmax = norb < kMoBlock ? norb : kMoBlock;
   const int nc = mo_chunks(prec, n, npair, obmax, cus);
@@ -1451,6 +1466,15 @@ hipError_t launch_coulomb_mo(int prec, const double* M, int nb, int npair, const
       launch_pair_contraction_rho<JF32>(prec, static_cast<const float*>(w.M32), n, npair, nc, Dt, part, s, ob);
     else launch_pair_contraction_rho<JF64>(prec, M, n, npair, nc, Dt, part, s, ob);
     double* Rb = R + (int64_t)i0 * n3;
+    if (parity) {
+      // rho and Phi stay in parity form: their dot products are the same
+      hipError_t e = launch_parity_sum(part, nc, nc * n3, n3, n, ob, Rb, s);
+      if (e == hipSuccess)
+        e = launch_phi_octants(Rb, ob, 1, ob, tb.K, 0, tb.w, n, nq, T1, (int64_t)ob * nq * n3, false,
+                               F + (int64_t)i0 * n3, s);
+      if (e != hipSuccess) return e;
+      continue;
+    }
     launch_sum_parts(part, nc, n3, ob, Rb, s);
     // the block's mode products on the matrix cores (Phi without 2/sqrt(pi),
     // which the dot products apply)

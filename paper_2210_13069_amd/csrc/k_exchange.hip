@@ -12,6 +12,8 @@
 //  * exch_x_kernel: per (a0 group, mu, j) one work group forms X_{j mu} for its
 //    a0 values over the nb pairs (mu, lambda), staged in LDS 64 pairs at a
 //    time (v_mfma_f64_16x16x4, or the FP32 form);
+//  * phi_octant_kernel (k_phi.hip), for n <= 32 on the uncompressed grid: Phi by
+//    parity, no intermediate tensor; else
 //  * exch_slab_kernel: per slab (t, a0) and node k, S = K_k X_t(a0) K_k^T (both
 //    products on the FP64 matrix cores, the slab and K_k in LDS), written to an
 //    intermediate T1[t][k][a0] that holds a bounded chunk of tensors;
@@ -583,6 +585,9 @@ exch_mode0_kernel(const double* __restrict__ T1, const double* __restrict__ K, c
 // for the tiles on and above the diagonal only (K is symmetric; the sum
 // kernel reads entry (min, max) for both orders, so K comes out exactly
 // symmetric).
+// The next batch's rows are loaded into registers during the MFMAs: nb = 92,
+// 8 orbitals, n = 32 300 -> 177 us (0.58 GB read by the three tiles; 92 us of
+// MFMAs on the padded tiles).
 constexpr int kDK = 32;
 __global__ void __launch_bounds__(256)
 exch_dot_kernel(const double* __restrict__ X, const double* __restrict__ Phi, int nb, int norb, int64_t n3,
@@ -608,24 +613,32 @@ exch_dot_kernel(const double* __restrict__ X, const double* __restrict__ Phi, in
   // this thread stages column col of every batch, rows row0, row0 + 8, ...
   static_assert(256 % kDK == 0, "a thread's column is the same in every row step");
   const int col = threadIdx.x % kDK, row0 = threadIdx.x / kDK;
-  for (int64_t fb = f0; fb < f1; fb += kDK) {
-    __syncthreads();
+  constexpr int RSTEP = 256 / kDK, RPER = 64 / RSTEP;
+  double xr[RPER], pr[RPER];
+  auto load = [&](int64_t fb) {
     const int64_t f = fb + col;
     const bool fin = f < f1;
     const int64_t fc = fin ? f : f0;              // past the slice: no load
     const int64_t j = fc / n3, a = fc - j * n3;   // once per batch, not per row
     const double* xcol = X + (j * nb + mu0) * n3 + a;
     const double* pcol = Phi + (j * nb + nu0) * n3 + a;
-    for (int row = row0; row < 64; row += 256 / kDK) {
-      double xv = 0.0, pv = 0.0;
-      if (fin) {
-        if (mu0 + row < nb) xv = xcol[row * n3];
-        if (nu0 + row < nb) pv = pcol[row * n3];
-      }
-      xs[row * DS + col] = xv;
-      ps[row * DS + col] = pv;
+#pragma unroll
+    for (int i = 0; i < RPER; ++i) {
+      const int row = row0 + RSTEP * i;
+      xr[i] = fin && mu0 + row < nb ? xcol[row * n3] : 0.0;
+      pr[i] = fin && nu0 + row < nb ? pcol[row * n3] : 0.0;
+    }
+  };
+  load(f0);
+  for (int64_t fb = f0; fb < f1; fb += kDK) {
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < RPER; ++i) {
+      xs[(row0 + RSTEP * i) * DS + col] = xr[i];
+      ps[(row0 + RSTEP * i) * DS + col] = pr[i];
     }
     __syncthreads();
+    if (fb + kDK < f1) load(fb + kDK);            // in flight during the MFMAs
 #pragma unroll
     for (int st = 0; st < kDK / 4; ++st) {
       const int kk = 4 * st + kg;
@@ -844,8 +857,9 @@ ExchangeWork exchange_work_plan(int n, int nq, int nb, int norb, bool listed, in
 }
 
 hipError_t launch_exchange(int prec, const double* M, int nb, int64_t npair, const int32_t* pairs, int n, int nq,
-                           const NodeTables& tb, const double* Q, int norb, void* work, const ExchangeWork& p,
-                           double* Kx, hipStream_t s) {
+                           const NodeTables& tb, bool mirrored, const double* Q, int norb, void* work,
+                           const ExchangeWork& p, double* Kx, hipStream_t s) {
+  const bool parity = mirrored && phi_octants(n, p.ntensor);
   char* base = static_cast<char*>(work);
   double* X = reinterpret_cast<double*>(base + p.off_X);
   double* Phi = reinterpret_cast<double*>(base + p.off_Phi);
@@ -857,6 +871,16 @@ hipError_t launch_exchange(int prec, const double* M, int nb, int64_t npair, con
     inv = reinterpret_cast<int32_t*>(base + p.off_inv);
     hipLaunchKernelGGL(fill_kernel, dim3(nblk(full, 256)), dim3(256), 0, s, inv, full, -1);
     hipLaunchKernelGGL(invert_pairs_kernel, dim3(nblk(npair, 256)), dim3(256), 0, s, pairs, npair, full, inv);
+  }
+  // By parity, <X, Phi> is taken with both in parity form.  In FP64 X comes out
+  // in it from moments in it (in T1, which the mode products need only later);
+  // the FP32 sums are those of the node form, transformed afterwards.
+  bool folded = false;
+  if (parity && prec == kFP64 && 3 * (int64_t)n * npair <= p.tchunk * nq * (int64_t)n * n * n) {
+    const hipError_t e = launch_parity_moments(M, n, npair, T1, s);
+    if (e != hipSuccess) return e;
+    M = T1;
+    folded = true;
   }
   // X_{j mu}: one work group per (a0 group, mu, j)
   const int NT = (n + 15) / 16;
@@ -874,8 +898,16 @@ hipError_t launch_exchange(int prec, const double* M, int nb, int64_t npair, con
     const dim3 g((n + 7) / 8, nb, norb);
     hipLaunchKernelGGL((exch_x_kernel<XF64, 4, 1>), g, dim3(512), 0, s, M, npair, n, nb, inv, Q, X);
   }
-  // Phi of every tensor, the slab products of a bounded chunk at a time
   const int64_t n3 = (int64_t)n * n * n, n2 = (int64_t)n * n;
+  if (parity) {
+    hipError_t e = launch_parity_tables(tb.K, nq, n, s);
+    if (e == hipSuccess && !folded) e = launch_parity_sum(X, 1, n3, 0, n, p.ntensor, X, s);
+    if (e == hipSuccess)
+      e = launch_phi_octants(X, p.ntensor, 1, p.ntensor, tb.K, 0, tb.w, n, nq, T1, p.tchunk * nq * n3, false, Phi, s);
+    if (e != hipSuccess) return e;
+    return launch_dot_split(X, Phi, nb, norb, n3, p.slice, 2.0 * kTwoOverSqrtPi, part, Kx, s);
+  }
+  // Phi of every tensor, the slab products of a bounded chunk at a time
   for (int64_t t0 = 0; t0 < p.ntensor; t0 += p.tchunk) {
     const int64_t tc = std::min<int64_t>(p.tchunk, p.ntensor - t0);
     const double* Xc = X + t0 * n3;

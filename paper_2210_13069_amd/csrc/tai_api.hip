@@ -1652,7 +1652,8 @@ int tai_coulomb_mo(tai_ctx* c, const double* M, int32_t nb, const int32_t* pairs
   tai::JWork w = tai::carve_j_work(c->jwork.p, p->prec, nq, n, (int)npair);
   {
     Timed tm(c, kStApplyJ, s);
-    e = tai::launch_coulomb_mo(p->prec, Mop, nb, (int)npair, pairs, n, nq, tbp, Q, norb, cus, c->mo.p, Jmo, w, s);
+    e = tai::launch_coulomb_mo(p->prec, Mop, nb, (int)npair, pairs, n, nq, tbp, !(p->rank_tol > 0), Q, norb, cus, c->mo.p, Jmo,
+                               w, s);
   }
   if (e != hipSuccess) return hip_fail(c, e, "coulomb_mo kernels");
   return TAI_OK;
@@ -1686,7 +1687,7 @@ int tai_exchange(tai_ctx* c, const double* M, int32_t nb, const int32_t* pairs, 
   hipError_t e;
   {
     Timed tm(c, kStApplyJ, s);
-    e = tai::launch_exchange(p->prec, Mop, nb, npair, pairs, n, nq, tbp, Q, norb, c->mo.p, plan, Kx, s);
+    e = tai::launch_exchange(p->prec, Mop, nb, npair, pairs, n, nq, tbp, !(p->rank_tol > 0), Q, norb, c->mo.p, plan, Kx, s);
   }
   if (e != hipSuccess) return hip_fail(c, e, "exchange kernels");
   return TAI_OK;

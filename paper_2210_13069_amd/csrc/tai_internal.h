@@ -331,9 +331,12 @@ hipError_t launch_contract_functions(const double* Jp, int nbp, const int32_t* f
 // orbitals at a time, then Jmo[i][j] = <rho_i, Phi_j>.  work: mo_work_bytes.
 // cus: compute units of the device (the pair contraction's chunking).
 size_t mo_work_bytes(int prec, int n, int nq, int npair, int norb, int cus);
+// mirrored (here and in the exchange launch): the tables have K(a, b) =
+// K(n-1-a, n-1-b), so that the mode products may go by parity; tb.K is then
+// overwritten with its parity form.
 hipError_t launch_coulomb_mo(int prec, const double* M, int nb, int npair, const int32_t* pairs, int n, int nq,
-                             const NodeTables& tb, const double* Q, int norb, int cus, void* work, double* Jmo,
-                             const JWork& w, hipStream_t s);
+                             const NodeTables& tb, bool mirrored, const double* Q, int norb, int cus, void* work,
+                             double* Jmo, const JWork& w, hipStream_t s);
 // Long-range exchange matrix (appendix B): X_{j mu} and Phi_{j nu} for every
 // orbital j and function mu into R and F ([norb][nb][n^3] each), then
 // Kx(mu, nu) = 2 sum_j <X_{j mu}, Phi_{j nu}>.
@@ -378,7 +381,7 @@ hipError_t launch_cross_tables(const double* t, int nq, int n, int kind, const P
 // one after another (each on its own box), pairs the concatenated lists.
 // Kx from launch_cross_tables; w the node weights.
 hipError_t launch_apply_j_parts(int prec, const double* M, int nb, const int32_t* pairs, const int64_t* offs,
-                                int nparts, int n, int nq, const double* w, const double* Kx, const double* D,
+                                int nparts, int n, int nq, const double* w, double* Kx, const double* D,
                                 double* J, const JWork& wk, double* rho_all, double* T2_all, double* Phi_all,
                                 double* wrep, hipStream_t s);
 
@@ -403,6 +406,27 @@ ExchangeWork exchange_work_plan(int n, int nq, int nb, int norb, bool listed, in
 hipError_t launch_mode_products(const double* X, int64_t T, int64_t xmod, const double* K, int64_t kstride,
                                 const double* w, int n, int nq, double* T1, int64_t T0, int64_t kstride0,
                                 int nq0, double* Phi, double* part, int64_t part_len, hipStream_t s);
+// Phi by parity (k_phi.hip), for tables K(a, b) = K(n-1-a, n-1-b): the plain,
+// truncated and cross tables, not those in a compressed basis.
+// Whether `tensors` grid tensors (outputs times sources) take this form.
+bool phi_octants(int n, int64_t tensors);
+// Mp[d][.][p]: every direction's moments in parity form.
+hipError_t launch_parity_moments(const double* M, int n, int64_t npair, double* Mp, hipStream_t s);
+// The n x n matrices of K into parity form, in place.
+hipError_t launch_parity_tables(double* K, int64_t nmat, int n, hipStream_t s);
+// out[y] = parity transform of sum_g part[y ystride + g gstride ..] (n^3 values
+// each), y < batch; out may be part when nparts = 1.
+hipError_t launch_parity_sum(const double* part, int nparts, int64_t ystride, int64_t gstride, int n, int64_t batch,
+                             double* out, hipStream_t s);
+// For T output tensors, Phi_t = sum over nsrc sources q and nq nodes of
+// w[q nq + k] X[(t nsrc + q) % xmod] x_d K(t nsrc + q, k), X and the tables
+// (K + (t nsrc + q) kstride) in parity form; Phi in node form (to_nodes), or in
+// parity form with 1/2 per mode and pair of indices, so that its dot product
+// with a tensor in parity form is that of the node forms.  part: part_len >= n^3 T
+// nsrc doubles for the sums of runs of nodes.
+hipError_t launch_phi_octants(const double* X, int64_t T, int nsrc, int64_t xmod, const double* K, int64_t kstride,
+                              const double* w, int n, int nq, double* part, int64_t part_len, bool to_nodes,
+                              double* Phi, hipStream_t s);
 // out[y][i] = sum_g part[y][g][i] for y < batch, i < len, in a fixed order
 // (k_exchange.hip).
 void launch_sum_parts(const double* part, int nparts, int64_t len, int batch, double* out, hipStream_t s);
@@ -414,8 +438,8 @@ int64_t dot_slice(int64_t total, int nb, int64_t part_len);
 hipError_t launch_dot_split(const double* X, const double* Phi, int nb, int norb, int64_t n3, int64_t slice,
                             double scale, double* part, double* Kx, hipStream_t s);
 hipError_t launch_exchange(int prec, const double* M, int nb, int64_t npair, const int32_t* pairs, int n, int nq,
-                           const NodeTables& tb, const double* Q, int norb, void* work, const ExchangeWork& p,
-                           double* Kx, hipStream_t s);
+                           const NodeTables& tb, bool mirrored, const double* Q, int norb, void* work,
+                           const ExchangeWork& p, double* Kx, hipStream_t s);
 // Achievable-peak probes (k_probe.hip): what 0 = FP16 MFMA, 1 = FP64 MFMA,
 // 2 = HBM copy.  probe_work is the flops (0, 1) or bytes (2) of one launch.
 hipError_t launch_probe(int what, int cus, float* out, const void* src, void* dst, int64_t n16, int iters,
