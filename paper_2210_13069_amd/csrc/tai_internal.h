@@ -166,13 +166,15 @@ hipError_t launch_moments_batch(const PrepMol* mols, int nmol, int64_t max_npair
 hipError_t launch_coef_moments_batch(const PrepMol* mols, int nmol, int64_t max_npair, int n, int kind,
                                      hipStream_t s);
 hipError_t launch_pack_batch(int prec, const PrepMol* mols, int nmol, int max_prow, int n, hipStream_t s);
+// any_general: some molecule is compressed or in coefficient form.
 hipError_t launch_project_batch(int prec, const PrepMol* mols, int nmol, int max_prow, int n, int nq,
-                                hipStream_t s);
+                                bool any_general, hipStream_t s);
 
 hipError_t launch_pack(int prec, const double* M, int n, int npair, int prow,
                        void* A, int32_t* ex, hipStream_t s);
+// mirrored: the tables have K(a, b) = K(n-1-a, n-1-b) (the node form).
 hipError_t launch_project(int prec, const double* M, int n, int npair, int prow, int nq,
-                          const NodeTables& tb, const int32_t* ex, int ysh, void* Y, hipStream_t s);
+                          const NodeTables& tb, bool mirrored, const int32_t* ex, int ysh, void* Y, hipStream_t s);
 // Single molecule, one work group per tile.
 hipError_t launch_assemble(int prec, const AsmMol& m, hipStream_t s);
 // Persistent launch over a device work list of molecules; `counter` is a
