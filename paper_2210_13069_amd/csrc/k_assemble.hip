@@ -121,19 +121,29 @@ __device__ inline void tile_pad(int prec, int n, int kc, uint32_t* row) {
   }
 }
 
-// Copy the LDS tile of kRowsPerTile rows to dst (rows contiguous, kc elements
-// each) in 16-byte stores: a row is kc * es bytes, a multiple of 16 for every
-// operand format (kc is a multiple of 8, or of 32 for the 16-bit slices), and
-// dst is 16-byte aligned.
+// Copy the LDS tile of kRowsPerTile rows to dst in the fragment order of
+// tai_internal.h in 16-byte stores: a fragment is 16 rows by one
+// chunk of the inner index, 64 lanes of 16 bytes (FP32: of 8), lane 16 g + r
+// holding group g of row r; dst is 16-byte aligned.
 __device__ inline void tile_store(int prec, int kc, const uint32_t* tile, int stride_w, uint32_t* __restrict__ dst) {
   const int es = prec == kFP64 ? 8 : (prec == kFP32 ? 4 : 2);
   const int qpr = kc * es / 16;  // 16-byte quads per row
-  const int total = kRowsPerTile * qpr;
   uint4* __restrict__ dst4 = reinterpret_cast<uint4*>(dst);
-  for (int e = threadIdx.x; e < total; e += blockDim.x) {
-    const int r = e / qpr, q = e - r * qpr;
-    const uint32_t* src = tile + r * stride_w + 4 * q;
-    dst4[e] = uint4{src[0], src[1], src[2], src[3]};
+  // wave w stores the 16 rows from 16 w on: its quads are consecutive
+  static_assert(kRowsPerTile == 64, "one wave per 16 rows");
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t* __restrict__ src0 = tile + 16 * wave * stride_w;
+  uint4* __restrict__ out = dst4 + 16 * wave * qpr;
+  if (prec == kFP32) {
+    // a quad is group g of two rows: 32 quads per chunk of 8
+    const int r = 2 * (lane & 7), g = (lane >> 3) & 3;
+    for (int e = lane; e < 16 * qpr; e += 64) {
+      const uint32_t* src = src0 + r * stride_w + 8 * (e >> 5) + 2 * g;
+      out[e] = uint4{src[0], src[1], src[stride_w], src[stride_w + 1]};
+    }
+  } else {
+    const uint32_t* src = src0 + (lane & 15) * stride_w + 4 * (lane >> 4);
+    for (int c = 0; c < qpr / 4; ++c, src += 16) out[64 * c + lane] = uint4{src[0], src[1], src[2], src[3]};
   }
 }
 
@@ -560,14 +570,14 @@ __device__ inline void assemble_tile(const AsmMol& m, int I, int J) {
       for (int i = 0; i < WM; ++i)
 #pragma unroll
         for (int j = 0; j < WN; ++j) G[i][j] = Op::zero();
-      const T* Ad = Abase + ((int64_t)d * prow + row0 + r16) * kc + kg * Op::kPerLane;
-      const T* Yd = Ybase + (((int64_t)k * 3 + d) * prow + col0 + r16) * kc + kg * Op::kPerLane;
+      const T* Ad = Abase + ((int64_t)d * prow + row0) * kc + lane * Op::kPerLane;
+      const T* Yd = Ybase + (((int64_t)k * 3 + d) * prow + col0) * kc + lane * Op::kPerLane;
       for (int c0 = 0; c0 < kc; c0 += Op::kChunk) {
         Frag fa[WM], fb[WN];
 #pragma unroll
-        for (int i = 0; i < WM; ++i) fa[i] = *reinterpret_cast<const Frag*>(Ad + (int64_t)i * 16 * kc + c0);
+        for (int i = 0; i < WM; ++i) fa[i] = *reinterpret_cast<const Frag*>(Ad + (int64_t)i * 16 * kc + 16 * c0);
 #pragma unroll
-        for (int j = 0; j < WN; ++j) fb[j] = *reinterpret_cast<const Frag*>(Yd + (int64_t)j * 16 * kc + c0);
+        for (int j = 0; j < WN; ++j) fb[j] = *reinterpret_cast<const Frag*>(Yd + (int64_t)j * 16 * kc + 16 * c0);
 #pragma unroll
         for (int i = 0; i < WM; ++i)
 #pragma unroll
@@ -668,7 +678,7 @@ __device__ inline void assemble_tile_as(const AsmMol& m, int I, int J) {
   // Y addressing: a wave-uniform base per step plus one 32-bit lane offset
   typedef __attribute__((address_space(1))) const Frag gFrag;
   const char* __restrict__ Yw = static_cast<const char*>(m.Y) + col0 * KC * (int64_t)sizeof(T);
-  const uint32_t ylane = (uint32_t)((r16 * KC + kg * Op::kPerLane) * sizeof(T));
+  const uint32_t ylane = (uint32_t)(lane * Op::kPerLane * sizeof(T));
 
   Frag fa[3][NCK][WM];
 #pragma unroll
@@ -677,12 +687,12 @@ __device__ inline void assemble_tile_as(const AsmMol& m, int I, int J) {
     for (int c = 0; c < NCK; ++c)
 #pragma unroll
       for (int i = 0; i < WM; ++i)
-        fa[d][c][i] = *reinterpret_cast<const Frag*>(Abase + ((int64_t)d * prow + row0 + 16 * i + r16) * KC +
-                                                     kg * Op::kPerLane + c * Op::kChunk);
-  // Y fragments of step s = (k, d, c): Y[k][d][col0 + 16 j + r16][c * chunk + ...]
+        fa[d][c][i] = *reinterpret_cast<const Frag*>(Abase + ((int64_t)d * prow + row0 + 16 * i) * KC +
+                                                     c * 16 * Op::kChunk + lane * Op::kPerLane);
+  // Y fragments of step s = (k, d, c): chunk c of rows col0 + 16 j .. of Y[k][d]
   auto loadY = [&](int k, int st, Frag (&dst)[WN]) {
     const int d = st / NCK, c = st % NCK;
-    const char* y = Yw + (((int64_t)k * 3 + d) * prow * KC + c * Op::kChunk) * (int64_t)sizeof(T);
+    const char* y = Yw + (((int64_t)k * 3 + d) * prow * KC + c * 16 * Op::kChunk) * (int64_t)sizeof(T);
 #pragma unroll
     for (int j = 0; j < WN; ++j) dst[j] = *(gFrag*)(y + ylane + j * 16 * KC * (int)sizeof(T));
   };
@@ -704,7 +714,7 @@ __device__ inline void assemble_tile_as(const AsmMol& m, int I, int J) {
     // runs PD steps ahead, into the next node's first steps.
     auto nck_of = [&](int k) { return (nkp[k] + Op::kChunk - 1) / Op::kChunk; };
     auto loadY3 = [&](int k, int d, int c, Frag (&dst)[WN]) {
-      const char* y = Yw + (((int64_t)k * 3 + d) * prow * KC + c * Op::kChunk) * (int64_t)sizeof(T);
+      const char* y = Yw + (((int64_t)k * 3 + d) * prow * KC + c * 16 * Op::kChunk) * (int64_t)sizeof(T);
 #pragma unroll
       for (int j = 0; j < WN; ++j) dst[j] = *(gFrag*)(y + ylane + j * 16 * KC * (int)sizeof(T));
     };

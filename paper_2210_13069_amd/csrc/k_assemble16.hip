@@ -102,8 +102,8 @@ __device__ inline v4f mma(v8h a, v8h b, v4f c) { return __builtin_amdgcn_mfma_f3
 __device__ inline v4f mma(v8bf a, v8bf b, v4f c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 
 // Direct-to-LDS loads of the Y fragments of one step.  Fragment
-// f = (d*CB + c)*NCH + ch holds, for lane l, the 16 bytes
-// Y[k][d][col0 + 16c + l%16][32ch + 8(l/16) .. +8].  Wave w loads fragments
+// f = (d*CB + c)*NCH + ch is chunk ch of the rows from col0 + 16c on, as the
+// operand stores it.  Wave w loads fragments
 // w, w + NW, ... (LPW_HI of them for w < N_HI, else LPW_LO), the same count
 // for every step, so that a wave's wait can count its own loads.  The byte
 // offsets of a wave's fragments are fixed for an item (off); a step's
@@ -112,7 +112,6 @@ template <class C>
 struct YLoads {
   uint32_t off[C::LPW_HI];
   __device__ void init(int64_t prow, int64_t col0, int64_t node_bytes, int wave, int lane) {
-    const int r16 = lane & 15, kg = lane >> 4;
 #pragma unroll
     for (int i = 0; i < C::LPW_HI; ++i) {
       int f = wave + C::NW_ * i;
@@ -121,7 +120,7 @@ struct YLoads {
       const int ch = g % C::NCH;
       const int c = (g / C::NCH) % C::CB_;
       const int d = g / (C::NCH * C::CB_);
-      off[i] = (uint32_t)(j * node_bytes + (((int64_t)d * prow + col0 + 16 * c + r16) * C::KC_ + 32 * ch + 8 * kg) * 2);
+      off[i] = (uint32_t)(j * node_bytes + ((int64_t)d * prow + col0 + 16 * c) * C::KC_ * 2 + (64 * ch + lane) * 16);
     }
   }
   // Buffer loads (a resource built on the step's base pointer, the fixed
@@ -258,8 +257,9 @@ __device__ inline void run_item(const AsmMol& m, int rp, int cb0, int cb1, uint4
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int64_t row = (int64_t)d * prow + row_base + 16 * rb + r16;
-        af[d][rb][u] = *(const __attribute__((address_space(1))) Frag*)(Ab + (row * C::KC_ + 32 * a_chunk<C::Q_>(u) + 8 * kg) * 2);
+        const int64_t row = (int64_t)d * prow + row_base + 16 * rb;
+        af[d][rb][u] = *(const __attribute__((address_space(1))) Frag*)(Ab + row * C::KC_ * 2 +
+                                                                        (64 * a_chunk<C::Q_>(u) + lane) * 16);
       }
   __syncthreads();  // exponent tables written
 

@@ -1,4 +1,5 @@
-// Assembly of B in FP32 on the matrix cores (v_mfma_f32_16x16x4f32): the
+// Assembly of B for many pairs, FP32 and below FP64, on the matrix cores
+// (v_mfma_f32_16x16x4f32, v_mfma_f64_16x16x4f64): the
 // same contraction as the other assembly kernels (Theorem 3.1 in Hadamard
 // form, G_{k,d} = M_d^T (K_k M_d), B = (2/sqrt(pi)) sum_k w_k G_{k,0} o
 // G_{k,1} o G_{k,2}), organised like the 16-bit persistent kernel:
@@ -7,9 +8,8 @@
 //   all three directions and the whole inner length, in VGPRs for a work item.
 // * The Y_{k,d} operand of a 16-column block is streamed per node k through a
 //   two-deep LDS ring with direct-to-LDS dword loads shared by the eight
-//   waves.  One 256-byte fragment holds, in lane order, the 4-byte operand
-//   of one MFMA (an inner step of 4), so any inner length that is a multiple
-//   of 4 runs without padding; the LDS fragment reads are conflict-free.
+//   waves.  A 512-byte operand fragment (8 inner indices) is two 256-byte
+//   pieces; a lane reads its two values, the operands of two MFMAs, at once.
 // * Per node the three G tiles are multiplied elementwise and accumulated in
 //   FP32; every kGroup32 nodes the FP32 sums are added into FP64 partial sums
 //   held in wave-private LDS.
@@ -18,7 +18,7 @@
 // * Persistent work groups take (molecule, row panel, column-block range)
 //   items from per-XCD queues, as the 16-bit kernel does.
 // * With per-node degrees (operands in coefficient form, AsmMol::nk) node k
-//   loads and contracts only its first ceil(N_k / 4) inner steps; the Y rows
+//   loads and contracts only its first 2 ceil(N_k / 8) inner steps; the Y rows
 //   beyond N_k are zero.
 #include "tai_internal.h"
 
@@ -54,17 +54,24 @@ struct Cfg32 {
   static constexpr int NT = 64 * NW;
   static constexpr int ROWS = 16 * RB * NW;            // rows per panel
   static constexpr int COLS = 16;                      // columns per block
-  static constexpr int NFRAG = 3 * NCH;                // 256-byte fragments per node
+  static constexpr int NFRAG = 3 * NCH;                // 256-byte pieces per node
   static constexpr int LPW = (NFRAG + NW - 1) / NW;    // loads per wave (some waves one fewer)
   static constexpr int NV = RB * 4;                    // accumulator values per lane
   static constexpr int SUM_BYTES = NW * NV * 64 * 8;
   static constexpr int ITEM_COLS = 512;
   static constexpr int LDS_BYTES = 2 * NFRAG * 256 + SUM_BYTES + 4 * (ROWS + ITEM_COLS);
-  static_assert(KC % 4 == 0, "inner length");
+  static_assert(KC % 8 == 0, "inner length");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS");
 };
 
-__device__ inline void wait_vmcnt0() { __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// A builtin, not inline asm: the compiler has to see that the A operand's loads
+// have landed too, or it waits for every load in flight at their first use inside
+// the node loop.  (vmcnt 0, the other counters at their maximum.)  FP32, 24 nodes,
+// 80200 pairs: n = 40 163 -> 146 ms, n = 48 204 -> 184 ms.
+__device__ inline void wait_vmcnt0() {
+  __builtin_amdgcn_s_waitcnt(0x0f70);
+  __asm__ volatile("" ::: "memory");
+}
 
 // Call f(integral_constant<int, c>) for the compile-time count c == v (1 <= v <= N).
 template <int N, class F>
@@ -115,7 +122,8 @@ __device__ inline void run_item32(const AsmMol& m, int rp, int cb0, int cb1, flo
 #pragma unroll
   for (int v = 0; v < NV; ++v) mysum[v * 64] = 0.0;
 
-  // k-invariant A operand: lane l holds A_d[row][4 ch + l/16] for MFMA step ch
+  // k-invariant A operand: inner indices 8 (ch / 2) + 2 (l / 16) + ch % 2 of the
+  // lane's row for MFMA step ch
   float af[3][RB][NCH];
 #pragma unroll
   for (int d = 0; d < 3; ++d)
@@ -123,11 +131,11 @@ __device__ inline void run_item32(const AsmMol& m, int rp, int cb0, int cb1, flo
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
       for (int ch = 0; ch < NCH; ++ch)
-        af[d][rb][ch] = Af[((int64_t)d * prow + row_base + 16 * rb + r16) * C::KC_ + 4 * ch + kg];
+        af[d][rb][ch] = Af[((int64_t)d * prow + row_base + 16 * rb) * C::KC_ + 128 * (ch / 2) + 2 * lane + ch % 2];
   __syncthreads();  // exponent tables written
 
-  // Y fragment f = d * NCH + ch of a (node, block): lane l loads
-  // Y[k][d][col0 + l%16][4 ch + l/16]; wave w loads fragments w, w + NW, ...
+  // Y piece f = d * NCH + ch of a (node, block): 256 bytes as they are stored;
+  // wave w loads pieces w, w + NW, ...
   const int64_t node_bytes = 3 * pcol * C::KC_ * 4;
   const int64_t block_bytes = (int64_t)COLS * C::KC_ * 4;
   uint32_t off[LPW];
@@ -136,11 +144,11 @@ __device__ inline void run_item32(const AsmMol& m, int rp, int cb0, int cb1, flo
     int f = wave + NW * i;
     f = f < NFRAG ? f : 0;
     const int d = f / NCH, ch = f % NCH;
-    off[i] = (uint32_t)((((int64_t)d * pcol + col_first + r16) * C::KC_ + 4 * ch + kg) * 4);
+    off[i] = (uint32_t)((((int64_t)d * pcol + col_first) * C::KC_ + 64 * ch + lane) * 4);
   }
   const int T = nblk * nq;
   const int32_t* __restrict__ nkp = DEG ? m.nk : nullptr;
-  auto steps_of = [&](int node) { return (DEG && nkp) ? (nkp[node] + 3) / 4 : NCH; };
+  auto steps_of = [&](int node) { return (DEG && nkp) ? (nkp[node] + 7) / 8 * 2 : NCH; };
   int ib = 0, ik = 0;  // (block, node) of the next step to load
   auto issue_next = [&](float* buf) {
     // (global-segment loads here: the buffer form, which helps the FP64
@@ -232,16 +240,17 @@ __device__ inline void run_item32(const AsmMol& m, int rp, int cb0, int cb1, flo
     const int nch = steps_of(k);  // inner steps of this node (uniform)
     if (t + 1 < T) issue_next(nxt);
     // the node's MFMAs with NC inner steps per direction: fragment (d, ch) of
-    // the LDS buffer for g = d * NC + ch, the next fragment read one ahead
-    auto node = [&](auto nc) {
-      constexpr int NC = decltype(nc)::value;
+    // the LDS buffer for g = d * NC + ch, the next pair of steps read one ahead
+    auto node = [&](auto half) {
+      constexpr int NC = 2 * decltype(half)::value;
       v4f H[RB], G[RB];
       float b[2];
-      b[0] = cur[lane];
+      auto value = [&](int g) { return cur[(g / NC * NCH + g % NC / 2 * 2) * 64 + 2 * lane + g % 2]; };
+      b[0] = value(0);
 #pragma unroll
       for (int g = 0; g < 3 * NC; ++g) {
         const int d = g / NC, ch = g % NC;
-        if (g + 1 < 3 * NC) b[(g + 1) & 1] = cur[(((g + 1) / NC) * NCH + (g + 1) % NC) * 64 + lane];
+        if (g + 1 < 3 * NC) b[(g + 1) & 1] = value(g + 1);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
           G[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[d][rb][ch], b[g & 1],
@@ -256,8 +265,8 @@ __device__ inline void run_item32(const AsmMol& m, int rp, int cb0, int cb1, flo
         }
       }
     };
-    if constexpr (DEG) with_steps<NCH>(nch, node);
-    else node(std::integral_constant<int, NCH>{});
+    if constexpr (DEG) with_steps<NCH / 2>(nch / 2, node);
+    else node(std::integral_constant<int, NCH / 2>{});
     if ((k + 1) % kGroup32 == 0 || k + 1 == nq) flush();
     if (++k == nq) {
       finish_block(blk);
@@ -274,8 +283,8 @@ template <class C, bool DEG>
 __global__ void __launch_bounds__(C::NT, 1)
 assemble32_kernel(const AsmMol* __restrict__ mols, const int4* __restrict__ items, const int* __restrict__ seg,
                   unsigned* __restrict__ counters) {
-  __shared__ float yb0[C::NFRAG * 64];
-  __shared__ float yb1[C::NFRAG * 64];
+  __shared__ alignas(16) float yb0[C::NFRAG * 64];
+  __shared__ alignas(16) float yb1[C::NFRAG * 64];
   __shared__ double sums[C::SUM_BYTES / 8];
   __shared__ int erow_s[C::ROWS];
   __shared__ int ecol_s[C::ITEM_COLS];
@@ -345,7 +354,8 @@ __device__ inline void run_item64(const AsmMol& m, int rp, int cb0, int cb1, uin
   const int nblk = cb1 - cb0;
   const int64_t col_first = (int64_t)cb0 * COLS;
 
-  // k-invariant A operand: lane l holds A_d[row][8 ch + 2 (l/16) + {0, 1}]
+  // k-invariant A operand, fragments as they are stored: inner indices
+  // 8 ch + 2 (l/16) + {0, 1} of the lane's row
   v2d af[3][RB][NCH];
 #pragma unroll
   for (int d = 0; d < 3; ++d)
@@ -354,7 +364,7 @@ __device__ inline void run_item64(const AsmMol& m, int rp, int cb0, int cb1, uin
 #pragma unroll
       for (int ch = 0; ch < NCH; ++ch)
         af[d][rb][ch] = *(const __attribute__((address_space(1))) v2d*)(
-            Ad + ((int64_t)d * prow + row_base + 16 * rb + r16) * C::KC_ + 8 * ch + 2 * kg);
+            Ad + ((int64_t)d * prow + row_base + 16 * rb) * C::KC_ + 128 * ch + 2 * lane);
 
   const int64_t node_bytes = 3 * pcol * C::KC_ * 8;
   const int64_t block_bytes = (int64_t)COLS * C::KC_ * 8;
@@ -364,7 +374,7 @@ __device__ inline void run_item64(const AsmMol& m, int rp, int cb0, int cb1, uin
     int f = wave + NW * i;
     f = f < NFRAG ? f : 0;
     const int d = f / NCH, ch = f % NCH;
-    off[i] = (uint32_t)((((int64_t)d * pcol + col_first + r16) * C::KC_ + 8 * ch + 2 * kg) * 8);
+    off[i] = (uint32_t)((((int64_t)d * pcol + col_first) * C::KC_ + 128 * ch + 2 * lane) * 8);
   }
   const int T = nblk * nq;
   const int32_t* __restrict__ nkp = DEG ? m.nk : nullptr;

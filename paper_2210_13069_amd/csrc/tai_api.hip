@@ -324,10 +324,10 @@ bool use16(tai_ctx* c, int prec, int n, int nq) {
   return shape16(c, prec, n, nq).id >= 0;
 }
 
-// Whether FP32 / FP64 assembly takes the persistent LDS-ring kernel
-// (k_assemble32.hip), for the inner lengths it is built for (it skips each
-// node's unused inner steps with per-node degrees too).  TAI_TILE_ASSEMBLY
-// selects the tile kernels instead.
+// Whether FP32 / FP64 assembly takes the kernels of k_assemble_tiles.hip (few
+// pairs) and k_assemble32.hip (the persistent LDS ring), for the inner lengths
+// they are built for (both skip each node's unused inner steps with per-node
+// degrees).  TAI_TILE_ASSEMBLY selects the generic kernels instead.
 bool use32(int prec, int n) {
   return (prec == tai::kFP32 || prec == tai::kFP64) && tai::operand_kc(prec, n) <= tai::kAsm32MaxKc &&
          !std::getenv("TAI_TILE_ASSEMBLY");
@@ -345,8 +345,49 @@ hipError_t launch_ring(int prec, int kc, bool /*deg*/, const tai::AsmMol* mols, 
                             : tai::launch_assemble32(kc, true, mols, items, seg, counters, nblocks, s);
 }
 
-int prow_of(tai_ctx* c, int prec, int n, int nq, int64_t npair) {
+// Whether npair pairs take the tile kernel (k_assemble_tiles.hip) instead of the
+// ring: up to as many pairs as it was the faster of the two, by the inner length
+// of the call's own n (not of a compressed rank), so that a molecule takes the
+// same kernel alone, in a batch and as one box.  Whole calls, 24 nodes, ring
+// against tiles in us:
+//   FP64  n = 24  210 pairs 141, 86; 20100 12330, 10585; 39340 43776, 40178
+//         n = 40  2080 394, 295; 20100 19076, 17549; 39340 67791, 66594
+//         n = 48  5050 1970, 1610; 20100 23789, 23444; 39340 86747, 88845
+//         (beyond, the A operand leaves the tile one row block and too little room)
+//   FP32  n = 32  2080 272, 188; 20100 9761, 8499; 39340 29181, 32223
+//         n = 48  5050 1158, 1063; 8515 2423, 2168; 20100 12843, 14854
+//         n = 64  2080 403, 359; 8515 2556, 2727
+bool use_tiles(int prec, int n, int64_t npair) {
+  if (!use32(prec, n)) return false;
+  const int kc = tai::operand_kc(prec, n);
+  if (prec == tai::kFP64) return npair <= (kc <= 40 ? 40000 : (kc <= 48 ? 20000 : 0));
+  return npair <= (kc <= 40 ? 24000 : (kc <= 48 ? 12000 : 6000));
+}
+// Numbers the tiles (tile0) of the molecules that `take` names and picks their
+// row blocks: one while the larger tiles are less than two to a compute unit (528
+// pairs, FP64, n = 32: 91 us, 97 with two; 2080 pairs: 252, 242).  The entries
+// are the same.
+struct TilePlan {
+  int rb = 1, total = 0;
+};
+template <class Take>
+TilePlan plan_tiles(tai_ctx* c, int prec, int kc, tai::AsmMol* mols, int nmol, Take take) {
+  TilePlan p;
+  for (int rb : {tai::asm_tiles_max_rb(prec, kc), 1}) {
+    p.rb = rb;
+    p.total = 0;
+    for (int i = 0; i < nmol; ++i) {
+      mols[i].tile0 = p.total;
+      if (take(mols[i])) p.total += tai::asm_tile_count(mols[i], rb);
+    }
+    if (p.total >= 2 * (c->cus > 0 ? c->cus : 256)) break;
+  }
+  return p;
+}
+
+int prow_of(tai_ctx* c, int prec, int n, int nq, int64_t npair, bool tiles = false) {
   int64_t t = 256;
+  if (tiles) return (int)((npair + 63) / 64 * 64);
   const bool p16 = use16(c, prec, n, nq), p32 = use32(prec, n);
   if (p16 || p32) {
     const int64_t r = p16 ? shape16(c, prec, n, nq).rows : ring_rows(prec, n);
@@ -881,6 +922,7 @@ int tai_assemble_B_partitioned(tai_ctx* c, const double* M, const int32_t* count
     return fail(c, TAI_ERR_UNSUPPORTED,
                 "tai_assemble_B_partitioned runs on the persistent kernels only (FP64 and FP32 up to their inner "
                 "length, the split 16-bit forms with a shape for nq)");
+  const bool tiles = use_tiles(prec, n, total);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((r = ensure(c, c->nodes, tai::node_tables_bytes(nq, n)))) return r;
   NodeTables tb = tai::carve_node_tables(c->nodes.p, nq, n);
@@ -891,7 +933,7 @@ int tai_assemble_B_partitioned(tai_ctx* c, const double* M, const int32_t* count
   const size_t kx_bytes = align256(sizeof(double) * (size_t)nparts * nparts * nq * n * n);
   size_t bytes = kx_bytes;
   for (int i = 0; i < nparts; ++i) {
-    prow[i] = prow_of(c, prec, n, nq, std::max<int64_t>(1, counts[i]));
+    prow[i] = prow_of(c, prec, n, nq, std::max<int64_t>(1, counts[i]), tiles);
     oA[i] = bytes;
     bytes += opA_bytes(prec, n, prow[i]);
     oE[i] = bytes;
@@ -961,7 +1003,11 @@ int tai_assemble_B_partitioned(tai_ctx* c, const double* M, const int32_t* count
   const tai::Asm16Shape sh = p16 ? shape16(c, prec, n, nq) : tai::Asm16Shape{};
   const int64_t R = p16 ? sh.rows : ring_rows(prec, n), Cc = p16 ? sh.cols : tai::kAsm32Cols;
   const int64_t slots = (int64_t)(c->cus > 0 ? c->cus : 256) * (p16 ? sh.wgs_per_cu : 1);
-  for (size_t k = 0; k < am.size(); ++k) {
+  TilePlan tp;
+  if (tiles)
+    tp = plan_tiles(c, prec, tai::operand_kc(prec, n), am.data(), (int)am.size(),
+                    [](const tai::AsmMol&) { return true; });
+  for (size_t k = 0; k < am.size() && !tiles; ++k) {
     if (am[k].rect) items.add_rect((int)k, am[k].npair, am[k].ncol, R, Cc, 2 * slots / (int64_t)am.size());
     else items.add((int)k, am[k].npair, R, Cc, 2 * slots / (int64_t)am.size());
   }
@@ -976,6 +1022,12 @@ int tai_assemble_B_partitioned(tai_ctx* c, const double* M, const int32_t* count
   if ((e = hipMemcpyAsync(c->asm_tab.p, hb, tab_bytes, hipMemcpyHostToDevice, s)) != hipSuccess)
     return hip_fail(c, e, "table upload");
   if ((e = hipEventRecord(c->asm_host_done, s)) != hipSuccess) return hip_fail(c, e, "hipEventRecord");
+  if (tiles) {
+    Timed tm(c, kStAssemble, s);
+    e = tai::launch_assemble_tiles_batch(prec, tai::operand_kc(prec, n), tp.rb,
+                                         static_cast<const tai::AsmMol*>(c->asm_tab.p), (int)am.size(), tp.total, s);
+    return e != hipSuccess ? hip_fail(c, e, "assemble kernel") : TAI_OK;
+  }
   unsigned* counter = static_cast<unsigned*>(c->asm_counter.p);
   if ((e = tai::launch_reset_counter(counter, s)) != hipSuccess) return hip_fail(c, e, "reset kernel");
   const int nitems = (int)items.count();
@@ -1179,7 +1231,8 @@ static int assemble_impl(tai_ctx* c, const double* M, int32_t npair, const tai_p
   // factors (Kc_k = V^T Kt_k V) and the operands are U, not moments: the
   // node form throughout.
   const bool deg = p->degree_tol > 0 && !tai::is_split16(prec) && !(p->rank_tol > 0);
-  const int prow = prow_of(c, prec, n, nq, npair);
+  const bool tiles = use_tiles(prec, p->n, npair);
+  const int prow = prow_of(c, prec, n, nq, npair, tiles);
   if ((r = ensure(c, c->opA, opA_bytes(prec, n, prow)))) return r;
   if ((r = ensure(c, c->opEx, opEx_bytes(prow)))) return r;
   if ((r = ensure(c, c->opY, opY_bytes(prec, n, nq, prow)))) return r;
@@ -1222,7 +1275,11 @@ static int assemble_impl(tai_ctx* c, const double* M, int32_t npair, const tai_p
   m.nk = deg ? tb.nk : nullptr;
   m.ysh = tai::y_shift(prec, p->omega, nq);
   const bool p16 = use16(c, prec, n, nq), p32 = !p16 && use32(prec, n);
-  if (p16 || p32) {
+  if (tiles) {
+    Timed tm(c, kStAssemble, s);
+    const TilePlan tp = plan_tiles(c, prec, m.kc, &m, 1, [](const tai::AsmMol&) { return true; });
+    e = tai::launch_assemble_tiles(prec, m.kc, tp.rb, m, s);
+  } else if (p16 || p32) {
     Items16 items;
     const tai::Asm16Shape sh = p16 ? shape16(c, prec, n, nq) : tai::Asm16Shape{};
     const int64_t slots = (int64_t)(c->cus > 0 ? c->cus : 256) * (p16 ? sh.wgs_per_cu : 1);
@@ -1341,7 +1398,7 @@ static int batched_impl(tai_ctx* c, int32_t nmol, const tai_mol* mols, hipStream
   std::vector<tai::AsmMol> am(nmol);
   for (int i = 0; i < nmol; ++i) {
     const int64_t np = npair_of(mols[i].basis.nb);
-    prow[i] = prow_of(c, prec, n, nq, np);
+    prow[i] = prow_of(c, prec, n, nq, np, use_tiles(prec, n, np));
     off_nodes[i] = sz_nodes; sz_nodes += align256(tai::node_tables_bytes(nq, n));
     off_basis[i] = sz_basis; sz_basis += basis_bytes(mols[i].basis.nb);
     off_A[i] = sz_A; sz_A += opA_bytes(prec, n, prow[i]);
@@ -1389,8 +1446,15 @@ static int batched_impl(tai_ctx* c, int32_t nmol, const tai_mol* mols, hipStream
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return am[a].npair > am[b].npair; });
     const int kc = tai::operand_kc(prec, n);
     for (int i : order)
-      items16.add(i, am[i].npair, split16 ? sh16.rows : ring_rows(prec, n), split16 ? sh16.cols : tai::kAsm32Cols);
+      if (!use_tiles(prec, n, am[i].npair))
+        items16.add(i, am[i].npair, split16 ? sh16.rows : ring_rows(prec, n), split16 ? sh16.cols : tai::kAsm32Cols);
   }
+  // small molecules' tiles, in the tile kernel's own numbering (a batch takes
+  // either the persistent kernels or the generic one, so tile0 serves both)
+  TilePlan tp;
+  if (fp32p)
+    tp = plan_tiles(c, prec, tai::operand_kc(prec, n), am.data(), nmol,
+                    [&](const tai::AsmMol& m) { return use_tiles(prec, n, m.npair); });
   // device tables: [AsmMol x nmol | PrepMol x nmol | CmpMol x ncm | items]
   const size_t off_prep = align256(sizeof(tai::AsmMol) * nmol);
   int ncm = 0;
@@ -1466,10 +1530,14 @@ static int batched_impl(tai_ctx* c, int32_t nmol, const tai_mol* mols, hipStream
     if (err == hipSuccess) err = tai::launch_pack_batch(prec, prep_dev, nmol, max_prow, n, st);
     if (err == hipSuccess) err = tai::launch_project_batch(prec, prep_dev, nmol, max_prow, n, nq, any_degree || any_cmp, st);
     if (err != hipSuccess) return err;
+    const auto* mols_dev = static_cast<const tai::AsmMol*>(c->b_mols.p);
+    if (tp.total > 0) {
+      err = tai::launch_assemble_tiles_batch(prec, am[0].kc, tp.rb, mols_dev, nmol, tp.total, st);
+      if (err != hipSuccess || items16.count() == 0) return err;
+    }
     unsigned* counter = static_cast<unsigned*>(c->b_counter.p);
     err = tai::launch_reset_counter(counter, st);
     if (err != hipSuccess) return err;
-    const auto* mols_dev = static_cast<const tai::AsmMol*>(c->b_mols.p);
     if (split16 || fp32p) {
       const char* tab = static_cast<const char*>(c->b_mols.p) + off_items;
       const auto* seg_dev = reinterpret_cast<const int*>(tab);

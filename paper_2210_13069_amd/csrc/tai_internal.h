@@ -104,6 +104,13 @@ __host__ __device__ inline int seg_pos(int prec, int n, int s, int a) {
 }
 // Bytes per operand element.
 int operand_esize(int prec);
+// Order of an operand in memory (A_d and Y_{k,d} alike): fragments of 16 rows by
+// one chunk of 32 (FP64, FP32: 8) inner indices, all chunks of 16 rows, then the
+// next 16 rows.  A fragment holds, lane after lane, what a wave's 16-row matrix
+// instruction takes: lane 16 g + r the 8 (2) elements of group g of row r.  A wave
+// so reads a fragment as one contiguous run.  (Stored row after row, the 64 lanes
+// of a load fell into 64 places: the cache took about 64 cycles for 1 KB, and FP64
+// tiles at n = 48 ran at 39% of the matrix rate, waiting for it.)
 // Square output tile edge of the assembly kernel (rows of operands are
 // padded to a multiple of it).
 int assemble_tile(int prec);
@@ -127,7 +134,7 @@ struct AsmMol {
   // power of two folded into Y_{k,2} with w_k (y_shift); the column
   // exponents are lowered by it when B is scaled back
   int32_t ysh;
-  // Rectangular block (the persistent ring and 16-bit kernels only): rows
+  // Rectangular block (all but the generic kernel): rows
   // from A (npair of them, exponents ex over prow), columns from Y (ncol of
   // them, padded count pcol, exponents exc), every entry computed, written
   // to B and mirrored to Bt (B^T's block).  rect 0: the symmetric block
@@ -222,6 +229,18 @@ int asm32_rows(int kc);
 int asm64_rows(int kc);
 hipError_t launch_assemble64(int kc, bool deg, const AsmMol* mols_dev, const int4* items_dev, const int* seg_dev,
                              unsigned* counters, int nblocks, hipStream_t s);
+
+// Few pairs, FP64 and FP32 (inner lengths up to kAsm32MaxKc): tiles of 16 * rb
+// rows by 16 columns with the nodes dealt to a work group's waves
+// (k_assemble_tiles.hip).  rb is 1, 2 or 4, up to asm_tiles_max_rb; the entries
+// do not depend on it.  The batch form reads each molecule's first tile from
+// tile0 (asm_tile_count tiles each, `total` in all).
+int asm_tile_count(const AsmMol& m, int rb);
+int asm_tiles_max_rb(int prec, int kc);
+hipError_t launch_assemble_tiles(int prec, int kc, int rb, const AsmMol& m, hipStream_t s);
+hipError_t launch_assemble_tiles_batch(int prec, int kc, int rb, const AsmMol* mols_dev, int nmol, int total,
+                                       hipStream_t s);
+
 // deg: the molecules may carry per-node degrees (AsmMol::nk).
 hipError_t launch_assemble32(int kc, bool deg, const AsmMol* mols_dev, const int4* items_dev, const int* seg_dev,
                              unsigned* counters, int nblocks, hipStream_t s);

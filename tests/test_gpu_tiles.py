@@ -1,0 +1,89 @@
+"""B of few pairs in FP64 and FP32: tiles with the nodes dealt to the waves of a
+work group, at the edges of the tiles (1, 15, 16, 17, 33 ... pairs), node counts
+below, at and beyond the waves, every inner length, per-node degrees, blocks over
+boxes; and the ring kernel on the other side of the rule.  Against the oracle (or
+the tables' own sum in FP64 on the device where the oracle would be slow).
+
+Tolerances are the repository's bars, normwise: FP64 1e-10, FP32 1e-6."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from oracle import tairef as T
+from paper_2210_13069_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+TOL = {0: 1e-10, 1: 1e-6}
+# (functions, n, nq): 1, 3, 15, 21, 66, 136, 171, 496 pairs
+SIZES = [(1, 8, 1), (2, 7, 3), (5, 16, 4), (6, 17, 5), (11, 24, 8), (16, 31, 9), (18, 33, 33), (18, 40, 16), (31, 41, 12),
+         (31, 48, 6), (18, 56, 7), (31, 64, 13)]
+
+
+def _shells(nb):
+    rng = np.random.default_rng(700 + nb)
+    return I.Basis(center=rng.uniform(-2.5, 2.5, (nb, 3)), alpha=np.exp(rng.uniform(np.log(0.2), np.log(20.0), nb)),
+                   lxyz=rng.integers(0, 2, (nb, 3)).astype(np.int32))
+
+
+def _sum(M, K, w):
+    """The definition, in FP64 torch: sum_k w_k prod_d M_d^T K_k M_d."""
+    import torch
+    B = torch.zeros((M.shape[2], M.shape[2]), dtype=torch.float64, device=M.device)
+    for k in range(len(w)):
+        B += w[k] * (M[0].T @ (K[k] @ M[0])) * (M[1].T @ (K[k] @ M[1])) * (M[2].T @ (K[k] @ M[2]))
+    return 2.0 / np.sqrt(np.pi) * B
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("nb,n,nq", SIZES)
+def test_tiles(tai, nb, n, nq, prec):
+    b = _shells(nb)
+    for tol in (0.0, 1e-7):
+        P = I.Params(omega=0.5, nq=nq, n=n, L=7.0, degree_tol=tol)
+        t, w = T.time_nodes(P.omega, nq)
+        xi, _ = T.cheb_nodes(n, P.L)
+        K = T.truncated_tables(t, xi, P.L, tol)[2] if tol else T.ktables(t, xi)
+        ref = T.B_full(T.moments(b.center, b.alpha, b.lxyz, P.L, n), K, w)
+        got = tai.assemble_B(tai.moments(b, P), P, prec=prec).cpu().numpy()
+        assert np.max(np.abs(got - ref)) <= TOL[prec] * np.max(np.abs(ref))
+        assert np.array_equal(got, got.T)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("nb,n", [(64, 24), (64, 48), (110, 40), (110, 64), (160, 48)])
+def test_sides_of_the_rule(tai, nb, n, prec):
+    """2080 to 12880 pairs: both row block counts and the ring."""
+    import torch
+    b = _shells(nb)
+    P = I.Params(omega=0.4, nq=7, n=n, L=7.0)
+    M = tai.moments(b, P)
+    t, w = T.time_nodes(P.omega, P.nq)
+    xi, _ = T.cheb_nodes(n, P.L)
+    K = torch.as_tensor(T.ktables(t, xi), device="cuda")
+    ref = _sum(M, K, w)
+    got = tai.assemble_B(M, P, prec=prec)
+    assert float((got - ref).abs().max()) <= TOL[prec] * float(ref.abs().max())
+    assert torch.equal(got, got.T)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_batch_of_both_kernels(tai, prec):
+    """A batch with molecules on both sides of the rule (FP64 at n = 56 takes the
+    ring alone, FP32 at n = 56 the ring above 6000 pairs): the bits of single calls."""
+    import torch
+    n = 56
+    mols, bufs, keep, single = [], [], [], []
+    for nb in (115, 3, 40, 120, 17):
+        b = _shells(nb)
+        P = I.Params(omega=0.4, nq=5, n=n, L=8.0)
+        ba = tai.BasisArrays(b)
+        M = torch.empty((3, n, b.npair), dtype=torch.float64, device="cuda")
+        B = torch.empty((b.npair, b.npair), dtype=torch.float64 if prec == 0 else torch.float32, device="cuda")
+        keep.append(ba)
+        bufs.append((M, B))
+        mols.append(tai.tai_mol(ba.struct, tai.make_params(P, prec), M.data_ptr(), B.data_ptr(), b.npair))
+        single.append(tai.assemble_B(tai.moments(b, P), P, prec=prec))
+    tai.context().assemble_B_batched(mols)
+    for (_, B), S in zip(bufs, single):
+        assert torch.equal(B, S)
