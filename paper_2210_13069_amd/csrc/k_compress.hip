@@ -31,6 +31,9 @@
 //  * U and Kc: plain FP64 products with V in LDS.
 #include "tai_internal.h"
 
+#include <cmath>
+#include <type_traits>
+
 namespace tai {
 namespace {
 
@@ -260,173 +263,270 @@ gram_sum_batch_kernel(const CmpMol* __restrict__ tab) {
 // order m with a zero row and column, which no rotation touches).  Outputs
 // sigma[r] = sqrt(max(lambda_r, 0)) in decreasing order, V[a][r] the matching
 // unit eigenvectors, and *rank.
-constexpr int kJacobiThreads = 1024;
+//   Round-robin pairing: index 0 stays in slot 0, the others move one slot down a
+// round (slot 1 to slot m - 1), and a round rotates the indices in slots i and
+// m-1-i.  The matrix is kept in slot order and every round writes it, moved on,
+// into the other of two buffers: all addresses of A are the same in every round.
+//   What bounds it: one work group's chain of m - 1 rounds a sweep, 6 to 9 sweeps.
+// A round holds one barrier: wave 0 works out the angles of the next round, from
+// the entries that this round's rotations leave at its pivots, while the other
+// waves rotate the matrix and the eigenvectors (eight waves, so that a worker's
+// addresses stay in registers).  n = 48, both passes of a compression: 940 us with
+// angles, matrix and eigenvectors in turn and the whole matrix stored, 576 us.
+constexpr int kJacobiThreads = 512;
+constexpr int kJacobiWorkers = kJacobiThreads - 64;
+
+// (x, y) rotated by (c, s); written out so that wave 0 and the workers round alike
+__device__ __forceinline__ double rot_lo(double2 r, double x, double y) { return fma(r.x, x, -(r.y * y)); }
+__device__ __forceinline__ double rot_hi(double2 r, double x, double y) { return fma(r.y, x, r.x * y); }
+
+// 1 / sqrt(x) for normal x: the instruction's estimate, e = 1 - x y^2, and the
+// series of (1 - e)^(-1/2) to e^2 (the estimate's e is below 2^-24)
+__device__ __forceinline__ double rsqrt_normal(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
+}
 
 // Off-diagonal entries at most rel * sqrt(|a_pp a_qq|), or at most
 // floor_rel * trace(G), are left alone: below the floor an entry is rounding
 // noise of the Gram matrix itself, and rotating on it would never settle.
+template <int NMAX>
 __device__ __forceinline__ void jacobi_body(const double* __restrict__ G, int n, double tol, double rel, double floor_rel,
                                    double* __restrict__ sigma, double* __restrict__ V, int32_t* __restrict__ rank) {
-  constexpr int S = kMaxN + 1;
-  __shared__ double A[kMaxN * S];
-  __shared__ double Q[kMaxN * S];
-  __shared__ double2 rcs[kMaxN / 2];  // (c, s) of the rotations of a round
-  __shared__ int order[kMaxN];
-  __shared__ int rotated;
+  constexpr int S = NMAX + 1, kBuf = NMAX * S, kHalf = NMAX / 2;
+  __shared__ double A[2 * kBuf];             // slot order, row <= column
+  __shared__ double Q[kBuf + S];             // index order; the last row takes idle lanes' writes
+  __shared__ double2 rcs[2 * kHalf];         // (c, s) of the rotations of a round
+  __shared__ int order[NMAX];
+  __shared__ int rotated[3];                 // whether sweep s rotated, at s % 3
   __shared__ double floor_abs;
   const int m = n + (n & 1), half = m / 2;
-  if (threadIdx.x == 0) {
-    double tr = 0.0;
-    for (int i = 0; i < n; ++i) tr += fabs(G[i * n + i]);
-    floor_abs = fmax(floor_rel * tr, 1e-290);
-  }
-  for (int e = threadIdx.x; e < m * m; e += kJacobiThreads) {
+  const int tid = threadIdx.x;
+  // index = slot before the first round and after every sweep
+  for (int e = tid; e < S; e += kJacobiThreads) Q[kBuf + e] = 0.0;
+  for (int e = tid; e < m * m; e += kJacobiThreads) {
     const int i = e / m, j = e % m;
     A[i * S + j] = (i < n && j < n) ? G[i * n + j] : 0.0;
     Q[i * S + j] = i == j ? 1.0 : 0.0;
   }
-  // This thread's share of a round, the same in every round: at most
-  // kAItems 2 x 2 blocks (ai, aj) of A (half^2 of them) and at most kQItems
-  // (row, rotation) pairs of the eigenvector update (m half of them).
-  constexpr int kAItems = ((kMaxN / 2) * (kMaxN / 2) + kJacobiThreads - 1) / kJacobiThreads;
-  constexpr int kQItems = (kMaxN * (kMaxN / 2) + kJacobiThreads - 1) / kJacobiThreads;
-  const int tid = threadIdx.x;
-  int ai[kAItems], aj[kAItems];
-#pragma unroll
-  for (int k = 0; k < kAItems; ++k) {
-    const int f = tid + k * kJacobiThreads;
-    ai[k] = f < half * half ? f / half : -1;
-    aj[k] = f < half * half ? f % half : 0;
-  }
-  int qr[kQItems], qj[kQItems];
-#pragma unroll
-  for (int k = 0; k < kQItems; ++k) {
-    const int f = tid + k * kJacobiThreads;
-    qr[k] = f < m * half ? f / half : -1;
-    qj[k] = f < m * half ? f % half : 0;
+  if (tid < 3) rotated[tid] = 0;
+  __syncthreads();
+  if (tid == 0) {
+    double tr = 0.0;
+    for (int i = 0; i < n; ++i) tr += fabs(A[i * S + i]);
+    floor_abs = fmax(floor_rel * tr, 1e-290);
   }
   __syncthreads();
-  for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
-    if (threadIdx.x == 0) rotated = 0;
-    __syncthreads();
-    for (int round = 0; round < m - 1; ++round) {
-      // round-robin pairing: slot 0 fixed, the other m-1 slots rotate; the
-      // pair (p_i, q_i), p_i < q_i, of rotation i is recomputed wherever used
-      auto slot = [&](int k) {
-        int x = k - 1 + round;
-        x = x >= m - 1 ? x - (m - 1) : x;
-        return k == 0 ? 0 : 1 + x;
-      };
-      auto pair_of = [&](int i, int& p, int& q) {
-        const int a = slot(i), b = slot(m - 1 - i);
-        p = a < b ? a : b;
-        q = a < b ? b : a;
-      };
-      if (threadIdx.x < half) {
-        const int i = threadIdx.x;
-        int p, q;
-        pair_of(i, p, q);
-        const double app = A[p * S + p], aqq = A[q * S + q], apq = A[p * S + q];
-        double c = 1.0, s = 0.0;
-        // rotate unless apq is negligible against the diagonal pair (a
-        // relative test, so tiny eigenvalues of a semi-definite G are still
-        // resolved) or below the underflow range
-        if (fabs(apq) > rel * sqrt(fabs(app * aqq)) && fabs(apq) > floor_abs) {
-          // the rotation that zeroes A'(p, q): tan = t, the root of smaller
-          // size of t^2 + 2 theta t - 1 = 0, theta = x / y with
-          // x = aqq - app, y = 2 apq, i.e. t = sgn(x) y / (|x| + sqrt(x^2 + y^2))
-          const double x = aqq - app, y = 2.0 * apq;
-          const double t = (x >= 0 ? y : -y) / (fabs(x) + sqrt(x * x + y * y));
-          c = rsqrt(t * t + 1.0);
-          s = t * c;
-          rotated = 1;
-        }
-        rcs[i] = double2{c, s};
+  const double floor_v = floor_abs, rel2 = rel * rel;
+  // the rotation by theta that zeroes A'(p, q): tan 2 theta = y / x with
+  // x = aqq - app, y = 2 apq, |theta| <= pi / 4; C = cos 2 theta gives
+  // cos^2 theta = (1 + C) / 2, sin theta = sin 2 theta / (2 cos theta).  The
+  // identity unless apq is above the floor and a relative bound (so tiny
+  // eigenvalues of a semi-definite G are still resolved)
+  auto angle = [&](double app, double aqq, double apq, int* flag) {
+    const double x = aqq - app, y = 2.0 * apq, r2 = fma(x, x, y * y);
+    const bool on = apq * apq > rel2 * fabs(app * aqq) && fabs(apq) > floor_v && r2 > 1e-280;
+    const double inv = rsqrt_normal(r2);
+    const double c2 = fma(0.5 * fabs(x), inv, 0.5), rc = rsqrt_normal(c2);
+    const double sn = 0.5 * (x >= 0 ? y : -y) * inv * rc;
+    if (on) *flag = 1;
+    return on ? double2{c2 * rc, sn} : double2{1.0, 0.0};
+  };
+  // slot of the next round
+  auto moved = [&](int k) { return k == 0 ? 0 : (k == 1 ? m - 1 : k - 1); };
+  // a pair of slots as it is stored
+  auto at = [&](int x, int y) { return x < y ? x * S + y : y * S + x; };
+  // A worker's share of a round, the same in every round: 2 x 2 blocks (i, j),
+  // i <= j, of A (lanes beyond the last repeat it; addresses read and written) and
+  // (row, rotation) pairs of the eigenvectors (m half; addresses of the round's
+  // columns).  Straight code over the most that n <= NMAX can need: the reads of a
+  // round go out together.
+  constexpr int kAItems = (kHalf * (kHalf + 1) / 2 + kJacobiWorkers - 1) / kJacobiWorkers;
+  constexpr int kQItems = (NMAX * kHalf + kJacobiWorkers - 1) / kJacobiWorkers;
+  const int blocks = half * (half + 1) / 2;
+  int ai[kAItems], aj[kAItems], rd[kAItems][4], wr[kAItems][4];
+#pragma unroll
+  for (int k = 0; k < kAItems; ++k) {
+    int f = tid - 64 + k * kJacobiWorkers;
+    f = f < 0 ? 0 : (f < blocks ? f : blocks - 1);
+    int j = 0;
+    while ((j + 1) * (j + 2) / 2 <= f) ++j;
+    const int i = f - j * (j + 1) / 2;
+    ai[k] = i;
+    aj[k] = j;
+    const int p = i, q = m - 1 - i, u = j, v = m - 1 - j;
+    rd[k][0] = at(p, u); rd[k][1] = at(p, v); rd[k][2] = at(q, u); rd[k][3] = at(q, v);
+    wr[k][0] = at(moved(p), moved(u)); wr[k][1] = at(moved(p), moved(v));
+    wr[k][2] = at(moved(q), moved(u)); wr[k][3] = at(moved(q), moved(v));
+  }
+  int qj[kQItems], qu[kQItems], qv[kQItems], qe[kQItems];
+#pragma unroll
+  for (int k = 0; k < kQItems; ++k) {
+    const int f = tid - 64 + k * kJacobiWorkers;
+    const bool in = tid >= 64 && f < m * half;
+    const int row = (in ? f / half : NMAX) * S;
+    qj[k] = in ? f % half : 0;
+    qu[k] = row + qj[k];                     // the index in slot j, then in m-1-j
+    qv[k] = row + m - 1 - qj[k];
+    qe[k] = row + m - 1;                     // the last index
+  }
+  // wave 0, lane i: the next round's pivot (slots i and m-1-i) is in these slots
+  // now, its indices in rotations pi and pj, second of the two where si, sj
+  int pi = 0, pj = 0, pr[3][4] = {};
+  bool si = false, sj = false;
+  if (tid < half) {
+    const int kp = tid == 0 ? 0 : (tid == m - 1 ? 1 : tid + 1), kq = tid == 0 ? 1 : m - tid;
+    pi = kp < half ? kp : m - 1 - kp;
+    pj = kq < half ? kq : m - 1 - kq;
+    si = kp >= half;
+    sj = kq >= half;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int r0 = c / 2 ? m - 1 - pi : pi, r1 = c / 2 ? m - 1 - pj : pj;
+      pr[0][c] = at(r0, c % 2 ? m - 1 - pi : pi);
+      pr[1][c] = at(r1, c % 2 ? m - 1 - pj : pj);
+      pr[2][c] = at(r0, c % 2 ? m - 1 - pj : pj);
+    }
+    rcs[tid] = angle(A[tid * S + tid], A[(m - 1 - tid) * S + m - 1 - tid], A[tid * S + m - 1 - tid], &rotated[0]);
+  }
+  if (tid < 64) __builtin_amdgcn_s_setprio(3);
+  __syncthreads();
+
+  // one round from buffer B into the other
+  auto step = [&](auto B, int* flag) {
+    const double* Ac = A + decltype(B)::value * kBuf;
+    double* An = A + (1 - decltype(B)::value) * kBuf;
+    const double2* rc = rcs + decltype(B)::value * kHalf;
+    if (tid < 64) {
+      if (tid < half) {
+        // the three 2 x 2 blocks that hold the pivot's entries, all read at once
+        const double2 ri = rc[pi], rj = rc[pj];
+        double e[3][4];
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) e[b][c] = Ac[pr[b][c]];
+        // the row (a, b) of a rotation that leaves the pivot's index: (c, -s) or (s, c)
+        const double2 li = si ? double2{ri.y, ri.x} : double2{ri.x, -ri.y};
+        const double2 lj = sj ? double2{rj.y, rj.x} : double2{rj.x, -rj.y};
+        auto entry = [&](const double (&x)[4], double2 l, double2 r) {
+          const double xp = fma(r.x, x[0], r.y * x[1]), xq = fma(r.x, x[2], r.y * x[3]);
+          return fma(l.x, xp, l.y * xq);
+        };
+        const double app = entry(e[0], li, li), aqq = entry(e[1], lj, lj);
+        double apq = entry(e[2], li, lj);
+        if (pi == pj && ri.y != 0.0) apq = 0.0;
+        rcs[(1 - decltype(B)::value) * kHalf + tid] = angle(app, aqq, apq, flag);
       }
-      __syncthreads();
+    } else {
       // A <- J^T A J and V <- V J for the block-diagonal J of this round's
       // disjoint rotations: entry block (p_i, q_i) x (p_j, q_j) of A depends
-      // only on the same block, so every 2 x 2 block is updated in place by
-      // one thread (columns by rotation j, then rows by rotation i); the
-      // rotated entries (p, q), (q, p) are zero by construction of the angle
-      // (each thread's items are fixed for the kernel: see below)
+      // only on the same block, so each 2 x 2 block is one thread's (columns by
+      // rotation j, then rows by rotation i); the rotated entries (p, q),
+      // (q, p) are zero by construction of the angle
+      double a[kAItems][4], x[kQItems], y[kQItems];
+      double2 ri[kAItems], rj[kAItems], rq[kQItems];
 #pragma unroll
       for (int k = 0; k < kAItems; ++k) {
-        if (ai[k] < 0) continue;
-        const int i = ai[k], j = aj[k];
-        int p, q, u, v;
-        pair_of(i, p, q);
-        pair_of(j, u, v);
-        const double2 ri = rcs[i], rj = rcs[j];
-        const double ci = ri.x, si = ri.y, cj = rj.x, sj = rj.y;
-        // two identity rotations (c = 1, s = 0) give back the block exactly:
-        // in late sweeps most blocks are left as they are
-        if (si == 0.0 && sj == 0.0) continue;
-        const double a_pu = A[p * S + u], a_pv = A[p * S + v], a_qu = A[q * S + u], a_qv = A[q * S + v];
-        const double b_pu = cj * a_pu - sj * a_pv, b_pv = sj * a_pu + cj * a_pv;
-        const double b_qu = cj * a_qu - sj * a_qv, b_qv = sj * a_qu + cj * a_qv;
-        const bool hit = i == j && si != 0.0;
-        A[p * S + u] = ci * b_pu - si * b_qu;
-        A[q * S + u] = hit ? 0.0 : si * b_pu + ci * b_qu;
-        A[p * S + v] = hit ? 0.0 : ci * b_pv - si * b_qv;
-        A[q * S + v] = si * b_pv + ci * b_qv;
+        ri[k] = rc[ai[k]];
+        rj[k] = rc[aj[k]];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) a[k][c] = Ac[rd[k][c]];
       }
 #pragma unroll
       for (int k = 0; k < kQItems; ++k) {
-        if (qr[k] < 0) continue;
-        const int r = qr[k];
-        int u, v;
-        pair_of(qj[k], u, v);
-        const double2 rj = rcs[qj[k]];
-        const double c = rj.x, sn = rj.y;
-        if (sn == 0.0) continue;   // the identity rotation
-        const double x = Q[r * S + u], y = Q[r * S + v];
-        Q[r * S + u] = c * x - sn * y;
-        Q[r * S + v] = sn * x + c * y;
+        rq[k] = rc[qj[k]];
+        x[k] = Q[qu[k]];
+        y[k] = Q[qv[k]];
       }
-      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < kAItems; ++k) {
+        const double b_pu = rot_lo(rj[k], a[k][0], a[k][1]), b_pv = rot_hi(rj[k], a[k][0], a[k][1]);
+        const double b_qu = rot_lo(rj[k], a[k][2], a[k][3]), b_qv = rot_hi(rj[k], a[k][2], a[k][3]);
+        const bool hit = ai[k] == aj[k] && ri[k].y != 0.0;
+        An[wr[k][0]] = rot_lo(ri[k], b_pu, b_qu);
+        An[wr[k][1]] = hit ? 0.0 : rot_lo(ri[k], b_pv, b_qv);
+        An[wr[k][2]] = hit ? 0.0 : rot_hi(ri[k], b_pu, b_qu);
+        An[wr[k][3]] = rot_hi(ri[k], b_pv, b_qv);
+      }
+#pragma unroll
+      for (int k = 0; k < kQItems; ++k) {
+        Q[qu[k]] = rot_lo(rq[k], x[k], y[k]);
+        Q[qv[k]] = rot_hi(rq[k], x[k], y[k]);
+        // the index that the next round finds in the slot is one higher
+        const int u = qu[k] == qe[k] ? qu[k] - (m - 2) : qu[k] + 1;
+        qu[k] = qj[k] ? u : qu[k];
+        qv[k] = qv[k] == qe[k] ? qv[k] - (m - 2) : qv[k] + 1;
+      }
     }
-    if (!rotated) break;
     __syncthreads();
+  };
+  int buf = 0;
+  for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
+    for (int round = 0; round < m - 1; ++round, buf ^= 1) {
+      if (tid == 0 && round == 0) rotated[(sweep + 1) % 3] = 0;
+      // the angles worked out in the last round are the next sweep's
+      int* flag = &rotated[(round + 1 < m - 1 ? sweep : sweep + 1) % 3];
+      if (buf) step(std::integral_constant<int, 1>{}, flag);
+      else step(std::integral_constant<int, 0>{}, flag);
+    }
+    if (!rotated[sweep % 3]) break;
   }
   // decreasing eigenvalues over the n real indices (the pad index n, when n
-  // is odd, keeps its zero eigenvalue and unit vector and is left out)
-  if (threadIdx.x == 0) {
-    for (int i = 0; i < n; ++i) order[i] = i;
-    for (int i = 0; i < n; ++i) {
-      int best = i;
-      for (int j = i + 1; j < n; ++j)
-        if (A[order[j] * S + order[j]] > A[order[best] * S + order[best]]) best = j;
-      const int t = order[i];
-      order[i] = order[best];
-      order[best] = t;
+  // is odd, keeps its zero eigenvalue and unit vector and is left out); a NaN
+  // counts as the lowest value, so that order stays a permutation
+  const double* Ac = A + buf * kBuf;
+  if (tid < n) {
+    auto value = [&](int j) {
+      const double y = Ac[j * S + j];
+      return y == y ? y : -INFINITY;
+    };
+    const double x = value(tid);
+    int at = 0;
+    for (int j = 0; j < n; ++j) {
+      const double y = value(j);
+      at += (y > x || (y == x && j < tid)) ? 1 : 0;
     }
-    const double s0 = sqrt(fmax(A[order[0] * S + order[0]], 0.0));
-    int r = 0;
-    for (int i = 0; i < n; ++i)
-      if (sqrt(fmax(A[order[i] * S + order[i]], 0.0)) > tol * s0) ++r;
-    *rank = r < 1 ? 1 : r;
+    order[at] = tid;
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < n * n; e += kJacobiThreads) {
+  if (tid == 0) {
+    const double s0 = sqrt(fmax(Ac[order[0] * S + order[0]], 0.0));
+    int r = 0;
+    for (int i = 0; i < n; ++i)
+      if (sqrt(fmax(Ac[i * S + i], 0.0)) > tol * s0) ++r;
+    *rank = r < 1 ? 1 : r;
+  }
+  for (int e = tid; e < n * n; e += kJacobiThreads) {
     const int a = e / n, r = e % n;
     V[a * n + r] = Q[a * S + order[r]];
   }
-  if (threadIdx.x < n) sigma[threadIdx.x] = sqrt(fmax(A[order[threadIdx.x] * S + order[threadIdx.x]], 0.0));
+  if (tid < n) sigma[tid] = sqrt(fmax(Ac[order[tid] * S + order[tid]], 0.0));
 }
 
+template <int NMAX>
 __global__ void __launch_bounds__(kJacobiThreads)
 jacobi_kernel(const double* __restrict__ G, int n, double tol, double rel, double floor_rel,
               double* __restrict__ sigma, double* __restrict__ V, int32_t* __restrict__ rank) {
-  jacobi_body(G, n, tol, rel, floor_rel, sigma, V, rank);
+  jacobi_body<NMAX>(G, n, tol, rel, floor_rel, sigma, V, rank);
 }
 
 // batched: molecule blockIdx.x; pass 0 writes V1, pass 1 V2 (and both the
 // singular values and the rank, the second pass's final)
+template <int NMAX>
 __global__ void __launch_bounds__(kJacobiThreads)
 jacobi_batch_kernel(const CmpMol* __restrict__ tab, int n, int pass, double rel, double floor_rel) {
   const CmpMol& m = tab[blockIdx.x];
-  jacobi_body(m.G, n, m.tol, rel, floor_rel, m.sigma, pass == 0 ? m.V1 : m.V2, m.rank);
+  jacobi_body<NMAX>(m.G, n, m.tol, rel, floor_rel, m.sigma, pass == 0 ? m.V1 : m.V2, m.rank);
+}
+
+// Call f(integral_constant<int, NMAX>{}) for the smallest class that holds n.
+template <class F>
+void with_jacobi_class(int n, F&& f) {
+  if (n <= 32) f(std::integral_constant<int, 32>{});
+  else if (n <= 48) f(std::integral_constant<int, 48>{});
+  else f(std::integral_constant<int, kMaxN>{});
 }
 
 // U[d][r][q] = sum_a V[a][r] M[d][a][q] for r < R (V is n x n, its first R
@@ -612,8 +712,10 @@ void launch_gram_eig(const double* M, const double* V1, int n, int64_t npair, do
   else
     hipLaunchKernelGGL(gram_kernel, dim3(nchunk), dim3(256), 0, s, M, n, npair, chunk, w.part);
   hipLaunchKernelGGL(gram_sum_kernel, dim3(n * n), dim3(kGramSumThreads), 0, s, w.part, nchunk, w.G);
-  hipLaunchKernelGGL(jacobi_kernel, dim3(1), dim3(kJacobiThreads), 0, s, w.G, n, tol, rel, floor_rel, w.sigma, V,
-                     w.rank);
+  with_jacobi_class(n, [&](auto c) {
+    hipLaunchKernelGGL((jacobi_kernel<decltype(c)::value>), dim3(1), dim3(kJacobiThreads), 0, s, w.G, n, tol, rel,
+                       floor_rel, w.sigma, V, w.rank);
+  });
 }
 }  // namespace
 
@@ -677,7 +779,10 @@ hipError_t launch_compress_batch(const CmpMol* tab, int ncm, int n, int nq, int6
     if (pass == 0) hipLaunchKernelGGL(gram_batch_kernel, dim3(max_nchunk, ncm), dim3(256), 0, s, tab, n);
     else hipLaunchKernelGGL(gram_y_batch_kernel, dim3(max_nchunk, ncm), dim3(256), gram_v1_bytes(n), s, tab, n);
     hipLaunchKernelGGL(gram_sum_batch_kernel, dim3(n * n, ncm), dim3(kGramSumThreads), 0, s, tab);
-    hipLaunchKernelGGL(jacobi_batch_kernel, dim3(ncm), dim3(kJacobiThreads), 0, s, tab, n, pass, rel, floor_rel);
+    with_jacobi_class(n, [&](auto c) {
+      hipLaunchKernelGGL((jacobi_batch_kernel<decltype(c)::value>), dim3(ncm), dim3(kJacobiThreads), 0, s, tab, n, pass,
+                         rel, floor_rel);
+    });
   };
   // the two passes of launch_compress_basis, with its tolerances
   gram_eig(0, 1e-10, 1e-14);

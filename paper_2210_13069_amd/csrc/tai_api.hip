@@ -693,7 +693,7 @@ int tai_degrees(tai_ctx* c, const tai_params* p, int32_t* nk, double* C, void* s
 }
 
 static int compress_impl(tai_ctx* c, const double* M, int64_t npair, const tai_params* p, const NodeTables& tb,
-                         bool operands, hipStream_t s, tai::CompressWork* w, int* R);
+                         bool operands, hipStream_t s, tai::CompressWork* w, int* R, double* U = nullptr);
 
 int tai_compress(tai_ctx* c, const double* M, int32_t npair, const tai_params* p, int32_t* rank, double* sigma,
                  double* V, double* U, double* Kc, void* stream) {
@@ -717,14 +717,19 @@ int tai_compress(tai_ctx* c, const double* M, int32_t npair, const tai_params* p
     e = tai::launch_nodes(p->omega, p->nq, p->n, p->L, p->nodes, p->degree_tol, tb, s);
     if (e != hipSuccess) return hip_fail(c, e, "nodes kernel");
   }
-  if ((r = compress_impl(c, M, npair, p, tb, operands, s, &w, &R))) return r;
+  // U goes straight to the caller, unless its address is no place for doubles or
+  // it may share memory with M
+  const size_t most = sizeof(double) * 3 * (size_t)p->n * npair;
+  const uintptr_t u = reinterpret_cast<uintptr_t>(U), m = reinterpret_cast<uintptr_t>(M);
+  double* direct = U && u % sizeof(double) == 0 && (u >= m + most || m >= u + most) ? U : nullptr;
+  if ((r = compress_impl(c, M, npair, p, tb, operands, s, &w, &R, direct))) return r;
   const size_t n = p->n;
   const size_t Rp = tai::padded_rank(R, p->n);
   if (sigma && (e = hipMemcpyAsync(sigma, w.sigma, 8 * n, hipMemcpyDeviceToDevice, s)) != hipSuccess)
     return hip_fail(c, e, "copy sigma");
   if (V && (e = hipMemcpyAsync(V, w.V, 8 * n * n, hipMemcpyDeviceToDevice, s)) != hipSuccess)
     return hip_fail(c, e, "copy V");
-  if (U && (e = hipMemcpyAsync(U, c->cmpU.p, 8 * 3 * Rp * npair, hipMemcpyDeviceToDevice, s)) != hipSuccess)
+  if (U && !direct && (e = hipMemcpyAsync(U, c->cmpU.p, 8 * 3 * Rp * npair, hipMemcpyDeviceToDevice, s)) != hipSuccess)
     return hip_fail(c, e, "copy U");
   if (Kc && (e = hipMemcpyAsync(Kc, w.Kc, 8 * (size_t)p->nq * Rp * Rp, hipMemcpyDeviceToDevice, s)) != hipSuccess)
     return hip_fail(c, e, "copy Kc");
@@ -1156,14 +1161,14 @@ int tai_moments_pairs(tai_ctx* c, const tai_basis* b, const tai_params* p, const
 
 // Low-rank compression of the moments (section 6.1, eqs. SVD and
 // approxepsilon) on s: basis and rank, then the compressed moments
-// (c->cmpU, [3][R][npair]) and tables (w->Kc, [nq][R][R]) from the node tables
+// (U or, without one, c->cmpU; [3][R][npair]) and tables (w->Kc, [nq][R][R]) from the node tables
 // tb.  The call waits on the host for the rank.
 static int compress_impl(tai_ctx* c, const double* M, int64_t npair, const tai_params* p, const NodeTables& tb,
-                         bool operands, hipStream_t s, tai::CompressWork* w, int* R) {
+                         bool operands, hipStream_t s, tai::CompressWork* w, int* R, double* U) {
   int r;
   const int n = p->n, nq = p->nq;
   if ((r = ensure(c, c->cmp, tai::compress_work_bytes(n, nq, npair)))) return r;
-  if ((r = ensure(c, c->cmpU, sizeof(double) * 3 * (size_t)n * npair))) return r;
+  if (!U && (r = ensure(c, c->cmpU, sizeof(double) * 3 * (size_t)n * npair))) return r;
   *w = tai::carve_compress_work(c->cmp.p, n, nq, npair);
   hipError_t e;
   {
@@ -1181,7 +1186,7 @@ static int compress_impl(tai_ctx* c, const double* M, int64_t npair, const tai_p
   {
     Timed tm(c, kStCompress, s);
     e = tai::launch_compress_operands(M, n, npair, tai::padded_rank(host, n), host, nq, tb.K, *w,
-                                      static_cast<double*>(c->cmpU.p), s);
+                                      U ? U : static_cast<double*>(c->cmpU.p), s);
   }
   if (e != hipSuccess) return hip_fail(c, e, "compression operand kernels");
   return TAI_OK;
