@@ -41,9 +41,20 @@ __device__ inline bool pair_of(const int32_t* pairs, int nb, int64_t p, int& mu,
   return true;
 }
 
+// Pair densities; the first work group also writes out[i] = scale w[i % nq] for
+// i < nq reps: the quadrature weights, repeated for each source box of the adaptive
+// J, with 2/sqrt(pi) folded in (a launch of their own was 2.3 us).
+struct ScaledWeights {
+  const double* w;
+  int nq, reps;
+  double scale;
+  double* out;
+};
 __global__ void __launch_bounds__(256)
 density_pairs_kernel(const double* __restrict__ D, int nb, int64_t npair, const int32_t* __restrict__ pairs,
-                     double* __restrict__ Dt) {
+                     double* __restrict__ Dt, ScaledWeights sw) {
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < sw.nq * sw.reps; i += blockDim.x) sw.out[i] = sw.scale * sw.w[i % sw.nq];
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= npair) return;
   int mu, nu;
@@ -772,14 +783,6 @@ jp16_kernel(const float* __restrict__ Mall, const __bf16* __restrict__ Psall, in
   }
 }
 
-// out[i] = scale w[i % nq] for i < nq reps: the quadrature weights, repeated
-// for each source box of the adaptive J, with 2/sqrt(pi) folded in.
-__global__ void __launch_bounds__(256)
-repeat_weights_kernel(const double* __restrict__ w, int nq, int reps, double scale, double* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nq * reps) out[i] = scale * w[i % nq];
-}
-
 // J_p for 256 pairs per work group of 512 threads: wave w owns the two
 // 16-pair tiles at blk*256 + 32 w.  The rows (a0, a1) of Phi are taken A0P
 // values of a0 at a time: the slab Phi(a0 .. a0 + A0P - 1, :, :) is staged in
@@ -1267,12 +1270,11 @@ void launch_rho_list(int prec, const double* M, const float* M32, int n, int npa
   else launch_sum_parts(w.rho_part, nchunk, n3, 1, rho, s);
 }
 
-// rho from the pair densities in w.Dt, then Phi = (2/sqrt(pi)) sum_k w_k rho x_d K_k
-// (into w.rho and w.Phi)
+// rho from the pair densities in w.Dt, then Phi = sum_k wsc_k rho x_d K_k (into
+// w.rho and w.Phi), with the scaled weights in w.wsc
 hipError_t launch_rho_phi(int prec, const double* M, int npair, int n, int nq, const NodeTables& tb, const JWork& w,
                           hipStream_t s) {
   launch_rho_list(prec, M, w.M32, n, npair, w, w.Dt, false, w.rho, s);
-  hipLaunchKernelGGL(repeat_weights_kernel, dim3(nblk(nq, 256)), dim3(256), 0, s, tb.w, nq, 1, kTwoOverSqrtPi, w.wsc);
   return launch_phi_grid(w.rho, tb.K, w.wsc, n, nq, w, w.Phi, s);
 }
 // J_p and J of the spans in the arithmetic prec
@@ -1289,7 +1291,7 @@ void launch_projection(int prec, const double* M, const float* M32, int n, const
 hipError_t launch_apply_j(int prec, const double* M, int nb, int npair, const int32_t* pairs, int n, int nq,
                           const NodeTables& tb, const double* D, double* J, const JWork& w, hipStream_t s) {
   hipLaunchKernelGGL(density_pairs_kernel, dim3(nblk(npair, 256)), dim3(256), 0, s, D, nb, (int64_t)npair, pairs,
-                     w.Dt);
+                     w.Dt, ScaledWeights{tb.w, nq, 1, kTwoOverSqrtPi, w.wsc});
   convert_moments(prec, M, n, npair, w, s);
   const hipError_t e = launch_rho_phi(prec, M, npair, n, nq, tb, w, s);
   if (e != hipSuccess) return e;
@@ -1334,14 +1336,13 @@ hipError_t launch_apply_j_parts(int prec, const double* M, int nb, const int32_t
                                 double* wrep, hipStream_t s) {
   const int64_t total = offs[nparts];
   const int64_t n3 = (int64_t)n * n * n, n2 = (int64_t)n * n;
-  hipLaunchKernelGGL(density_pairs_kernel, dim3(nblk(total, 256)), dim3(256), 0, s, D, nb, total, pairs, wk.Dt);
+  hipLaunchKernelGGL(density_pairs_kernel, dim3(nblk(total, 256)), dim3(256), 0, s, D, nb, total, pairs, wk.Dt,
+                     ScaledWeights{w, nq, nparts, kTwoOverSqrtPi, wrep});
   convert_moments(prec, M, n, (int)total, wk, s);
   // one box: the plain path's sequence (the same bits as tai_apply_J); the
   // weights carry 2/sqrt(pi) either way
   const bool one = nparts == 1;
   const bool parity = !one && phi_octants(n, (int64_t)nparts * nparts);
-  hipLaunchKernelGGL(repeat_weights_kernel, dim3(nblk((int64_t)nq * nparts, 256)), dim3(256), 0, s, w, nq, nparts,
-                     kTwoOverSqrtPi, wrep);
   Spans sp{};
   for (int p = 0; p <= nparts; ++p) sp.off[p] = offs[p];
   // chunks per partition: the single list's count shared out, so that the

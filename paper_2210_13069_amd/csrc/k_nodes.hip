@@ -20,110 +20,136 @@ namespace tai {
 namespace {
 
 constexpr int kNodeThreads = 256;
-constexpr int kXiBase = 128;     // threads [128, 128 + n) build the Chebyshev nodes
-
-// Legendre P_m and P_{m-1} at x by the three-term recurrence.
-__device__ inline void legendre_pair(int m, double x, double& pm, double& pm1) {
-  double p0 = 1.0, p1 = x;
-  for (int j = 1; j < m; ++j) {
-    const double p2 = ((2.0 * j + 1.0) * x * p1 - j * p0) / (j + 1.0);
-    p0 = p1;
-    p1 = p2;
-  }
-  pm = p1;
-  pm1 = p0;
-}
-
-// Root `i` (0-based, descending) of P_m and its Gauss weight.
-__device__ inline void gauss_root(int m, int i, double& x, double& wt) {
-  x = cos(M_PI * (i + 0.75) / (m + 0.5));
-  for (int it = 0; it < 100; ++it) {
-    double pm, pm1;
-    legendre_pair(m, x, pm, pm1);
-    const double dp = m * (x * pm - pm1) / (x * x - 1.0);
-    const double dx = pm / dp;
-    x -= dx;
-    if (fabs(dx) < 1e-15) break;
-  }
-  double pm, pm1;
-  legendre_pair(m, x, pm, pm1);
-  const double dp = m * (x * pm - pm1) / (x * x - 1.0);
-  wt = 2.0 / ((1.0 - x * x) * dp * dp);
-}
-
-__device__ inline void nodes_body(double omega, int nq, int n, double L, int kind, const NodeTables& tb) {
-  const int tid = threadIdx.x;
-  if (tid < nq) {
-    double z, zw;
-    gauss_root(nq, tid, z, zw);
-    const int k = nq - 1 - tid;  // ascending order
-    tb.t[k] = 0.5 * omega * (1.0 + z);
-    tb.w[k] = 0.5 * omega * zw;
-  } else if (tid >= kXiBase && tid < kXiBase + n) {
-    const int a = tid - kXiBase;
-    const double th = (kind == 0) ? M_PI * a / (n - 1) : (2.0 * a + 1.0) * M_PI / (2.0 * n);
-    tb.xi[a] = L * cos(th);
-  }
-}
-
-__global__ void __launch_bounds__(kNodeThreads)
-nodes_kernel(double omega, int nq, int n, double L, int kind, NodeTables tb) {
-  nodes_body(omega, nq, n, L, kind, tb);
-}
-
-// one work group per molecule (blockIdx.y)
-__global__ void __launch_bounds__(kNodeThreads)
-nodes_batch_kernel(const PrepMol* __restrict__ mols, int nq, int n, int kind) {
-  const PrepMol& m = mols[blockIdx.y];
-  nodes_body(m.omega, nq, n, m.L, kind, m.tb);
-}
+constexpr int kMaxNodes = 128, kMaxGrid = 64;
+// entries of one K_k that a work group fills: four exponentials per thread
+constexpr int kNodeEntries = 4 * kNodeThreads;
 
 // Entries of gam written: the n*n map and zeros up to its 256-byte boundary,
 // so that the moment kernel may read whole padded rows.
 __host__ __device__ inline int64_t gam_entries(int n) { return ((int64_t)n * n + 31) / 32 * 32; }
 
-// K tables (nq*n*n entries) followed by the n*n Chebyshev-to-Lagrange map.
-__device__ inline void ktables_body(int nq, int n, int kind, const NodeTables& tb) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t nk = (int64_t)nq * n * n;
-  if (g < nk) {
-    const int k = (int)(g / ((int64_t)n * n));
-    const int ab = (int)(g % ((int64_t)n * n));
-    const int a = ab / n, b = ab % n;
-    const double dx = tb.xi[a] - tb.xi[b];
-    const double t = tb.t[k];
-    tb.K[g] = exp(-t * t * dx * dx);
-  } else if (g < nk + gam_entries(n)) {
-    const int ak = (int)(g - nk);
-    const int a = ak / n, k = ak % n;
-    double v;
-    if (ak >= n * n) {
-      v = 0.0;
-    } else if (kind == 0) {
-      // Lobatto: l_a(u) = sum_k 2/(N c_a c_k) T_k(u_a) T_k(u), N = n-1,
-      // c_0 = c_N = 2, other c = 1; T_k(u_a) = cos(pi a k / N)
-      const int N = n - 1;
-      const double ca = (a == 0 || a == N) ? 2.0 : 1.0;
-      const double ck = (k == 0 || k == N) ? 2.0 : 1.0;
-      v = 2.0 / (N * ca * ck) * cos(M_PI * (double)((int64_t)a * k % (2 * N)) / N);
-    } else {
-      // first kind: l_a(u) = sum_k (2 - delta_k0)/n T_k(u_a) T_k(u),
-      // T_k(u_a) = cos(k (2a+1) pi / (2n))
-      const double ck = (k == 0) ? 1.0 : 2.0;
-      v = ck / n * cos(M_PI * (double)((int64_t)k * (2 * a + 1) % (4 * n)) / (2.0 * n));
+// Root `i` (0-based, descending) of P_m and its Gauss weight, by Newton's method
+// on the three-term recurrence P_{j+1} = a_j x P_j - b_j P_{j-1} (ab[j] = (a_j,
+// b_j): one dependent operation a step).  The start value is cos of the
+// asymptotic angle with its first correction, good to about m^-4, so that the
+// third step is below rounding; the last evaluation then also gives P_m' for the
+// weight.
+__device__ inline void gauss_root(int m, int i, const double2* ab, double& x, double& wt) {
+  x = (1.0 - (m - 1.0) / (8.0 * m * m * m)) * cos(M_PI * (i + 0.75) / (m + 0.5));
+  double dp = 1.0;
+  for (int it = 0; it < 100; ++it) {
+    double p0 = 1.0, p1 = x;
+#pragma unroll 4
+    for (int j = 1; j < m; ++j) {
+      const double2 c = ab[j];
+      const double p2 = fma(c.x * x, p1, -(c.y * p0));
+      p0 = p1;
+      p1 = p2;
     }
-    tb.gam[ak] = v;
+    dp = m * (x * p1 - p0) / (x * x - 1.0);
+    const double dx = p1 / dp;
+    x -= dx;
+    if (fabs(dx) < 1e-15) break;
   }
+  wt = 2.0 / ((1.0 - x * x) * dp * dp);
 }
 
-__global__ void __launch_bounds__(256)
-ktables_kernel(int nq, int n, int kind, NodeTables tb) {
-  ktables_body(nq, n, kind, tb);
+// Work groups of the tables that `parts` names: nq node groups (times the pieces
+// of a K table), then those of gam.
+__host__ __device__ inline int node_pieces(int n, unsigned parts) {
+  return parts & kTablesK ? (n * n + kNodeEntries - 1) / kNodeEntries : 1;
+}
+__host__ __device__ inline int node_groups(int nq, int n, unsigned parts) {
+  return parts & (kTablesK | kTablesNodes) ? nq * node_pieces(n, parts) : 0;
+}
+inline int table_groups(int nq, int n, unsigned parts) {
+  return node_groups(nq, n, parts) +
+         (parts & kTablesGam ? (int)((gam_entries(n) + kNodeThreads - 1) / kNodeThreads) : 0);
 }
 
-__global__ void __launch_bounds__(256)
-ktables_batch_kernel(const PrepMol* __restrict__ mols, int nq, int n, int kind) {
-  ktables_body(nq, n, kind, mols[blockIdx.y].tb);
+// One launch: a work group of a K_k works out its own node t_k (and one of them
+// writes it), others fill the map gam.
+//   What bounds it: latency, the recurrence's chain.  With the nodes in a launch of
+// their own, a division in every step and six evaluations: 24 nodes at n = 32
+// 12.5 us for the two launches, now 6.8 us (the moments, which read gam alone, 1.5).
+__device__ inline void tables_body(double omega, int nq, int n, double L, int kind, unsigned parts,
+                                   const NodeTables& tb) {
+  __shared__ double2 ab[kMaxNodes];
+  __shared__ double s_xi[kMaxGrid];
+  __shared__ double s_t;
+  const int tid = threadIdx.x, ng = node_groups(nq, n, parts);
+  if ((int)blockIdx.x < ng) {
+    const int pieces = node_pieces(n, parts);
+    const int k = blockIdx.x / pieces, piece = blockIdx.x % pieces;
+    if (tid >= 128) {
+      const int j = tid - 128;
+      if (j > 0 && j < nq) ab[j] = double2{(2.0 * j + 1.0) / (j + 1.0), j / (j + 1.0)};
+    } else if (tid >= 64 && tid - 64 < n) {
+      const int a = tid - 64;
+      const double th = (kind == 0) ? M_PI * a / (n - 1) : (2.0 * a + 1.0) * M_PI / (2.0 * n);
+      const double xi = L * cos(th);
+      s_xi[a] = xi;
+      if (blockIdx.x == 0) tb.xi[a] = xi;
+    }
+    __syncthreads();
+    if (tid < 64) {
+      double z, zw;
+      gauss_root(nq, nq - 1 - k, ab, z, zw);  // ascending order
+      if (tid == 0) {
+        const double t = 0.5 * omega * (1.0 + z);
+        s_t = t;
+        if (piece == 0) {
+          tb.t[k] = t;
+          tb.w[k] = 0.5 * omega * zw;
+        }
+      }
+    }
+    if (!(parts & kTablesK)) return;
+    __syncthreads();
+    const double t = s_t;
+    double* Kk = tb.K + (int64_t)k * n * n;
+#pragma unroll
+    for (int r = 0; r < kNodeEntries / kNodeThreads; ++r) {
+      const int e = piece * kNodeEntries + r * kNodeThreads + tid;
+      if (e < n * n) {
+        const double dx = s_xi[e / n] - s_xi[e % n];
+        Kk[e] = exp(-t * t * dx * dx);
+      }
+    }
+    return;
+  }
+  const int ak = ((int)blockIdx.x - ng) * kNodeThreads + tid;
+  if (ak >= gam_entries(n)) return;
+  const int a = ak / n, k = ak % n;
+  double v;
+  if (ak >= n * n) {
+    v = 0.0;
+  } else if (kind == 0) {
+    // Lobatto: l_a(u) = sum_k 2/(N c_a c_k) T_k(u_a) T_k(u), N = n-1,
+    // c_0 = c_N = 2, other c = 1; T_k(u_a) = cos(pi a k / N)
+    const int N = n - 1;
+    const double ca = (a == 0 || a == N) ? 2.0 : 1.0;
+    const double ck = (k == 0 || k == N) ? 2.0 : 1.0;
+    v = 2.0 / (N * ca * ck) * cos(M_PI * (double)((int64_t)a * k % (2 * N)) / N);
+  } else {
+    // first kind: l_a(u) = sum_k (2 - delta_k0)/n T_k(u_a) T_k(u),
+    // T_k(u_a) = cos(k (2a+1) pi / (2n))
+    const double ck = (k == 0) ? 1.0 : 2.0;
+    v = ck / n * cos(M_PI * (double)((int64_t)k * (2 * a + 1) % (4 * n)) / (2.0 * n));
+  }
+  tb.gam[ak] = v;
+}
+
+__global__ void __launch_bounds__(kNodeThreads)
+tables_kernel(double omega, int nq, int n, double L, int kind, unsigned parts, NodeTables tb) {
+  tables_body(omega, nq, n, L, kind, parts, tb);
+}
+
+// molecule blockIdx.y
+__global__ void __launch_bounds__(kNodeThreads)
+tables_batch_kernel(const PrepMol* __restrict__ mols, int nq, int n, int kind) {
+  const PrepMol& m = mols[blockIdx.y];
+  tables_body(m.omega, nq, n, m.L, kind, kTablesAll, m.tb);
 }
 
 constexpr int kDegThreads = 1024;
@@ -261,27 +287,22 @@ hipError_t launch_degrees(int nq, int n, int kind, double degree_tol, const Node
 }
 
 hipError_t launch_nodes(double omega, int nq, int n, double L, int kind, double degree_tol,
-                        const NodeTables& tb, hipStream_t s) {
-  hipLaunchKernelGGL(nodes_kernel, dim3(1), dim3(kNodeThreads), 0, s, omega, nq, n, L, kind, tb);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int64_t total = (int64_t)nq * n * n + gam_entries(n);
-  const int blocks = (int)((total + 255) / 256);
-  hipLaunchKernelGGL(ktables_kernel, dim3(blocks), dim3(256), 0, s, nq, n, kind, tb);
-  e = hipGetLastError();
+                        const NodeTables& tb, hipStream_t s, unsigned parts) {
+  if (nq > kMaxNodes || n > kMaxGrid) return hipErrorInvalidValue;
+  if (degree_tol > 0) parts = kTablesAll;
+  hipLaunchKernelGGL(tables_kernel, dim3(table_groups(nq, n, parts)), dim3(kNodeThreads), 0, s, omega, nq, n, L, kind,
+                     parts, tb);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess || !(degree_tol > 0)) return e;
   return launch_degrees(nq, n, kind, degree_tol, tb, s);
 }
 
 hipError_t launch_nodes_batch(const PrepMol* mols, int nmol, int nq, int n, int kind, bool any_degree,
                               hipStream_t s) {
-  hipLaunchKernelGGL(nodes_batch_kernel, dim3(1, nmol), dim3(kNodeThreads), 0, s, mols, nq, n, kind);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int64_t total = (int64_t)nq * n * n + gam_entries(n);
-  const int blocks = (int)((total + 255) / 256);
-  hipLaunchKernelGGL(ktables_batch_kernel, dim3(blocks, nmol), dim3(256), 0, s, mols, nq, n, kind);
-  e = hipGetLastError();
+  if (nq > kMaxNodes || n > kMaxGrid) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(tables_batch_kernel, dim3(table_groups(nq, n, kTablesAll), nmol), dim3(kNodeThreads), 0, s, mols,
+                     nq, n, kind);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess || !any_degree) return e;
   if (n > kDegMaxN) return hipErrorInvalidValue;
   hipLaunchKernelGGL(degrees_batch_kernel, dim3(nq, nmol), dim3(kDegThreads), 0, s, mols, n, kind);

@@ -659,7 +659,7 @@ int tai_quadrature(tai_ctx* c, const tai_params* p, double* t, double* w, double
   hipError_t e;
   {
     Timed tm(c, kStNodes, s);
-    e = tai::launch_nodes(p->omega, p->nq, p->n, p->L, p->nodes, p->degree_tol, tb, s);
+    e = tai::launch_nodes(p->omega, p->nq, p->n, p->L, p->nodes, p->degree_tol, tb, s, tai::kTablesK);
   }
   if (e != hipSuccess) return hip_fail(c, e, "nodes kernel");
   const size_t nq = p->nq, n = p->n;
@@ -682,7 +682,7 @@ int tai_degrees(tai_ctx* c, const tai_params* p, int32_t* nk, double* C, void* s
   hipError_t e;
   {
     Timed tm(c, kStNodes, s);
-    e = tai::launch_nodes(p->omega, p->nq, p->n, p->L, p->nodes, 0.0, tb, s);
+    e = tai::launch_nodes(p->omega, p->nq, p->n, p->L, p->nodes, 0.0, tb, s, tai::kTablesAll);
     if (e == hipSuccess) e = tai::launch_degrees(p->nq, p->n, p->nodes, p->degree_tol, tb, s);
   }
   if (e != hipSuccess) return hip_fail(c, e, "degrees kernel");
@@ -714,7 +714,7 @@ int tai_compress(tai_ctx* c, const double* M, int32_t npair, const tai_params* p
     if ((r = ensure(c, c->nodes, tai::node_tables_bytes(p->nq, p->n)))) return r;
     tb = tai::carve_node_tables(c->nodes.p, p->nq, p->n);
     Timed tm(c, kStNodes, s);
-    e = tai::launch_nodes(p->omega, p->nq, p->n, p->L, p->nodes, p->degree_tol, tb, s);
+    e = tai::launch_nodes(p->omega, p->nq, p->n, p->L, p->nodes, p->degree_tol, tb, s, tai::kTablesK);
     if (e != hipSuccess) return hip_fail(c, e, "nodes kernel");
   }
   // U goes straight to the caller, unless its address is no place for doubles or
@@ -758,7 +758,7 @@ int tai_apply_J_compressed(tai_ctx* c, const double* U, int32_t nb, const int32_
   hipError_t e;
   {
     Timed tm(c, kStNodes, s);
-    e = tai::launch_nodes(p->omega, nq, p->n, p->L, p->nodes, 0.0, tb, s);  // the weights w_k
+    e = tai::launch_nodes(p->omega, nq, p->n, p->L, p->nodes, 0.0, tb, s, tai::kTablesNodes);  // the weights w_k
   }
   if (e != hipSuccess) return hip_fail(c, e, "nodes kernel");
   NodeTables tbp = tb;
@@ -879,7 +879,7 @@ int tai_moments_partitioned(tai_ctx* c, const tai_basis* b, const tai_params* p,
   {
     // the node map of the moments does not depend on the box
     Timed tm(c, kStNodes, s);
-    e = tai::launch_nodes(p->omega, p->nq, p->n, boxes[nparts - 1], p->nodes, 0.0, tb, s);
+    e = tai::launch_nodes(p->omega, p->nq, p->n, boxes[nparts - 1], p->nodes, 0.0, tb, s, tai::kTablesGam);
   }
   if (e != hipSuccess) return hip_fail(c, e, "nodes kernel");
   {
@@ -957,7 +957,7 @@ int tai_assemble_B_partitioned(tai_ctx* c, const double* M, const int32_t* count
   hipError_t e;
   {
     Timed tm(c, kStNodes, s);
-    e = tai::launch_nodes(p->omega, nq, n, boxes[nparts - 1], p->nodes, 0.0, tb, s);
+    e = tai::launch_nodes(p->omega, nq, n, boxes[nparts - 1], p->nodes, 0.0, tb, s, tai::kTablesNodes);
     if (e == hipSuccess) e = tai::launch_cross_tables(tb.t, nq, n, p->nodes, bx, Kx, s);
   }
   if (e != hipSuccess) return hip_fail(c, e, "node kernels");
@@ -1103,7 +1103,7 @@ int tai_apply_J_partitioned(tai_ctx* c, const double* M, int32_t nb, const int32
   {
     Timed tm(c, kStNodes, s);
     // t_k, w_k (the plain tables on the largest box are not used)
-    e = tai::launch_nodes(p->omega, nq, n, boxes[nparts - 1], p->nodes, 0.0, tb, s);
+    e = tai::launch_nodes(p->omega, nq, n, boxes[nparts - 1], p->nodes, 0.0, tb, s, tai::kTablesNodes);
     if (e == hipSuccess) e = tai::launch_cross_tables(tb.t, nq, n, p->nodes, bx, Kx, s);
   }
   if (e != hipSuccess) return hip_fail(c, e, "node kernels");
@@ -1126,7 +1126,7 @@ static int moments_impl(tai_ctx* c, const tai_basis* b, const tai_params* p, con
   NodeTables tb = tai::carve_node_tables(c->nodes.p, p->nq, p->n);
   {
     Timed tm(c, kStNodes, s);
-    e = tai::launch_nodes(p->omega, p->nq, p->n, p->L, p->nodes, 0.0, tb, s);  // the moments need no K tables
+    e = tai::launch_nodes(p->omega, p->nq, p->n, p->L, p->nodes, 0.0, tb, s, tai::kTablesGam);  // the moments need no K tables
   }
   if (e != hipSuccess) return hip_fail(c, e, "nodes kernel");
   {
@@ -1202,7 +1202,7 @@ static int prepare_operands(tai_ctx* c, const double* M, int64_t npair, const ta
   hipError_t e;
   {
     Timed tm(c, kStNodes, s);
-    e = tai::launch_nodes(p->omega, p->nq, p->n, p->L, p->nodes, p->degree_tol, *tb, s);
+    e = tai::launch_nodes(p->omega, p->nq, p->n, p->L, p->nodes, p->degree_tol, *tb, s, tai::kTablesK);
   }
   if (e != hipSuccess) return hip_fail(c, e, "nodes kernel");
   *Mop = M;
@@ -1668,7 +1668,7 @@ int tai_apply_J_noalloc(tai_ctx* c, const double* M, int32_t nb, const tai_param
   char* base = static_cast<char*>(c->scratch);
   NodeTables tb = tai::carve_node_tables(base, nq, n);
   tai::JWork w = tai::carve_j_work(base + tab, p->prec, nq, n, (int)npair);
-  hipError_t e = tai::launch_nodes(p->omega, nq, n, p->L, p->nodes, p->degree_tol, tb, s);
+  hipError_t e = tai::launch_nodes(p->omega, nq, n, p->L, p->nodes, p->degree_tol, tb, s, tai::kTablesK);
   if (e != hipSuccess) return hip_fail(c, e, "nodes kernel");
   e = tai::launch_apply_j(p->prec, M, nb, (int)npair, nullptr, n, nq, tb, D, J, w, s);
   if (e != hipSuccess) return hip_fail(c, e, "apply_J kernels");

@@ -27,10 +27,12 @@ struct NodeTables {
 size_t node_tables_bytes(int nq, int n);
 NodeTables carve_node_tables(void* base, int nq, int n);
 
-// Nodes, weights, Chebyshev nodes and K tables; with degree_tol > 0 also the
-// per-node degrees, after which K holds the truncated tables (launch_degrees).
+// The tables a call reads: t, w and xi; K with them; gam.
+constexpr unsigned kTablesNodes = 1, kTablesK = 2, kTablesGam = 4, kTablesAll = kTablesK | kTablesGam;
+// Those tables; with degree_tol > 0 all of them and the per-node degrees, after
+// which K holds the truncated tables (launch_degrees).
 hipError_t launch_nodes(double omega, int nq, int n, double L, int kind, double degree_tol,
-                        const NodeTables& tb, hipStream_t s);
+                        const NodeTables& tb, hipStream_t s, unsigned parts);
 // Per-node degree (eq. chebcheb with N_k points for node k): C_k, N_k, and,
 // for degree_tol > 0, K_k replaced by the node values of the kept part.
 // Needs the tables of launch_nodes.
