@@ -410,32 +410,50 @@ size_t opY_bytes(int prec, int n, int nq, int prow) {
 }
 size_t opEx_bytes(int prow) { return align256(sizeof(int32_t) * 3 * (size_t)prow); }
 
-// Work items of the 16-bit assembly kernel for one molecule: row panels of
-// Work items of the 16-bit kernel: (molecule, row panel of R rows, run of up
-// to 512 columns in blocks of C), upper triangle only.  Column runs are
+// Work items of the persistent kernels: (molecule, row panel of R rows, run of
+// up to 512 columns in blocks of C), upper triangle only.  Column runs are
 // dealt round-robin to the kAsm16Queues queues (one per XCD; `rr` carries
 // the deal across molecules), each queue ordered column-run-major so that
 // the work groups of an XCD share the Y blocks of a run in its L2.
 struct Items16 {
   std::vector<int4> q[tai::kAsm16Queues];
   int rr = 0;
-  // Items of (row panel, run of column blocks) in the upper triangle, with
-  // runs of up to 512 columns.  With min_items > 0 the runs are halved
-  // until there are at least that many items (or one block per item), so
-  // that a small molecule still spreads over the device; the entries and
-  // the order of every entry's node sum do not depend on the runs.
-  void add(int mol, int64_t npair, int64_t R, int64_t C, int64_t min_items = 0) {
+  // Blocks per run, up to `cap` columns.  With slots > 0 (a molecule that is to
+  // spread over that many work groups) the run of 2^-i times that which takes the
+  // fewest block times: rounds over the slots times (run + a quarter of a block to
+  // load the row operand).  Runs halved until there were two items to a slot left
+  // most of the last round idle: whole calls, F16X3 n = 32, 8515 pairs 594 us, now
+  // 556; BF16X6 n = 40 1459, 1256; BF16X3 n = 48, 20100 pairs 4518, 4050 (half a
+  // block, or an eighth: within 3% of these, but 7% worse at 2080 or 8515 pairs).
+  // The entries and the order of every entry's node sum do not depend on the runs.
+  template <class Count>
+  static int64_t run_of(int64_t C, int64_t cap, int64_t slots, Count count) {
+    int64_t chunk = std::max<int64_t>(1, cap / C), best = chunk;
+    if (slots <= 0) return chunk;
+    double least = 0.0;
+    for (bool first = true;; first = false) {
+      const int64_t n = count(chunk);
+      const double t = (double)((n + slots - 1) / slots) * ((double)chunk + 0.25);
+      if (first || t < least) {
+        least = t;
+        best = chunk;
+      }
+      if (chunk == 1 || n > 16 * slots) return best;
+      chunk = (chunk + 1) / 2;
+    }
+  }
+  // Items of (row panel, run of column blocks) in the upper triangle.
+  void add(int mol, int64_t npair, int64_t R, int64_t C, int64_t slots = 0, int64_t cap = 512) {
     const int64_t ncb = (npair + C - 1) / C;
     const int64_t nrp = (npair + R - 1) / R;
-    int64_t chunk = std::max<int64_t>(1, 512 / C);
-    auto items_for = [&](int64_t ch) {
+    const int64_t chunk = run_of(C, cap, slots, [&](int64_t ch) {
       int64_t n = 0;
-      for (int64_t j = 0; j * ch < ncb; ++j)
-        for (int64_t rp = 0; rp < nrp; ++rp)
-          n += std::max(j * ch, rp * R / C) < std::min((j + 1) * ch, ncb) ? 1 : 0;
+      for (int64_t j = 0; j * ch < ncb; ++j) {
+        const int64_t hi = std::min((j + 1) * ch, ncb);
+        n += std::min(nrp, (hi * C - 1) / R + 1);  // panels with rp R / C < hi
+      }
       return n;
-    };
-    while (chunk > 1 && items_for(chunk) < min_items) chunk = (chunk + 1) / 2;
+    });
     for (int64_t j = 0; j * chunk < ncb; ++j) {
       std::vector<int4>& out = q[rr++ % tai::kAsm16Queues];
       for (int64_t rp = 0; rp < nrp; ++rp) {
@@ -447,11 +465,10 @@ struct Items16 {
   }
   // Items of a rectangular block (nrow rows against ncol columns, every
   // entry): all (row panel, run of column blocks), runs as in add.
-  void add_rect(int mol, int64_t nrow, int64_t ncol, int64_t R, int64_t C, int64_t min_items = 0) {
+  void add_rect(int mol, int64_t nrow, int64_t ncol, int64_t R, int64_t C, int64_t slots = 0) {
     const int64_t ncb = (ncol + C - 1) / C;
     const int64_t nrp = (nrow + R - 1) / R;
-    int64_t chunk = std::max<int64_t>(1, 512 / C);
-    while (chunk > 1 && ((ncb + chunk - 1) / chunk) * nrp < min_items) chunk = (chunk + 1) / 2;
+    const int64_t chunk = run_of(C, 512, slots, [&](int64_t ch) { return (ncb + ch - 1) / ch * nrp; });
     for (int64_t j = 0; j * chunk < ncb; ++j) {
       std::vector<int4>& out = q[rr++ % tai::kAsm16Queues];
       for (int64_t rp = 0; rp < nrp; ++rp)
@@ -1008,13 +1025,14 @@ int tai_assemble_B_partitioned(tai_ctx* c, const double* M, const int32_t* count
   const tai::Asm16Shape sh = p16 ? shape16(c, prec, n, nq) : tai::Asm16Shape{};
   const int64_t R = p16 ? sh.rows : ring_rows(prec, n), Cc = p16 ? sh.cols : tai::kAsm32Cols;
   const int64_t slots = (int64_t)(c->cus > 0 ? c->cus : 256) * (p16 ? sh.wgs_per_cu : 1);
+  const int64_t share = std::max<int64_t>(1, slots / (int64_t)am.size());
   TilePlan tp;
   if (tiles)
     tp = plan_tiles(c, prec, tai::operand_kc(prec, n), am.data(), (int)am.size(),
                     [](const tai::AsmMol&) { return true; });
   for (size_t k = 0; k < am.size() && !tiles; ++k) {
-    if (am[k].rect) items.add_rect((int)k, am[k].npair, am[k].ncol, R, Cc, 2 * slots / (int64_t)am.size());
-    else items.add((int)k, am[k].npair, R, Cc, 2 * slots / (int64_t)am.size());
+    if (am[k].rect) items.add_rect((int)k, am[k].npair, am[k].ncol, R, Cc, share);
+    else items.add((int)k, am[k].npair, R, Cc, share);
   }
   const size_t mol_bytes = align256(sizeof(tai::AsmMol) * am.size());
   const size_t tab_bytes = mol_bytes + items.bytes();
@@ -1288,8 +1306,8 @@ static int assemble_impl(tai_ctx* c, const double* M, int32_t npair, const tai_p
     Items16 items;
     const tai::Asm16Shape sh = p16 ? shape16(c, prec, n, nq) : tai::Asm16Shape{};
     const int64_t slots = (int64_t)(c->cus > 0 ? c->cus : 256) * (p16 ? sh.wgs_per_cu : 1);
-    if (p16) items.add(0, npair, sh.rows, sh.cols, 2 * slots);
-    else items.add(0, npair, ring_rows(prec, n), tai::kAsm32Cols, 2 * slots);
+    if (p16) items.add(0, npair, sh.rows, sh.cols, slots);
+    else items.add(0, npair, ring_rows(prec, n), tai::kAsm32Cols, slots);
     const size_t tab_bytes = align256(sizeof(tai::AsmMol)) + items.bytes();
     if ((r = ensure(c, c->asm_tab, tab_bytes))) return r;
     if ((r = ensure(c, c->asm_counter, 256))) return r;
@@ -1449,10 +1467,18 @@ static int batched_impl(tai_ctx* c, int32_t nmol, const tai_mol* mols, hipStream
     std::vector<int> order(nmol);
     for (int i = 0; i < nmol; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return am[a].npair > am[b].npair; });
-    const int kc = tai::operand_kc(prec, n);
-    for (int i : order)
-      if (!use_tiles(prec, n, am[i].npair))
-        items16.add(i, am[i].npair, split16 ? sh16.rows : ring_rows(prec, n), split16 ? sh16.cols : tai::kAsm32Cols);
+    // runs of 512 columns for the first four fifths of the entries, then of 128:
+    // the last items are what the work groups end on (64 molecules of 20 .. 120
+    // functions, n = 32, F16X3: 6600 us, 6270 with the short runs)
+    double entries = 0.0, dealt = 0.0;
+    for (const tai::AsmMol& m : am)
+      if (!use_tiles(prec, n, m.npair)) entries += (double)m.npair * m.npair;
+    for (int i : order) {
+      if (use_tiles(prec, n, am[i].npair)) continue;
+      items16.add(i, am[i].npair, split16 ? sh16.rows : ring_rows(prec, n), split16 ? sh16.cols : tai::kAsm32Cols, 0,
+                  dealt < 0.8 * entries ? 512 : 128);
+      dealt += (double)am[i].npair * am[i].npair;
+    }
   }
   // small molecules' tiles, in the tile kernel's own numbering (a batch takes
   // either the persistent kernels or the generic one, so tile0 serves both)
