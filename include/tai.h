@@ -244,7 +244,8 @@ typedef struct {
    molecules share nq, n, nodes and prec, each has its own omega, L, basis,
    M and B): one launch per preparation stage (nodes, moments, operand
    packing, projection) covering all molecules, then ONE persistent assembly
-   launch whose work groups drain a queue of (molecule, tile) items.  With a non-NULL stream the
+   launch whose work groups drain a queue of (molecule, tile) items (FP64 and
+   FP32: and one launch for the molecules of few pairs).  With a non-NULL stream the
    kernel sequence is recorded once into a HIP graph and replayed while the
    batch description (sizes, parameters, M/B pointers) is unchanged; the
    bases themselves are uploaded on every call.  Setting the environment
