@@ -1615,6 +1615,10 @@ static int batched_impl(tai_ctx* c, int32_t nmol, const tai_mol* mols, hipStream
                    c->b_counter.p, c->b_cmp.p};
   put(bases, sizeof bases);
   put(&sh16.id, sizeof sh16.id);
+  // the kernels taken (TAI_TILE_ASSEMBLY may change between calls, and with it the
+  // numbering in tile0) and the tiles' launch
+  put(&fp32p, sizeof fp32p);
+  put(&tp, sizeof tp);
   if (!c->graph || key != c->graph_key) {
     if (c->graph) {
       hipGraphExecDestroy(c->graph);

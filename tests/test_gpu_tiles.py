@@ -87,3 +87,38 @@ def test_batch_of_both_kernels(tai, prec):
     tai.context().assemble_B_batched(mols)
     for (_, B), S in zip(bufs, single):
         assert torch.equal(B, S)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_recorded_batch_and_the_generic_kernels(tai, prec, monkeypatch):
+    """A batch that is recorded and replayed on a stream, with the generic kernels
+    asked for in between: each call records what it takes."""
+    import torch
+    mols, bufs, keep, ref = [], [], [], []
+    for nb in (9, 20, 3):
+        b = _shells(nb)
+        P = I.Params(omega=0.4, nq=5, n=24, L=8.0)
+        ba = tai.BasisArrays(b)
+        M = torch.empty((3, P.n, b.npair), dtype=torch.float64, device="cuda")
+        B = torch.zeros((b.npair, b.npair), dtype=torch.float64 if prec == 0 else torch.float32, device="cuda")
+        keep.append(ba)
+        bufs.append((M, B))
+        mols.append(tai.tai_mol(ba.struct, tai.make_params(P, prec), M.data_ptr(), B.data_ptr(), b.npair))
+        ref.append(tai.assemble_B(tai.moments(b, P), P, prec=prec))
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    for generic in (False, False, True, True, False):
+        if generic:
+            monkeypatch.setenv("TAI_TILE_ASSEMBLY", "1")
+        else:
+            monkeypatch.delenv("TAI_TILE_ASSEMBLY", raising=False)
+        for _, B in bufs:
+            B.zero_()
+        torch.cuda.synchronize()
+        tai.context().assemble_B_batched(mols, stream=s)
+        torch.cuda.synchronize()
+        for (_, B), R in zip(bufs, ref):
+            if generic:
+                assert float((B - R).abs().max()) <= TOL[prec] * float(R.abs().max())
+            else:
+                assert torch.equal(B, R)
