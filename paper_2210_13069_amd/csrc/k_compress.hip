@@ -300,25 +300,30 @@ __device__ __forceinline__ void jacobi_body(const double* __restrict__ G, int n,
   __shared__ double2 rcs[2 * kHalf];         // (c, s) of the rotations of a round
   __shared__ int order[NMAX];
   __shared__ int rotated[3];                 // whether sweep s rotated, at s % 3
-  __shared__ double floor_abs;
+  __shared__ double trace;
   const int m = n + (n & 1), half = m / 2;
   const int tid = threadIdx.x;
+  if (tid == 0) {
+    double tr = 0.0;
+    for (int i = 0; i < n; ++i) tr += fabs(G[i * n + i]);
+    trace = tr;
+  }
+  __syncthreads();
+  // G 4^-h, its trace in [1/4, 1): the squares below stay in range for moments of
+  // any size, with the same digits, and sigma is scaled back by 2^h.  A trace that
+  // is zero or no finite number leaves G as it is.
+  const double tr = trace;
+  const int ex = tr > 0.0 && tr < INFINITY ? ilogb(tr) + 1 : 0, h = (ex + (ex & 1)) / 2;
+  const double floor_v = fmax(floor_rel * ldexp(tr, -2 * h), 1e-290), rel2 = rel * rel;
   // index = slot before the first round and after every sweep
   for (int e = tid; e < S; e += kJacobiThreads) Q[kBuf + e] = 0.0;
   for (int e = tid; e < m * m; e += kJacobiThreads) {
     const int i = e / m, j = e % m;
-    A[i * S + j] = (i < n && j < n) ? G[i * n + j] : 0.0;
+    A[i * S + j] = (i < n && j < n) ? ldexp(G[i * n + j], -2 * h) : 0.0;
     Q[i * S + j] = i == j ? 1.0 : 0.0;
   }
   if (tid < 3) rotated[tid] = 0;
   __syncthreads();
-  if (tid == 0) {
-    double tr = 0.0;
-    for (int i = 0; i < n; ++i) tr += fabs(A[i * S + i]);
-    floor_abs = fmax(floor_rel * tr, 1e-290);
-  }
-  __syncthreads();
-  const double floor_v = floor_abs, rel2 = rel * rel;
   // the rotation by theta that zeroes A'(p, q): tan 2 theta = y / x with
   // x = aqq - app, y = 2 apq, |theta| <= pi / 4; C = cos 2 theta gives
   // cos^2 theta = (1 + C) / 2, sin theta = sin 2 theta / (2 cos theta).  The
@@ -502,7 +507,7 @@ __device__ __forceinline__ void jacobi_body(const double* __restrict__ G, int n,
     const int a = e / n, r = e % n;
     V[a * n + r] = Q[a * S + order[r]];
   }
-  if (tid < n) sigma[tid] = sqrt(fmax(Ac[order[tid] * S + order[tid]], 0.0));
+  if (tid < n) sigma[tid] = ldexp(sqrt(fmax(Ac[order[tid] * S + order[tid]], 0.0)), h);
 }
 
 template <int NMAX>

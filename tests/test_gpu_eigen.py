@@ -54,3 +54,20 @@ def test_operands_over_the_moments(tai):
     flat = M.reshape(-1)
     assert tai.context().compress(M, NPAIR, P, U=flat) == R
     assert torch.equal(flat[:3 * Rp * NPAIR].view(3, Rp, NPAIR), U)
+
+
+@pytest.mark.parametrize("n", [5, 33, 64])
+@pytest.mark.parametrize("exponent", [-333, -260, 260, 333])
+def test_scale_of_the_moments(tai, n, exponent):
+    """Moments times a power of two, to 1e-100 and 1e100, give the same basis and
+    rank and singular values times it, bit for bit: no step leaves the range of a
+    double (the smallest product, of two values of the last singular vector, is
+    1e-15 of the largest)."""
+    import torch
+    M = torch.as_tensor(_array(n, "full"), device="cuda")
+    P = I.Params(omega=0.4, nq=8, n=n, L=8.0, rank_tol=1e-4)
+    rank, sigma, V = tai.compress(M, P)
+    got_rank, got_sigma, got_V = tai.compress(M * 2.0 ** exponent, P)
+    assert got_rank == rank
+    assert torch.equal(got_V, V)
+    assert np.array_equal(np.ldexp(got_sigma.cpu().numpy(), -exponent), sigma.cpu().numpy())
