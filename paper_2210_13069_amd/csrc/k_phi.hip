@@ -82,13 +82,15 @@ __device__ inline double parity_lanes(double v, int bits, bool mid0, bool mid1, 
 // its waves; npb work groups per tensor.  out may be part when nparts = 1.
 template <int WAVES>
 __global__ void __launch_bounds__(64 * WAVES)
-parity_sum_kernel(const double* part, int nparts, int64_t ystride, int64_t gstride, int n, int npb, double* out) {
+parity_sum_kernel(const double* part, int nparts, int64_t ystride, int64_t gstride, int n, int npb, int64_t batch,
+                  double* out) {
   __shared__ double s_sum[WAVES][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, bits = lane & 7;
   const int he = (n + 1) / 2;
   const int64_t n3 = (int64_t)n * n * n, npoint = (int64_t)he * he * he;
-  const int64_t y = blockIdx.x / npb;
-  const int64_t pt = (blockIdx.x - y * npb) * 8 + (lane >> 3);
+  const int64_t blk = grid_block(), y = blk / npb;
+  if (y >= batch) return;
+  const int64_t pt = (blk - y * npb) * 8 + (lane >> 3);
   const int a2 = (int)(pt % he), a1 = (int)(pt / he % he), a0 = (int)(pt / ((int64_t)he * he));
   const bool m0 = 2 * a0 == n - 1, m1 = 2 * a1 == n - 1, m2 = 2 * a2 == n - 1;
   const bool in = pt < npoint && !((bits & 1) && m0) && !((bits & 2) && m1) && !((bits & 4) && m2);
@@ -114,10 +116,10 @@ parity_sum_kernel(const double* part, int nparts, int64_t ystride, int64_t gstri
   if (in) out[y * n3 + at] = v;
 }
 
-// Phi in parity form for n <= 32 (H4 = ceil(ceil(n/2) / 4)).  Grid (2 T, 1, G):
-// the work group of eight waves takes the four octants with sigma_0 =
-// blockIdx.x % 2 of tensor t = blockIdx.x / 2, in LDS, wave w octant w % 4; waves
-// w and w + 4 take the run's nodes in turn.  Run z = blockIdx.z takes source
+// Phi in parity form for n <= 32 (H4 = ceil(ceil(n/2) / 4)).  Grid: rows of 2 T, by
+// G along z.  Work group b of eight waves takes the four octants with sigma_0 = b % 2
+// of tensor t = b / 2, in LDS, wave w octant w % 4; waves w and w + 4 take the run's
+// nodes in turn.  Run z = blockIdx.z takes source
 // z / kruns (X[(t nsrc + source) % xmod], tables K + (t nsrc + source) kstride,
 // weights w + source nq) and its share of the nodes.  Per node and a0:
 //   U = X(a0) K_2^T     H4 MFMAs, X from LDS, the rows a1 and columns i2;
@@ -139,8 +141,8 @@ parity_sum_kernel(const double* part, int nparts, int64_t ystride, int64_t gstri
 // instead of during V's MFMAs: 1157 us.
 template <int H4>
 __global__ void __launch_bounds__(512, 1)
-phi_octant_kernel(const double* __restrict__ X, int nsrc, int64_t xmod, const double* __restrict__ K, int64_t kstride,
-                  const double* __restrict__ w, int n, int nq, int kruns, double* __restrict__ Phi) {
+phi_octant_kernel(const double* __restrict__ X, int64_t T, int nsrc, int64_t xmod, const double* __restrict__ K,
+                  int64_t kstride, const double* __restrict__ w, int n, int nq, int kruns, double* __restrict__ Phi) {
   constexpr int HM = 4 * H4, XS = HM + 1, OCT = HM * HM * XS;
   constexpr int kRed = 64 * HM * H4;                     // doubles of one wave's sums
   constexpr int kLds = 4 * OCT > 4 * kRed ? 4 * OCT : 4 * kRed;
@@ -150,7 +152,8 @@ phi_octant_kernel(const double* __restrict__ X, int nsrc, int64_t xmod, const do
   const int r16 = lane & 15, kg = lane >> 4;
   const int he = (n + 1) / 2, ho = n / 2;
   const int64_t n2 = (int64_t)n * n, n3 = n2 * n;
-  const int64_t t = blockIdx.x >> 1;
+  const int64_t t = grid_block() >> 1;
+  if (t >= T) return;
   const int sg0 = blockIdx.x & 1, oct = wave & 3, sg1 = oct >> 1, sg2 = oct & 1, half = wave >> 2;
   const int h0 = sg0 ? ho : he, h1 = sg1 ? ho : he, h2 = sg2 ? ho : he;
   const int src = blockIdx.z / kruns, run = blockIdx.z - src * kruns;
@@ -248,7 +251,7 @@ phi_octant_kernel(const double* __restrict__ X, int nsrc, int64_t xmod, const do
       if ((i & 1) != half) red[64 * (i * H4 + r)] = W[i][r];
   __syncthreads();
   if (r16 >= h2) return;
-  double* out = Phi + ((int64_t)blockIdx.z * (gridDim.x >> 1) + t) * n3 + parity_position(n, sg2, r16);
+  double* out = Phi + ((int64_t)blockIdx.z * T + t) * n3 + parity_position(n, sg2, r16);
   const double c2 = 2 * r16 == n - 1 ? 1.0 : 0.5;
 #pragma unroll
   for (int r = 0; r < H4; ++r) {
@@ -285,10 +288,12 @@ hipError_t launch_parity_sum(const double* part, int nparts, int64_t ystride, in
                              double* out, hipStream_t s) {
   const int64_t he = (n + 1) / 2;
   const int npb = (int)nblk(he * he * he, 8);
-  const dim3 g((unsigned)(npb * batch));
+  const dim3 g = grid_rows(npb * batch);
   if (nparts == 1)
-    hipLaunchKernelGGL(parity_sum_kernel<1>, g, dim3(64), 0, s, part, nparts, ystride, gstride, n, npb, out);
-  else hipLaunchKernelGGL(parity_sum_kernel<4>, g, dim3(256), 0, s, part, nparts, ystride, gstride, n, npb, out);
+    hipLaunchKernelGGL(parity_sum_kernel<1>, g, dim3(64), 0, s, part, nparts, ystride, gstride, n, npb, batch,
+                       out);
+  else
+    hipLaunchKernelGGL(parity_sum_kernel<4>, g, dim3(256), 0, s, part, nparts, ystride, gstride, n, npb, batch, out);
   return hipGetLastError();
 }
 
@@ -302,10 +307,10 @@ hipError_t launch_phi_octants(const double* X, int64_t T, int nsrc, int64_t xmod
   kruns = std::max<int64_t>(1, std::min(kruns, part_len / (n3 * T * nsrc)));
   const int64_t G = nsrc * kruns;
   double* out = G > 1 ? part : Phi;
-  const dim3 g((unsigned)(2 * T), 1, (unsigned)G);
+  const dim3 g = grid_rows(2 * T, (unsigned)G);
   const int h4 = ((n + 1) / 2 + 3) / 4;
 #define TAI_OCT(H)                                                                                                     \
-  hipLaunchKernelGGL(phi_octant_kernel<H>, g, dim3(512), 0, s, X, nsrc, xmod, K, kstride, w, n, nq, (int)kruns, out)
+  hipLaunchKernelGGL(phi_octant_kernel<H>, g, dim3(512), 0, s, X, T, nsrc, xmod, K, kstride, w, n, nq, (int)kruns, out)
   if (h4 == 1) TAI_OCT(1);
   else if (h4 == 2) TAI_OCT(2);
   else if (h4 == 3) TAI_OCT(3);

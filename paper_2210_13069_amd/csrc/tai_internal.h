@@ -10,6 +10,16 @@ namespace tai {
 
 enum Prec { kFP64 = 0, kFP32 = 1, kBF16X3 = 2, kBF16X6 = 3, kF16X3 = 4 };
 
+// A grid of `blocks` work groups in rows along y.  A launch counts its threads along
+// x in 32 bits and drops what is beyond without an error, and a work group per
+// tensor or per few entries can pass that.  Their kernels take their number from
+// grid_block and return past the last one.
+constexpr int64_t kGridRow = int64_t(1) << 22;   // 2^31 threads at 512 a work group
+inline dim3 grid_rows(int64_t blocks, unsigned z = 1) {
+  return dim3((unsigned)(blocks < kGridRow ? blocks : kGridRow), (unsigned)((blocks + kGridRow - 1) / kGridRow), z);
+}
+__device__ inline int64_t grid_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 // Device-resident FP64 tables for one (omega, nq, n, L, nodes).
 struct NodeTables {
   double* t;     // [nq]      Gauss-Legendre nodes on (0, omega)

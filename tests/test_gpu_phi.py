@@ -74,3 +74,47 @@ def test_phi_truncated_tables(tai, n):
     D = I.random_density(np.random.default_rng(n), b)
     M = tai.moments(b, P)
     _close(tai.apply_J(M, torch.as_tensor(D, device=M.device), P).cpu().numpy(), T.J_grid(Mr, Kt, w, D))
+
+
+@pytest.mark.parametrize("prec,n,nb", [(0, 4, 4100), (1, 4, 4100), (1, 31, 140)])
+def test_exchange_beyond_one_grid(tai, prec, n, nb):
+    """1024 orbitals: 4.2 million tensors (n = 4: 1024 threads each in one launch),
+    and X and Phi of 64 GiB at an odd n (32^3 threads per 31^3 values), both past
+    2^32 threads.  Sampled entries against the equation in FP64 torch; FP32 to the
+    repository's 1e-6."""
+    import torch
+    dev, f64 = torch.device("cuda"), torch.float64
+    rng = torch.Generator(device=dev).manual_seed(5)
+    npair = nb * (nb + 1) // 2
+    M = torch.randn((3, n, npair), dtype=f64, device=dev, generator=rng)
+    Q = torch.randn((1024, nb), dtype=f64, device=dev, generator=rng) / np.sqrt(nb)
+    P = I.Params(omega=0.5, nq=2, n=n, L=6.0)
+    ctx = tai.Context(0)
+    Kx = torch.full((nb, nb), float("nan"), dtype=f64, device=dev)
+    ctx.exchange(M, nb, tai.make_params(P, prec), Q, 1024, Kx)
+    torch.cuda.synchronize()
+    ctx.close()
+    t, w = T.time_nodes(P.omega, P.nq)
+    K = torch.as_tensor(T.ktables(t, T.cheb_nodes(n, P.L)[0]), device=dev)
+
+    def grids(mu):
+        lam = torch.arange(nb, device=dev)
+        a, b = lam.clamp(max=mu), lam.clamp(min=mu)
+        m = M[:, :, a * nb - a * (a - 1) // 2 + (b - a)]
+        return (Q[:, None] * m[0]).reshape(1024 * n, nb) @ (m[1][:, None] * m[2]).reshape(n * n, nb).T.contiguous()
+
+    def phi(X):
+        out = torch.zeros_like(X)
+        for k in range(P.nq):
+            y = (X.view(-1, n) @ K[k]).view(-1, n, n).transpose(1, 2).reshape(-1, n) @ K[k]
+            y = y.view(-1, n, n, n).permute(0, 2, 3, 1).reshape(-1, n) @ K[k]   # (a2, a1, a0)
+            out += w[k] * y.view(-1, n, n, n).permute(0, 3, 2, 1).reshape(X.shape)
+        return out
+
+    assert bool(torch.isfinite(Kx).all()) and torch.equal(Kx, Kx.T)
+    scale = float(Kx.abs().max())
+    for mu in (0, nb // 2, nb - 1):
+        Phi = phi(grids(mu))
+        for nu in (0, 1, nb // 2, nb - 1):
+            ref = 4.0 / np.sqrt(np.pi) * float((grids(nu) * Phi).sum())
+            assert abs(float(Kx[mu, nu]) - ref) <= (1e-11 if prec == 0 else 1e-6) * scale
