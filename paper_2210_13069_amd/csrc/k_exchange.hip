@@ -708,11 +708,11 @@ sum_parts_kernel(const double* __restrict__ part, int nparts, int64_t len, doubl
 }
 
 // K(mu, nu) = K(nu, mu) = scale sum_s part[s][mu][nu], mu <= nu (the entries
-// of the upper tiles).
+// of the upper tiles); rows of the grid (grid_rows).
 __global__ void __launch_bounds__(kSumThreads)
 exch_dot_sum_kernel(const double* __restrict__ part, int nsplit, int nb, double scale, double* __restrict__ Kx) {
   const int64_t nn = (int64_t)nb * nb;
-  const int64_t i = (int64_t)blockIdx.x * kDotCols + threadIdx.x % kDotCols;
+  const int64_t i = grid_block() * kDotCols + threadIdx.x % kDotCols;
   const int64_t mu = i / nb, nu = i - mu * nb;
   const bool in = i < nn && mu <= nu;
   const double t = sum_column<kDotCols>(part + i, nsplit, nn, in);
@@ -790,8 +790,8 @@ hipError_t launch_dot_split(const double* X, const double* Phi, int nb, int norb
   const int nsplit = (int)(((int64_t)norb * n3 + slice - 1) / slice);
   const dim3 dg(nblk(nb, 64), nblk(nb, 64), nsplit);
   hipLaunchKernelGGL(exch_dot_kernel, dg, dim3(256), 0, s, X, Phi, nb, norb, n3, slice, part);
-  hipLaunchKernelGGL(exch_dot_sum_kernel, dim3(nblk((int64_t)nb * nb, kDotCols)), dim3(kSumThreads), 0, s, part, nsplit, nb,
-                     scale, Kx);
+  hipLaunchKernelGGL(exch_dot_sum_kernel, grid_rows(((int64_t)nb * nb + kDotCols - 1) / kDotCols), dim3(kSumThreads), 0,
+                     s, part, nsplit, nb, scale, Kx);
   return hipGetLastError();
 }
 

@@ -42,3 +42,38 @@ def test_pair_sum_parts(tai, natoms, n):
     M = tai.moments(b, P)
     got = tai.apply_J(M, torch.as_tensor(D, device=M.device), P).cpu().numpy()
     assert np.max(np.abs(got - ref)) <= 1e-11 * np.max(np.abs(ref))
+
+
+def test_exchange_of_many_functions(tai):
+    """11600 functions: 32 threads for each of nb^2 entries in the sum over the
+    slices, past 2^32.  Every entry is written, and sampled ones are the equation in
+    FP64 torch."""
+    import torch
+    dev, f64, nb, n = torch.device("cuda"), torch.float64, 11600, 2
+    rng = torch.Generator(device=dev).manual_seed(6)
+    M = torch.randn((3, n, nb * (nb + 1) // 2), dtype=f64, device=dev, generator=rng)
+    Q = torch.randn((1, nb), dtype=f64, device=dev, generator=rng) / np.sqrt(nb)
+    P = I.Params(omega=0.5, nq=2, n=n, L=6.0)
+    ctx = tai.Context(0)
+    Kx = torch.full((nb, nb), float("nan"), dtype=f64, device=dev)
+    ctx.exchange(M, nb, tai.make_params(P, tai.FP64), Q, 1, Kx)
+    torch.cuda.synchronize()
+    ctx.close()
+    t, w = T.time_nodes(P.omega, P.nq)
+    K = torch.as_tensor(T.ktables(t, T.cheb_nodes(n, P.L)[0]), device=dev)
+    W = sum(w[k] * torch.kron(torch.kron(K[k], K[k]), K[k]) for k in range(P.nq))
+
+    def grid(mu):
+        lam = torch.arange(nb, device=dev)
+        a, b = lam.clamp(max=mu), lam.clamp(min=mu)
+        m = M[:, :, a * nb - a * (a - 1) // 2 + (b - a)]
+        return (m[0][:, None, None] * m[1][:, None] * m[2]).reshape(n ** 3, nb) @ Q[0]
+
+    assert bool(torch.isfinite(Kx).all()) and torch.equal(Kx, Kx.T)
+    scale = float(Kx.abs().max())
+    rows = (0, 1, 5800, nb - 2, nb - 1)
+    X = {mu: grid(mu) for mu in rows}
+    for mu in rows:
+        for nu in rows:
+            ref = 4.0 / np.sqrt(np.pi) * float(X[mu] @ (W @ X[nu]))
+            assert abs(float(Kx[mu, nu]) - ref) <= 1e-11 * scale
