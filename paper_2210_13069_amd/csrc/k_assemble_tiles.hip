@@ -222,17 +222,18 @@ __device__ inline void run_tile(const AsmMol& m, int tr, int tc, double (*sums)[
 __device__ inline int xcd_tile(int b, int total) {
   const int per = (total + kXcds - 1) / kXcds;
   const int t = (b % kXcds) * per + b / kXcds;
-  return t < total ? t : -1;
+  return b < kXcds * per && t < total ? t : -1;
 }
 
 // One molecule (m), or a batch (mols): molecule i owns the tiles from its tile0 up
-// to the next one's (none of a molecule that the ring kernel takes).
+// to the next one's (none of a molecule that the ring kernel takes).  Rows of the
+// grid (grid_rows): the tiles of a batch with 70 GB of B pass 2^32 threads.
 template <class T, int KC, int RB>
 __global__ void __launch_bounds__(64 * kTileWaves, 2)
 assemble_tiles_kernel(AsmMol m, const AsmMol* __restrict__ mols, int nmol, int total) {
   __shared__ double sums[kTileWaves][16 * RB][17];
   __shared__ int exps[16 * RB + 16];
-  int t = xcd_tile(blockIdx.x, total);
+  int t = xcd_tile((int)grid_block(), total);
   if (t < 0) return;
   if (mols) {
     int lo = 0, hi = nmol - 1;  // the last molecule with tile0 <= t
@@ -262,7 +263,8 @@ constexpr int max_rb(int kc) { return sizeof(T) == 4 ? (kc <= 40 ? 4 : 2) : (kc 
 
 template <class T, int KC, int RB>
 hipError_t launch_one(const AsmMol& m, const AsmMol* mols_dev, int nmol, int total, hipStream_t s) {
-  const dim3 grid(kXcds * ((total + kXcds - 1) / kXcds)), block(64 * kTileWaves);
+  static_assert(kGridRow % kXcds == 0, "a work group's number gives its XCD in every row");
+  const dim3 grid = grid_rows((int64_t)kXcds * ((total + kXcds - 1) / kXcds)), block(64 * kTileWaves);
   hipLaunchKernelGGL((assemble_tiles_kernel<T, KC, RB>), grid, block, 0, s, m, mols_dev, nmol, total);
   return hipGetLastError();
 }

@@ -122,3 +122,25 @@ def test_recorded_batch_and_the_generic_kernels(tai, prec, monkeypatch):
                 assert float((B - R).abs().max()) <= TOL[prec] * float(R.abs().max())
             else:
                 assert torch.equal(B, R)
+
+
+def test_batch_beyond_one_grid(tai):
+    """22 molecules of 19900 pairs, FP64 at n = 41: 70 GB of B in 17 million tiles of
+    256 threads, past 2^32.  The same basis in each, so that every B is the bits of
+    a single call."""
+    import torch
+    b = _shells(199)
+    P = I.Params(omega=0.4, nq=4, n=41, L=7.0)
+    ba = tai.BasisArrays(b)
+    M = torch.empty((22, 3, P.n, b.npair), dtype=torch.float64, device="cuda")
+    B = torch.full((22, b.npair, b.npair), float("nan"), dtype=torch.float64, device="cuda")
+    single = tai.assemble_B(tai.moments(b, P), P)
+    ctx = tai.Context(0)
+    ctx.assemble_B_batched([tai.tai_mol(ba.struct, tai.make_params(P, 0), M[i].data_ptr(), B[i].data_ptr(), b.npair)
+                            for i in range(22)])
+    torch.cuda.synchronize()
+    ctx.close()
+    for i in range(22):
+        assert torch.equal(B[i], single)
+    del M, B
+    torch.cuda.empty_cache()
