@@ -327,7 +327,8 @@ bool use16(tai_ctx* c, int prec, int n, int nq) {
 // Whether FP32 / FP64 assembly takes the kernels of k_assemble_tiles.hip (few
 // pairs) and k_assemble32.hip (the persistent LDS ring), for the inner lengths
 // they are built for (both skip each node's unused inner steps with per-node
-// degrees).  TAI_TILE_ASSEMBLY selects the generic kernels instead.
+// degrees).  TAI_TILE_ASSEMBLY selects the generic kernels instead, and
+// TAI_RING_ASSEMBLY the ring for any number of pairs (use_tiles).
 bool use32(int prec, int n) {
   return (prec == tai::kFP32 || prec == tai::kFP64) && tai::operand_kc(prec, n) <= tai::kAsm32MaxKc &&
          !std::getenv("TAI_TILE_ASSEMBLY");
@@ -358,7 +359,7 @@ hipError_t launch_ring(int prec, int kc, bool /*deg*/, const tai::AsmMol* mols, 
 //         n = 48  5050 1158, 1063; 8515 2423, 2168; 20100 12843, 14854
 //         n = 64  2080 403, 359; 8515 2556, 2727
 bool use_tiles(int prec, int n, int64_t npair) {
-  if (!use32(prec, n)) return false;
+  if (!use32(prec, n) || std::getenv("TAI_RING_ASSEMBLY")) return false;
   const int kc = tai::operand_kc(prec, n);
   if (prec == tai::kFP64) return npair <= (kc <= 40 ? 40000 : (kc <= 48 ? 20000 : 0));
   return npair <= (kc <= 40 ? 24000 : (kc <= 48 ? 12000 : 6000));
@@ -1615,8 +1616,8 @@ static int batched_impl(tai_ctx* c, int32_t nmol, const tai_mol* mols, hipStream
                    c->b_counter.p, c->b_cmp.p};
   put(bases, sizeof bases);
   put(&sh16.id, sizeof sh16.id);
-  // the kernels taken (TAI_TILE_ASSEMBLY may change between calls, and with it the
-  // numbering in tile0) and the tiles' launch
+  // the kernels taken (TAI_TILE_ASSEMBLY and TAI_RING_ASSEMBLY may change between
+  // calls, and with them the numbering in tile0) and the tiles' launch
   put(&fp32p, sizeof fp32p);
   put(&tp, sizeof tp);
   if (!c->graph || key != c->graph_key) {
