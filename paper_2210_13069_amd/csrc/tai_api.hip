@@ -419,22 +419,29 @@ size_t opEx_bytes(int prow) { return align256(sizeof(int32_t) * 3 * (size_t)prow
 struct Items16 {
   std::vector<int4> q[tai::kAsm16Queues];
   int rr = 0;
+  // Time of an item's row operand, in blocks: that of 3 nodes of a block (FP64 and
+  // FP32: 2), and a quarter of a block at least.
+  double setup = 0.25;
+  void set_setup(bool split16, int nq) { setup = std::max(0.25, (split16 ? 3.0 : 2.0) / nq); }
   // Blocks per run, up to `cap` columns.  With slots > 0 (a molecule that is to
   // spread over that many work groups) the run of 2^-i times that which takes the
-  // fewest block times: rounds over the slots times (run + a quarter of a block to
-  // load the row operand).  Runs halved until there were two items to a slot left
-  // most of the last round idle: whole calls, F16X3 n = 32, 8515 pairs 594 us, now
-  // 556; BF16X6 n = 40 1459, 1256; BF16X3 n = 48, 20100 pairs 4518, 4050 (half a
-  // block, or an eighth: within 3% of these, but 7% worse at 2080 or 8515 pairs).
-  // The entries and the order of every entry's node sum do not depend on the runs.
+  // fewest block times: rounds over the slots times (run + setup).  Runs halved until
+  // there were two items to a slot left most of the last round idle: whole calls at
+  // 24 nodes, F16X3 n = 32, 8515 pairs 594 us, now 556; BF16X6 n = 40 1459, 1256;
+  // BF16X3 n = 48, 20100 pairs 4518, 4050.  A setup of a quarter of a block whatever
+  // the number of nodes made the runs too short where there are few: 8515 pairs, FP64
+  // n = 32 (the ring), one node 401 us, halved 351, now 311; BF16X6 n = 40, two
+  // nodes 353, 345, 266.  (Twice these setups, or no quarter: up to 9% worse at 8 to
+  // 16 nodes.)  The entries and the order of every entry's node sum do not
+  // depend on the runs.
   template <class Count>
-  static int64_t run_of(int64_t C, int64_t cap, int64_t slots, Count count) {
+  int64_t run_of(int64_t C, int64_t cap, int64_t slots, Count count) const {
     int64_t chunk = std::max<int64_t>(1, cap / C), best = chunk;
     if (slots <= 0) return chunk;
     double least = 0.0;
     for (bool first = true;; first = false) {
       const int64_t n = count(chunk);
-      const double t = (double)((n + slots - 1) / slots) * ((double)chunk + 0.25);
+      const double t = (double)((n + slots - 1) / slots) * ((double)chunk + setup);
       if (first || t < least) {
         least = t;
         best = chunk;
@@ -1031,6 +1038,7 @@ int tai_assemble_B_partitioned(tai_ctx* c, const double* M, const int32_t* count
   if (tiles)
     tp = plan_tiles(c, prec, tai::operand_kc(prec, n), am.data(), (int)am.size(),
                     [](const tai::AsmMol&) { return true; });
+  items.set_setup(p16, nq);
   for (size_t k = 0; k < am.size() && !tiles; ++k) {
     if (am[k].rect) items.add_rect((int)k, am[k].npair, am[k].ncol, R, Cc, share);
     else items.add((int)k, am[k].npair, R, Cc, share);
@@ -1307,6 +1315,7 @@ static int assemble_impl(tai_ctx* c, const double* M, int32_t npair, const tai_p
     Items16 items;
     const tai::Asm16Shape sh = p16 ? shape16(c, prec, n, nq) : tai::Asm16Shape{};
     const int64_t slots = (int64_t)(c->cus > 0 ? c->cus : 256) * (p16 ? sh.wgs_per_cu : 1);
+    items.set_setup(p16, nq);
     if (p16) items.add(0, npair, sh.rows, sh.cols, slots);
     else items.add(0, npair, ring_rows(prec, n), tai::kAsm32Cols, slots);
     const size_t tab_bytes = align256(sizeof(tai::AsmMol)) + items.bytes();

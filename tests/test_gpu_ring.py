@@ -2,7 +2,8 @@
 number of pairs) at every inner length, whole and padded, with and without per-node
 degrees, node counts below, at and beyond the FP32 sums' groups of 8, pairs that end
 inside a row panel and a column block; over boxes (rectangular blocks); and in
-batches, recorded and replayed.  Against the oracle and the tile kernels.
+batches, recorded and replayed; and all persistent kernels with few nodes, whose work
+items are longest.  Against the oracle, the tile kernels and FP64 torch.
 
 Tolerances are the repository's bars, normwise: FP64 1e-10, FP32 1e-6; ring against
 tiles 1e-13 and 1e-6 (the same terms in another order)."""
@@ -115,3 +116,24 @@ def test_batch_recorded_and_switched(tai, ring, prec):
         torch.cuda.synchronize()
         for B, S in zip(bufs, single):
             assert torch.equal(B, S)
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("nq", [1, 2, 3])
+def test_few_nodes(tai, ring, nq, prec):
+    """3003 and 5050 pairs: the longest runs of column blocks per work item."""
+    import torch
+    ring(True)
+    for nb, n in ((77, 16), (100, 24)):
+        b = _shells(nb)
+        P = I.Params(omega=0.5, nq=nq, n=n, L=7.0)
+        M = tai.moments(b, P)
+        t, w = T.time_nodes(P.omega, nq)
+        K = torch.as_tensor(T.ktables(t, T.cheb_nodes(n, P.L)[0]), device=M.device)
+        ref = torch.zeros((b.npair, b.npair), dtype=torch.float64, device=M.device)
+        for k in range(nq):
+            ref += w[k] * (M[0].T @ (K[k] @ M[0])) * (M[1].T @ (K[k] @ M[1])) * (M[2].T @ (K[k] @ M[2]))
+        ref *= 2.0 / np.sqrt(np.pi)
+        got = tai.assemble_B(M, P, prec=prec)
+        assert float((got - ref).abs().max()) <= {0: 1e-10, 2: 3e-5}.get(prec, 1e-6) * float(ref.abs().max())
+        assert torch.equal(got, got.T) or prec > 1
