@@ -347,22 +347,47 @@ hipError_t launch_ring(int prec, int kc, bool /*deg*/, const tai::AsmMol* mols, 
 }
 
 // Whether npair pairs take the tile kernel (k_assemble_tiles.hip) instead of the
-// ring: up to as many pairs as it was the faster of the two, by the inner length
-// of the call's own n (not of a compressed rank), so that a molecule takes the
-// same kernel alone, in a batch and as one box.  Whole calls, 24 nodes, ring
-// against tiles in us:
-//   FP64  n = 24  210 pairs 141, 86; 20100 12330, 10585; 39340 43776, 40178
-//         n = 40  2080 394, 295; 20100 19076, 17549; 39340 67791, 66594
-//         n = 48  5050 1970, 1610; 20100 23789, 23444; 39340 86747, 88845
-//         (beyond, the A operand leaves the tile one row block and too little room)
-//   FP32  n = 32  2080 272, 188; 20100 9761, 8499; 39340 29181, 32223
-//         n = 48  5050 1158, 1063; 8515 2423, 2168; 20100 12843, 14854
-//         n = 64  2080 403, 359; 8515 2556, 2727
-bool use_tiles(int prec, int n, int64_t npair) {
-  if (!use32(prec, n) || std::getenv("TAI_RING_ASSEMBLY")) return false;
-  const int kc = tai::operand_kc(prec, n);
-  if (prec == tai::kFP64) return npair <= (kc <= 40 ? 40000 : (kc <= 48 ? 20000 : 0));
-  return npair <= (kc <= 40 ? 24000 : (kc <= 48 ? 12000 : 6000));
+// ring.  By the call's own n (not a compressed rank) and nothing of its
+// surroundings, so that a molecule takes the same kernel, and gives the same bits,
+// alone, in a batch and as one box.
+//   A tile costs a fixed time beside its nodes (its row operand and the waves' last
+// sums, and whole rounds of its four waves over the nodes); the ring pads its pairs
+// to panels of 128 to 512 rows, and a single molecule of a few thousand pairs
+// leaves part of the device idle, which a batch does not.  The tiles are the
+// faster of the two from nq = q (npair - p0) / (npair + h) on, which is fitted so that
+// the ratios of a single call and of a batch of such molecules balance and the batch
+// is not slower than it was on the ring alone before.  Ring / tiles, whole
+// calls (single, batch of 64 of 2080, 24 of 5050 or 10 of 8515 pairs):
+//   FP64 n = 32  2080 pairs  nq 4 1.27, 0.73; 8 1.31, 0.92; 24 1.44, 1.13
+//                5050        nq 8 1.02, 0.83; 13 1.12, 0.96; 24 1.15, 1.04
+//                8515        nq 8 0.92, 0.81; 17 1.02, 0.98; 24 1.04, 1.03
+//                39340       nq 8 0.83; 18 1.00; 24 1.04; 128 1.08
+//        n = 48  2080        nq 8 1.19, 0.79; 17 1.21, 0.94; 5050 24 1.01, 0.96
+//   FP32 n = 40  2080        nq 4 1.34, 0.74; 8 1.40, 0.96; 24 1.52, 1.22
+//                5050        nq 8 1.00, 0.79; 13 1.08, 0.91; 24 1.12, 1.00
+//                8515        nq 17 1.00, 0.92; 24 1.02, 0.96; 20100 24 0.91
+//        n = 64  2080        nq 4 1.07, 0.60; 24 1.14, 0.89; 3003 24 0.97
+// Beyond `cap` pairs (and FP64 inner lengths past 48) the ring is the faster one
+// at any nq, or nothing was measured.  Nodes of per-node degrees or in a compressed
+// basis are shorter, a tile's fixed part is not (FP32, n = 40, degrees to 1e-8, 24
+// nodes: 5050 pairs 1.03, 8515 0.95): they count three quarters.
+bool use_tiles(const tai_params& p, int64_t npair) {
+  if (!use32(p.prec, p.n) || std::getenv("TAI_RING_ASSEMBLY")) return false;
+  const int kc = tai::operand_kc(p.prec, p.n);
+  struct Rule {
+    int kc, cap, q, p0, h;
+  };
+  static const Rule f64[] = {{8, 40000, 30, 400, 12000}, {16, 40000, 15, 400, 4500}, {24, 40000, 15, 400, 3000},
+                             {32, 40000, 21, 400, 2800}, {40, 40000, 23, 400, 3000}, {48, 20000, 36, 400, 1800}};
+  static const Rule f32[] = {{8, 24000, 24, 400, 14000}, {16, 24000, 34, 400, 12000}, {24, 24000, 38, 400, 9000},
+                             {40, 14000, 110, 400, 27000}, {64, 2500, 1300, 700, 140000}};
+  const int64_t nodes = p.degree_tol > 0 || p.rank_tol > 0 ? p.nq * 3 / 4 : p.nq;
+  auto take = [&](const Rule* r, int count) {
+    for (int i = 0; i < count; ++i)
+      if (kc <= r[i].kc) return npair <= r[i].cap && nodes * (npair + r[i].h) >= r[i].q * (npair - r[i].p0);
+    return false;
+  };
+  return p.prec == tai::kFP64 ? take(f64, 6) : take(f32, 5);
 }
 // Numbers the tiles (tile0) of the molecules that `take` names and picks their
 // row blocks: one while the larger tiles are less than two to a compute unit (528
@@ -952,7 +977,7 @@ int tai_assemble_B_partitioned(tai_ctx* c, const double* M, const int32_t* count
     return fail(c, TAI_ERR_UNSUPPORTED,
                 "tai_assemble_B_partitioned runs on the persistent kernels only (FP64 and FP32 up to their inner "
                 "length, the split 16-bit forms with a shape for nq)");
-  const bool tiles = use_tiles(prec, n, total);
+  const bool tiles = use_tiles(*p, total);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((r = ensure(c, c->nodes, tai::node_tables_bytes(nq, n)))) return r;
   NodeTables tb = tai::carve_node_tables(c->nodes.p, nq, n);
@@ -1263,7 +1288,7 @@ static int assemble_impl(tai_ctx* c, const double* M, int32_t npair, const tai_p
   // factors (Kc_k = V^T Kt_k V) and the operands are U, not moments: the
   // node form throughout.
   const bool deg = p->degree_tol > 0 && !tai::is_split16(prec) && !(p->rank_tol > 0);
-  const bool tiles = use_tiles(prec, p->n, npair);
+  const bool tiles = use_tiles(*p, npair);
   const int prow = prow_of(c, prec, n, nq, npair, tiles);
   if ((r = ensure(c, c->opA, opA_bytes(prec, n, prow)))) return r;
   if ((r = ensure(c, c->opEx, opEx_bytes(prow)))) return r;
@@ -1429,9 +1454,11 @@ static int batched_impl(tai_ctx* c, int32_t nmol, const tai_mol* mols, hipStream
   size_t sz_nodes = 0, sz_basis = 0, sz_A = 0, sz_Ex = 0, sz_Y = 0, sz_Mu = 0, sz_cmp = 0;
   int64_t nitems = 0;
   std::vector<tai::AsmMol> am(nmol);
+  std::vector<bool> tiled(nmol);  // molecules that take the tile kernel
   for (int i = 0; i < nmol; ++i) {
     const int64_t np = npair_of(mols[i].basis.nb);
-    prow[i] = prow_of(c, prec, n, nq, np, use_tiles(prec, n, np));
+    tiled[i] = use_tiles(mols[i].params, np);
+    prow[i] = prow_of(c, prec, n, nq, np, tiled[i]);
     off_nodes[i] = sz_nodes; sz_nodes += align256(tai::node_tables_bytes(nq, n));
     off_basis[i] = sz_basis; sz_basis += basis_bytes(mols[i].basis.nb);
     off_A[i] = sz_A; sz_A += opA_bytes(prec, n, prow[i]);
@@ -1481,10 +1508,10 @@ static int batched_impl(tai_ctx* c, int32_t nmol, const tai_mol* mols, hipStream
     // the last items are what the work groups end on (64 molecules of 20 .. 120
     // functions, n = 32, F16X3: 6600 us, 6270 with the short runs)
     double entries = 0.0, dealt = 0.0;
-    for (const tai::AsmMol& m : am)
-      if (!use_tiles(prec, n, m.npair)) entries += (double)m.npair * m.npair;
+    for (int i = 0; i < nmol; ++i)
+      if (!tiled[i]) entries += (double)am[i].npair * am[i].npair;
     for (int i : order) {
-      if (use_tiles(prec, n, am[i].npair)) continue;
+      if (tiled[i]) continue;
       items16.add(i, am[i].npair, split16 ? sh16.rows : ring_rows(prec, n), split16 ? sh16.cols : tai::kAsm32Cols, 0,
                   dealt < 0.8 * entries ? 512 : 128);
       dealt += (double)am[i].npair * am[i].npair;
@@ -1495,7 +1522,7 @@ static int batched_impl(tai_ctx* c, int32_t nmol, const tai_mol* mols, hipStream
   TilePlan tp;
   if (fp32p)
     tp = plan_tiles(c, prec, tai::operand_kc(prec, n), am.data(), nmol,
-                    [&](const tai::AsmMol& m) { return use_tiles(prec, n, m.npair); });
+                    [&](const tai::AsmMol& m) { return tiled[&m - am.data()]; });
   // device tables: [AsmMol x nmol | PrepMol x nmol | CmpMol x ncm | items]
   const size_t off_prep = align256(sizeof(tai::AsmMol) * nmol);
   int ncm = 0;

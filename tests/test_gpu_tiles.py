@@ -144,3 +144,29 @@ def test_batch_beyond_one_grid(tai):
         assert torch.equal(B[i], single)
     del M, B
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("prec,n,nq,nb,tiles", [(0, 32, 5, 64, False), (0, 32, 7, 64, False), (0, 32, 13, 64, True),
+                                                (0, 40, 13, 110, False), (0, 48, 9, 64, False), (0, 24, 6, 20, True),
+                                                (1, 40, 3, 64, False), (1, 40, 9, 64, True), (1, 64, 5, 64, False),
+                                                (1, 24, 13, 110, False)])
+def test_rule_and_node_counts(tai, prec, n, nq, nb, tiles, monkeypatch):
+    """With few nodes the ring, whose bits TAI_RING_ASSEMBLY shows (FP64: from five nodes
+    on, up to four are added in the same order); alone, in a batch and as one box a
+    molecule takes the same kernel."""
+    import torch
+    b = _shells(nb)
+    pairs, counts, boxes = tai.partition_pairs(b, 1e-16, 1)
+    P = I.Params(omega=0.4, nq=nq, n=n, L=boxes[0])
+    M = tai.moments(b, P)
+    got = tai.assemble_B(M, P, prec=prec)
+    ba = tai.BasisArrays(b)
+    Mb, Bb = torch.empty_like(M), torch.empty_like(got)
+    tai.context().assemble_B_batched([tai.tai_mol(ba.struct, tai.make_params(P, prec), Mb.data_ptr(), Bb.data_ptr(),
+                                                  b.npair)])
+    box = tai.assemble_B_partitioned(tai.moments_partitioned(b, P, pairs, counts, boxes), counts, boxes, P, prec=prec)
+    monkeypatch.setenv("TAI_RING_ASSEMBLY", "1")
+    ring = tai.assemble_B(M, P, prec=prec)
+    assert torch.equal(got, Bb) and torch.equal(got, box)
+    assert torch.equal(got, ring) == (not tiles)
+    assert float((got - ring).abs().max()) <= (1e-13 if prec == 0 else 1e-6) * float(ring.abs().max())
