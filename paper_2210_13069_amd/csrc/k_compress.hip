@@ -303,9 +303,18 @@ __device__ __forceinline__ void jacobi_body(const double* __restrict__ G, int n,
   __shared__ double trace;
   const int m = n + (n & 1), half = m / 2;
   const int tid = threadIdx.x;
+  // index = slot before the first round and after every sweep
+  for (int e = tid; e < S; e += kJacobiThreads) Q[kBuf + e] = 0.0;
+  for (int e = tid; e < m * m; e += kJacobiThreads) {
+    const int i = e / m, j = e % m;
+    A[i * S + j] = (i < n && j < n) ? G[i * n + j] : 0.0;
+    Q[i * S + j] = i == j ? 1.0 : 0.0;
+  }
+  if (tid < 3) rotated[tid] = 0;
+  __syncthreads();
   if (tid == 0) {
     double tr = 0.0;
-    for (int i = 0; i < n; ++i) tr += fabs(G[i * n + i]);
+    for (int i = 0; i < n; ++i) tr += fabs(A[i * S + i]);
     trace = tr;
   }
   __syncthreads();
@@ -315,14 +324,10 @@ __device__ __forceinline__ void jacobi_body(const double* __restrict__ G, int n,
   const double tr = trace;
   const int ex = tr > 0.0 && tr < INFINITY ? ilogb(tr) + 1 : 0, h = (ex + (ex & 1)) / 2;
   const double floor_v = fmax(floor_rel * ldexp(tr, -2 * h), 1e-290), rel2 = rel * rel;
-  // index = slot before the first round and after every sweep
-  for (int e = tid; e < S; e += kJacobiThreads) Q[kBuf + e] = 0.0;
   for (int e = tid; e < m * m; e += kJacobiThreads) {
-    const int i = e / m, j = e % m;
-    A[i * S + j] = (i < n && j < n) ? ldexp(G[i * n + j], -2 * h) : 0.0;
-    Q[i * S + j] = i == j ? 1.0 : 0.0;
+    double& a = A[e / m * S + e % m];
+    a = ldexp(a, -2 * h);
   }
-  if (tid < 3) rotated[tid] = 0;
   __syncthreads();
   // the rotation by theta that zeroes A'(p, q): tan 2 theta = y / x with
   // x = aqq - app, y = 2 apq, |theta| <= pi / 4; C = cos 2 theta gives
@@ -531,6 +536,7 @@ template <class F>
 void with_jacobi_class(int n, F&& f) {
   if (n <= 32) f(std::integral_constant<int, 32>{});
   else if (n <= 48) f(std::integral_constant<int, 48>{});
+  else if (n <= 56) f(std::integral_constant<int, 56>{});
   else f(std::integral_constant<int, kMaxN>{});
 }
 
