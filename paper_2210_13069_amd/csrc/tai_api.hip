@@ -475,18 +475,20 @@ struct Items16 {
       chunk = (chunk + 1) / 2;
     }
   }
-  // Items of (row panel, run of column blocks) in the upper triangle.
+  // Items of (row panel, run of `chunk` column blocks) in the upper triangle.
+  static int64_t triangle_items(int64_t npair, int64_t R, int64_t C, int64_t chunk) {
+    const int64_t ncb = (npair + C - 1) / C, nrp = (npair + R - 1) / R;
+    int64_t n = 0;
+    for (int64_t j = 0; j * chunk < ncb; ++j) {
+      const int64_t hi = std::min((j + 1) * chunk, ncb);
+      n += std::min(nrp, (hi * C - 1) / R + 1);  // panels with rp R / C < hi
+    }
+    return n;
+  }
   void add(int mol, int64_t npair, int64_t R, int64_t C, int64_t slots = 0, int64_t cap = 512) {
     const int64_t ncb = (npair + C - 1) / C;
     const int64_t nrp = (npair + R - 1) / R;
-    const int64_t chunk = run_of(C, cap, slots, [&](int64_t ch) {
-      int64_t n = 0;
-      for (int64_t j = 0; j * ch < ncb; ++j) {
-        const int64_t hi = std::min((j + 1) * ch, ncb);
-        n += std::min(nrp, (hi * C - 1) / R + 1);  // panels with rp R / C < hi
-      }
-      return n;
-    });
+    const int64_t chunk = run_of(C, cap, slots, [&](int64_t ch) { return triangle_items(npair, R, C, ch); });
     for (int64_t j = 0; j * chunk < ncb; ++j) {
       std::vector<int4>& out = q[rr++ % tai::kAsm16Queues];
       for (int64_t rp = 0; rp < nrp; ++rp) {
@@ -1510,10 +1512,20 @@ static int batched_impl(tai_ctx* c, int32_t nmol, const tai_mol* mols, hipStream
     double entries = 0.0, dealt = 0.0;
     for (int i = 0; i < nmol; ++i)
       if (!tiled[i]) entries += (double)am[i].npair * am[i].npair;
+    const int64_t R = split16 ? sh16.rows : ring_rows(prec, n), C = split16 ? sh16.cols : tai::kAsm32Cols;
+    // Shorter runs from the start where the ring would have fewer than two items to a
+    // compute unit (one of 25 molecules is left to it, 1653 pairs, FP64, n = 48, 12
+    // nodes: 2040 us in runs of 512, all on the ring 1270)
+    int64_t cap = 512;
+    for (int64_t items = 0; !split16 && cap > C; cap /= 2) {
+      items = 0;
+      for (int i = 0; i < nmol; ++i)
+        if (!tiled[i]) items += Items16::triangle_items(am[i].npair, R, C, cap / C);
+      if (items >= 2 * (int64_t)(c->cus > 0 ? c->cus : 256)) break;
+    }
     for (int i : order) {
       if (tiled[i]) continue;
-      items16.add(i, am[i].npair, split16 ? sh16.rows : ring_rows(prec, n), split16 ? sh16.cols : tai::kAsm32Cols, 0,
-                  dealt < 0.8 * entries ? 512 : 128);
+      items16.add(i, am[i].npair, R, C, 0, dealt < 0.8 * entries ? cap : std::min<int64_t>(cap, 128));
       dealt += (double)am[i].npair * am[i].npair;
     }
   }

@@ -170,3 +170,25 @@ def test_rule_and_node_counts(tai, prec, n, nq, nb, tiles, monkeypatch):
     assert torch.equal(got, Bb) and torch.equal(got, box)
     assert torch.equal(got, ring) == (not tiles)
     assert float((got - ring).abs().max()) <= (1e-13 if prec == 0 else 1e-6) * float(ring.abs().max())
+
+
+@pytest.mark.parametrize("prec,n,nbs", [(0, 48, (57, 12, 30, 41)), (1, 48, (75, 20, 33)), (0, 40, (60, 62, 9)),
+                                        (1, 24, (64, 30, 70, 2))])
+def test_batch_with_few_ring_molecules(tai, prec, n, nbs):
+    """The one or two largest molecules of a batch go to the ring, in runs short enough
+    to spread them over the device: the bits of single calls."""
+    import torch
+    mols, bufs, keep, single = [], [], [], []
+    for nb in nbs:
+        b = _shells(nb)
+        P = I.Params(omega=0.4, nq=6, n=n, L=8.0)
+        ba = tai.BasisArrays(b)
+        M = torch.empty((3, n, b.npair), dtype=torch.float64, device="cuda")
+        B = torch.empty((b.npair, b.npair + 1), dtype=torch.float64 if prec == 0 else torch.float32, device="cuda")
+        keep.append((ba, M))
+        bufs.append(B)
+        mols.append(tai.tai_mol(ba.struct, tai.make_params(P, prec), M.data_ptr(), B.data_ptr(), b.npair + 1))
+        single.append(tai.assemble_B(tai.moments(b, P), P, prec=prec))
+    tai.context().assemble_B_batched(mols)
+    for B, S in zip(bufs, single):
+        assert torch.equal(B[:, :-1], S)
