@@ -499,11 +499,14 @@ struct Items16 {
     }
   }
   // Items of a rectangular block (nrow rows against ncol columns, every
-  // entry): all (row panel, run of column blocks), runs as in add.
-  void add_rect(int mol, int64_t nrow, int64_t ncol, int64_t R, int64_t C, int64_t slots = 0) {
+  // entry): all (row panel, run of column blocks), runs of up to `cap` columns.
+  static int64_t rect_items(int64_t nrow, int64_t ncol, int64_t R, int64_t C, int64_t chunk) {
+    return ((ncol + C - 1) / C + chunk - 1) / chunk * ((nrow + R - 1) / R);
+  }
+  void add_rect(int mol, int64_t nrow, int64_t ncol, int64_t R, int64_t C, int64_t cap) {
     const int64_t ncb = (ncol + C - 1) / C;
     const int64_t nrp = (nrow + R - 1) / R;
-    const int64_t chunk = run_of(C, 512, slots, [&](int64_t ch) { return (ncb + ch - 1) / ch * nrp; });
+    const int64_t chunk = std::max<int64_t>(1, cap / C);
     for (int64_t j = 0; j * chunk < ncb; ++j) {
       std::vector<int4>& out = q[rr++ % tai::kAsm16Queues];
       for (int64_t rp = 0; rp < nrp; ++rp)
@@ -1060,15 +1063,26 @@ int tai_assemble_B_partitioned(tai_ctx* c, const double* M, const int32_t* count
   const tai::Asm16Shape sh = p16 ? shape16(c, prec, n, nq) : tai::Asm16Shape{};
   const int64_t R = p16 ? sh.rows : ring_rows(prec, n), Cc = p16 ? sh.cols : tai::kAsm32Cols;
   const int64_t slots = (int64_t)(c->cus > 0 ? c->cus : 256) * (p16 ? sh.wgs_per_cu : 1);
-  const int64_t share = std::max<int64_t>(1, slots / (int64_t)am.size());
   TilePlan tp;
-  if (tiles)
+  if (tiles) {
     tp = plan_tiles(c, prec, tai::operand_kc(prec, n), am.data(), (int)am.size(),
                     [](const tai::AsmMol&) { return true; });
-  items.set_setup(p16, nq);
-  for (size_t k = 0; k < am.size() && !tiles; ++k) {
-    if (am[k].rect) items.add_rect((int)k, am[k].npair, am[k].ncol, R, Cc, share);
-    else items.add((int)k, am[k].npair, R, Cc, share);
+  } else {
+    // One queue holds the items of every block, so one run serves them all (a run per
+    // block, for a share of the slots each: F16X3, n = 12, 24 nodes, 9045 pairs in two
+    // boxes 876 us, now 619)
+    items.set_setup(p16, nq);
+    const int64_t run = items.run_of(Cc, 512, slots, [&](int64_t chunk) {
+      int64_t count = 0;
+      for (const tai::AsmMol& m : am)
+        count += m.rect ? Items16::rect_items(m.npair, m.ncol, R, Cc, chunk)
+                        : Items16::triangle_items(m.npair, R, Cc, chunk);
+      return count;
+    });
+    for (size_t k = 0; k < am.size(); ++k) {
+      if (am[k].rect) items.add_rect((int)k, am[k].npair, am[k].ncol, R, Cc, run * Cc);
+      else items.add((int)k, am[k].npair, R, Cc, 0, run * Cc);
+    }
   }
   const size_t mol_bytes = align256(sizeof(tai::AsmMol) * am.size());
   const size_t tab_bytes = mol_bytes + items.bytes();
