@@ -348,7 +348,11 @@ __device__ inline void project_mfma_body(const ProjectArgs& p) {
 // sums and the differences of the moments at b and n-1-b go through
 // K(i, b) + K(n-1-i, b) and K(i, b) - K(n-1-i, b), both of half the size, and Y at
 // i and n-1-i is half the sum and half the difference of the two products: 8
-// instead of 16 MFMAs per wave and node at n = 32, 20 instead of 36 at n = 40.
+// instead of 16 MFMAs per wave and node at n = 32, 20 instead of 36 at n = 40.  Not
+// for n <= 16 (kMirroredNT), where it saves no MFMA and a small batch waits for its
+// longer chain at every node: two molecules of 10 and 45 pairs, 32 nodes, BF16X6
+// n = 3 103 us against 48, n = 16 61 and 53; FP64 33 and 31, at n = 24 39 and 56.
+constexpr int kMirroredNT = 2;
 template <int NT, int PREC>
 __device__ inline void project_mirrored_body(const ProjectArgs& p) {
   constexpr int H4 = 2 * NT, HT = (NT + 1) / 2;      // inner steps and column tiles of ceil(n / 2) <= 8 NT
@@ -938,6 +942,7 @@ project_kernel(ProjectArgs p, int nq) {
   const int per = (nq + (int)gridDim.z - 1) / (int)gridDim.z;
   p.k0 = (int)blockIdx.z * per;
   p.k1 = min(nq, p.k0 + per);
+  static_assert(!MIRRORED || NT >= kMirroredNT, "the mirrored form");
   if constexpr (MIRRORED) project_mirrored_body<NT, PREC>(p);
   else project_mfma_body<NT, PREC>(p);
 }
@@ -951,8 +956,10 @@ project_batch_kernel(const PrepMol* __restrict__ mols, int n, int nq, int kc) {
   // degrees: moments against T_j, kept coefficients), or the node form
   ProjectArgs p{m.U ? m.U : (m.Mu ? m.Mu : m.M), n,  m.npair, m.prow, 0, nq, kc,
                 m.U ? m.Kc : (m.Mu ? m.tb.C : m.tb.K), m.tb.w, m.ex, m.ysh, static_cast<char*>(m.Y)};
-  if (m.U || m.Mu) project_mfma_body<NT, PREC>(p);
-  else project_mirrored_body<NT, PREC>(p);
+  if constexpr (NT >= kMirroredNT) {
+    if (!m.U && !m.Mu) return project_mirrored_body<NT, PREC>(p);
+  }
+  project_mfma_body<NT, PREC>(p);
 }
 
 size_t project_lds(int prec, int n, bool mirrored) {
@@ -985,9 +992,13 @@ hipError_t launch_pack_t(int prec, const double* M, int n, int npair, int prow, 
 template <int NT, int PREC>
 hipError_t launch_project_p(const ProjectArgs& p, int nq, bool mirrored, hipStream_t s) {
   const dim3 g(p.prow / kRowsPerTile, 3, project_runs(p.prow, nq));
-  if (mirrored)
-    hipLaunchKernelGGL((project_kernel<NT, PREC, true>), g, dim3(256), project_lds(PREC, p.n, true), s, p, nq);
-  else hipLaunchKernelGGL((project_kernel<NT, PREC, false>), g, dim3(256), project_lds(PREC, p.n, false), s, p, nq);
+  if constexpr (NT >= kMirroredNT) {
+    if (mirrored) {
+      hipLaunchKernelGGL((project_kernel<NT, PREC, true>), g, dim3(256), project_lds(PREC, p.n, true), s, p, nq);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((project_kernel<NT, PREC, false>), g, dim3(256), project_lds(PREC, p.n, false), s, p, nq);
   return hipGetLastError();
 }
 
@@ -1016,7 +1027,7 @@ template <int NT, int PREC>
 hipError_t launch_project_batch_p(const PrepMol* mols, int nmol, int max_prow, int n, int nq, bool any_general,
                                   hipStream_t s) {
   hipLaunchKernelGGL((project_batch_kernel<NT, PREC>), dim3(max_prow / kRowsPerTile, 3, nmol), dim3(256),
-                     project_lds(PREC, n, !any_general), s, mols, n, nq, operand_kc(PREC, n));
+                     project_lds(PREC, n, NT >= kMirroredNT && !any_general), s, mols, n, nq, operand_kc(PREC, n));
   return hipGetLastError();
 }
 
