@@ -369,8 +369,11 @@ hipError_t launch_ring(int prec, int kc, bool /*deg*/, const tai::AsmMol* mols, 
 //        n = 64  2080        nq 4 1.07, 0.60; 24 1.14, 0.89; 3003 24 0.97
 // Beyond `cap` pairs (and FP64 inner lengths past 48) the ring is the faster one
 // at any nq, or nothing was measured.  Nodes of per-node degrees or in a compressed
-// basis are shorter, a tile's fixed part is not (FP32, n = 40, degrees to 1e-8, 24
-// nodes: 5050 pairs 1.03, 8515 0.95): they count three quarters.
+// basis are shorter by what only the device knows, a tile's fixed part is not (ring /
+// tiles, 24 nodes: FP32, n = 40, degrees to 1e-8, 5050 pairs 1.03, 8515 0.95; degrees
+// below 8, FP64, n = 40, 10731 pairs 0.91; n = 48, 32 nodes, a batch of 30 of 2080
+// pairs 0.8): degrees count as two inner chunks of 8, a compressed basis as three
+// quarters of n.
 bool use_tiles(const tai_params& p, int64_t npair) {
   if (!use32(p.prec, p.n) || std::getenv("TAI_RING_ASSEMBLY")) return false;
   const int kc = tai::operand_kc(p.prec, p.n);
@@ -381,7 +384,7 @@ bool use_tiles(const tai_params& p, int64_t npair) {
                              {32, 40000, 21, 400, 2800}, {40, 40000, 23, 400, 3000}, {48, 20000, 36, 400, 1800}};
   static const Rule f32[] = {{8, 24000, 24, 400, 14000}, {16, 24000, 34, 400, 12000}, {24, 24000, 38, 400, 9000},
                              {40, 14000, 110, 400, 27000}, {64, 2500, 1300, 700, 140000}};
-  const int64_t nodes = p.degree_tol > 0 || p.rank_tol > 0 ? p.nq * 3 / 4 : p.nq;
+  const int64_t nodes = p.rank_tol > 0 ? p.nq * 3 / 4 : (p.degree_tol > 0 ? p.nq * 16 / std::max(kc, 16) : p.nq);
   auto take = [&](const Rule* r, int count) {
     for (int i = 0; i < count; ++i)
       if (kc <= r[i].kc) return npair <= r[i].cap && nodes * (npair + r[i].h) >= r[i].q * (npair - r[i].p0);
