@@ -1530,15 +1530,17 @@ static int batched_impl(tai_ctx* c, int32_t nmol, const tai_mol* mols, hipStream
     for (int i = 0; i < nmol; ++i)
       if (!tiled[i]) entries += (double)am[i].npair * am[i].npair;
     const int64_t R = split16 ? sh16.rows : ring_rows(prec, n), C = split16 ? sh16.cols : tai::kAsm32Cols;
-    // Shorter runs from the start where the ring would have fewer than two items to a
-    // compute unit (one of 25 molecules is left to it, 1653 pairs, FP64, n = 48, 12
-    // nodes: 2040 us in runs of 512, all on the ring 1270)
+    // Shorter runs from the start where the ring would have fewer than eight items to
+    // a compute unit (two a node below four nodes: an item's row operand is the longer
+    // part there).  One of 25 molecules left to it, 1653 pairs, FP64, n = 48, 12 nodes:
+    // 2040 us in runs of 512, 1180; twenty of 210 to 5050 pairs, n = 40, 8 nodes: two
+    // items a unit 1.0, eight 1.15 of the speed with every molecule on the ring.
     int64_t cap = 512;
     for (int64_t items = 0; !split16 && cap > C; cap /= 2) {
       items = 0;
       for (int i = 0; i < nmol; ++i)
         if (!tiled[i]) items += Items16::triangle_items(am[i].npair, R, C, cap / C);
-      if (items >= 2 * (int64_t)(c->cus > 0 ? c->cus : 256)) break;
+      if (items >= 2 * std::min(nq, 4) * (int64_t)(c->cus > 0 ? c->cus : 256)) break;
     }
     for (int i : order) {
       if (tiled[i]) continue;
