@@ -1445,13 +1445,13 @@ hipError_t launch_coulomb_mo(int prec, const double* M, int nb, int npair, const
                              const NodeTables& tb, bool mirrored, const double* Q, int norb, int cus, void* work,
                              double* Jmo, const JWork& w, hipStream_t s) {
   const int64_t n3 = (int64_t)n * n * n;
-  const bool parity = mirrored && phi_octants(n, norb);
+  const int obmax = norb < kMoBlock ? norb : kMoBlock;
+  const bool parity = mirrored && phi_octants(n, obmax);   // obmax tensors a launch
   if (parity) {
     const hipError_t e = launch_parity_tables(tb.K, nq, n, s);
     if (e != hipSuccess) return e;
   }
   convert_moments(prec, M, n, npair, w, s);
-  const int obmax = norb < kMoBlock ? norb : kMoBlock;
   const int nc = mo_chunks(prec, n, npair, obmax, cus);
   char* p = static_cast<char*>(work);
   double* R = reinterpret_cast<double*>(p); p += align256(8 * n3 * norb);

@@ -272,7 +272,13 @@ phi_octant_kernel(const double* __restrict__ X, int64_t T, int nsrc, int64_t xmo
 // leaves the octants 24 work groups of one node per wave each: J at n = 32
 // 85 us against 76 with the slab kernels; two tensors 78 against 83, four 83
 // against 97, sixteen 117 against 145 (orbital J), 96 tensors 299 against 473.
-bool phi_octants(int n, int64_t tensors) { return n >= 3 && n <= kOctMaxN && tensors >= 2; }
+// For 9 <= n <= 13 an octant pads its 4 to 7 indices a side to 8, and many tensors,
+// which leave no latency to hide, are done sooner by the slab kernels (exchange, 32
+// nodes, slabs against octants: n = 9 64 tensors 1.41 of the time, 128 1.18, 400 0.71,
+// 800 0.67; n = 13 1.36, 1.03, 0.73, 0.95; n = 14 1.33, 1.05, 0.92, 1.05).
+bool phi_octants(int n, int64_t tensors) {
+  return n >= 3 && n <= kOctMaxN && tensors >= 2 && (n < 9 || n > 13 || tensors <= 256);
+}
 
 hipError_t launch_parity_moments(const double* M, int n, int64_t npair, double* Mp, hipStream_t s) {
   hipLaunchKernelGGL(parity_moments_kernel, dim3(nblk(npair, 256), (n + 1) / 2, 3), dim3(256), 0, s, M, n, npair, Mp);

@@ -76,6 +76,24 @@ def test_phi_truncated_tables(tai, n):
     _close(tai.apply_J(M, torch.as_tensor(D, device=M.device), P).cpu().numpy(), T.J_grid(Mr, Kt, w, D))
 
 
+@pytest.mark.parametrize("n", [8, 9, 13, 14])
+@pytest.mark.parametrize("norb", [16, 17])
+def test_both_sides_of_256_tensors(tai, n, norb):
+    """256 and 272 tensors: octants, and for 9 <= n <= 13 the slab products beyond 256."""
+    import torch
+    b = I.small_random(400 + n, natoms=4, shells=("s", "p"), box=3.0)
+    assert b.nb == 16
+    P = I.Params(omega=0.6, nq=5, n=n, L=7.0)
+    t, w = T.time_nodes(P.omega, P.nq)
+    K = T.ktables(t, T.cheb_nodes(n, P.L)[0])
+    Mr = T.moments(b.center, b.alpha, b.lxyz, P.L, n)
+    Q = np.random.default_rng(n).standard_normal((norb, b.nb))
+    M = tai.moments(b, P)
+    Qg = torch.as_tensor(Q, device=M.device)
+    _close(tai.exchange(M, b.nb, Qg, P).cpu().numpy(), T.exchange_grid(Mr, K, w, Q))
+    _close(tai.coulomb_mo(M, b.nb, Qg, P).cpu().numpy(), T.coulomb_mo(Mr, K, w, Q))
+
+
 @pytest.mark.parametrize("prec,n,nb", [(0, 4, 4100), (1, 4, 4100), (1, 31, 140)])
 def test_exchange_beyond_one_grid(tai, prec, n, nb):
     """1024 orbitals: 4.2 million tensors (n = 4: 1024 threads each in one launch),
