@@ -11,7 +11,7 @@
 //   waves.  A 512-byte operand fragment (8 inner indices) is two 256-byte
 //   pieces; a lane reads its two values, the operands of two MFMAs, at once.
 // * Per node the three G tiles are multiplied elementwise and accumulated in
-//   FP32; every kGroup32 nodes the FP32 sums are added into FP64 partial sums
+//   FP32; every few nodes (fp32_group) the FP32 sums are added into FP64 partial sums
 //   held in wave-private LDS.
 // * A finished column block leaves straight from registers: rows for
 //   row <= col, 16-byte mirrored columns for row < col.
@@ -42,8 +42,12 @@ constexpr double kTwoOverSqrtPi = 1.1283791670955126;
 __device__ inline __amdgpu_buffer_rsrc_t y_rsrc(const char* base) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), (short)0, 0x7fffffff, 0x00020000);
 }
-// FP32 accumulation group of quadrature nodes (as in the FP32 tile kernel)
-constexpr int kGroup32 = 8;
+// Nodes summed in FP32 before they go to FP64: a quarter of them, as many as a wave
+// of the tile kernel sums (k_assemble_tiles.hip), so that a molecule is as accurate on
+// either side of the rule between the two; at least 4, at most 8.  With 8 at any nq
+// the ring's Frobenius error was larger, 16 nodes 7.9e-8 against 7.0e-8, 24 nodes
+// 6.7e-8 against 6.4e-8.  (Down to 2 at 8 nodes: 4% slower, 9% at n = 16.)
+__device__ inline int fp32_group(int nq) { return min(8, max(4, (nq + 3) / 4)); }
 constexpr int kQueues = kAsm16Queues;
 constexpr int kNW32 = 8;  // waves per work group (two per SIMD)
 
@@ -230,6 +234,8 @@ __device__ inline void run_item32(const AsmMol& m, int rp, int cb0, int cb1, flo
   };
 
   int k = 0, blk = 0;  // (block, node) of the current step
+  const int group = fp32_group(nq);
+  int left = group;
   float* cur = yb0;
   float* nxt = yb1;
   for (int t = 0; t < T; ++t) {
@@ -267,7 +273,10 @@ __device__ inline void run_item32(const AsmMol& m, int rp, int cb0, int cb1, flo
     };
     if constexpr (DEG) with_steps<NCH / 2>(nch / 2, node);
     else node(std::integral_constant<int, NCH / 2>{});
-    if ((k + 1) % kGroup32 == 0 || k + 1 == nq) flush();
+    if (--left == 0 || k + 1 == nq) {
+      flush();
+      left = group;
+    }
     if (++k == nq) {
       finish_block(blk);
       k = 0;
