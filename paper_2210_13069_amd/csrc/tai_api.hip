@@ -383,7 +383,7 @@ bool use_tiles(const tai_params& p, int64_t npair) {
   static const Rule f64[] = {{8, 40000, 30, 400, 12000}, {16, 40000, 15, 400, 4500}, {24, 40000, 15, 400, 3000},
                              {32, 40000, 21, 400, 2800}, {40, 40000, 23, 400, 3000}, {48, 20000, 36, 400, 1800}};
   static const Rule f32[] = {{8, 24000, 24, 400, 14000}, {16, 24000, 34, 400, 12000}, {24, 24000, 38, 400, 9000},
-                             {40, 14000, 110, 400, 27000}, {64, 2500, 1300, 700, 140000}};
+                             {40, 14000, 110, 400, 27000}, {64, 2500, 1300, 600, 140000}};
   const int64_t nodes = p.rank_tol > 0 ? p.nq * 3 / 4 : (p.degree_tol > 0 ? p.nq * 16 / std::max(kc, 16) : p.nq);
   auto take = [&](const Rule* r, int count) {
     for (int i = 0; i < count; ++i)
