@@ -71,7 +71,7 @@ struct Cfg32 {
 // A builtin, not inline asm: the compiler has to see that the A operand's loads
 // have landed too, or it waits for every load in flight at their first use inside
 // the node loop.  (vmcnt 0, the other counters at their maximum.)  FP32, 24 nodes,
-// 80200 pairs: n = 40 163 -> 146 ms, n = 48 204 -> 184 ms.
+// 80200 pairs: n = 40 151 -> 147 ms, n = 48 242 -> 185 ms.
 __device__ inline void wait_vmcnt0() {
   __builtin_amdgcn_s_waitcnt(0x0f70);
   __asm__ volatile("" ::: "memory");

@@ -16,7 +16,8 @@
 //   What bounds it: the matrix cores (20100 pairs, 24 nodes: FP64 n = 40 66 TFLOP/s,
 // FP32 n = 40 110 TFLOP/s), and for a few hundred pairs the loads' latency once
 // through.  Moments and B, ring against tiles: 36 pairs, FP64, n = 24, 106 -> 60 us;
-// 2080, n = 32, 338 -> 239 us; 8515, FP32, n = 37 with degrees, 2588 -> 2300 us.
+// 2080, n = 32, 338 -> 239 us.  Which calls come here is use_tiles' rule
+// (tai_api.hip): by pairs and nodes, both kernels measured there.
 #include "tai_internal.h"
 
 #include <cmath>

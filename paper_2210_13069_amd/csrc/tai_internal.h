@@ -128,7 +128,7 @@ int operand_esize(int prec);
 int assemble_tile(int prec);
 
 struct AsmMol {
-  // operands (device): A[d][prow][kc], Y[k][d][prow][kc]; prow = padded rows
+  // operands (device): A[d], Y[k][d], each prow (padded rows) x kc in fragment order
   const void* A;
   const void* Y;
   const int32_t* ex;     // [3][prow] power-of-two exponents (zeros for FP64)
@@ -244,8 +244,8 @@ hipError_t launch_assemble64(int kc, bool deg, const AsmMol* mols_dev, const int
 
 // Few pairs, FP64 and FP32 (inner lengths up to kAsm32MaxKc): tiles of 16 * rb
 // rows by 16 columns with the nodes dealt to a work group's waves
-// (k_assemble_tiles.hip).  rb is 1, 2 or 4, up to asm_tiles_max_rb; the entries
-// do not depend on it.  The batch form reads each molecule's first tile from
+// (k_assemble_tiles.hip).  rb is 1 or asm_tiles_max_rb; the entries do not depend
+// on it.  The batch form reads each molecule's first tile from
 // tile0 (asm_tile_count tiles each, `total` in all).
 int asm_tile_count(const AsmMol& m, int rb);
 int asm_tiles_max_rb(int prec, int kc);
