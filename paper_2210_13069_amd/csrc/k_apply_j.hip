@@ -1102,7 +1102,7 @@ void launch_pair_contraction_rho(int prec, const MT* M, int n, int npair, int nc
 }  // namespace
 
 __global__ void __launch_bounds__(256) to_fp32_kernel(const double* __restrict__ x, int64_t count, float* __restrict__ y) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t i = grid_block() * blockDim.x + threadIdx.x;
   if (i < count) y[i] = (float)x[i];
 }
 
@@ -1239,7 +1239,7 @@ void launch_jp16(const float* M, int n, const int64_t* offs, int nspan, const do
 void convert_moments(int prec, const double* M, int n, int npair, const JWork& w, hipStream_t s) {
   if (prec != kFP32 && !split_j(prec)) return;
   const int64_t count = 3 * (int64_t)n * npair;
-  hipLaunchKernelGGL(to_fp32_kernel, dim3(nblk(count, 256)), dim3(256), 0, s, M, count, w.M32);
+  hipLaunchKernelGGL(to_fp32_kernel, grid_rows((count + 255) / 256), dim3(256), 0, s, M, count, w.M32);
 }
 
 // Phi = sum_k wsc_k rho x_0 K_k x_1 K_k x_2 K_k (wsc = (2/sqrt(pi)) w) on the

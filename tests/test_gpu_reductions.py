@@ -77,3 +77,23 @@ def test_exchange_of_many_functions(tai):
         for nu in rows:
             ref = 4.0 / np.sqrt(np.pi) * float(X[mu] @ (W @ X[nu]))
             assert abs(float(Kx[mu, nu]) - ref) <= 1e-11 * scale
+
+
+@pytest.mark.parametrize("prec", ["FP32", "BF16X6"])
+def test_fp32_copy_beyond_one_grid(tai, prec):
+    """7730 functions at n = 48: the moments' FP32 copy is past 2^32 values.  J against
+    the FP64 form, relative 2-norm to the repository's 1e-6."""
+    import torch
+    dev, f64, nb, n = torch.device("cuda"), torch.float64, 7730, 48
+    assert 3 * n * (nb * (nb + 1) // 2) > 2 ** 32
+    rng = torch.Generator(device=dev).manual_seed(7)
+    M = torch.randn((3, n, nb * (nb + 1) // 2), dtype=f64, device=dev, generator=rng)
+    D = torch.randn((nb, nb), dtype=f64, device=dev, generator=rng)
+    P = I.Params(omega=0.5, nq=2, n=n, L=6.0)
+    J = [torch.full((nb, nb), float("nan"), dtype=f64, device=dev) for _ in range(2)]
+    ctx = tai.Context(0)
+    for out, pr in zip(J, (tai.FP64, getattr(tai, prec))):
+        ctx.apply_J(M, nb, tai.make_params(P, pr), D, out)
+        torch.cuda.synchronize()
+    ctx.close()
+    assert float((J[1] - J[0]).norm() / J[0].norm()) <= 1e-6
